@@ -27,7 +27,8 @@
 //          wave holds gate and up outputs of the same (row, column) in the
 //          same lane: the SwiGLU epilogue is register-local. H is bf16.
 //   GEMM2: Y = H W2^T, bf16.
-// f32 (exact path for float32 layers): 64 x 64 FMA tiles, same work table.
+// f32 (exact path for float32 layers): gemm_rm_kernel on the float32 matrix
+// instructions, same work table.
 #include <type_traits>
 
 #include "common.h"
@@ -40,8 +41,8 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kGroupM = 8;  // m-tiles per super-row in the work order
 
-// f32 FMA tiles
-constexpr int FBM = 64, FBNB = 64, FBK = 16;
+// rows per tile of the row-major matrix tiles (gemm_rm_kernel)
+constexpr int FBM = 64;
 
 struct ExpWs {
     void* h_r;   // [R, inter]
@@ -1006,123 +1007,46 @@ __global__ void pack_weights_kernel(const uint16_t* __restrict__ src, int batch,
     }
 }
 
-// ============================================================== f32 FMA path
-
-template <int MODE>
-__global__ void __launch_bounds__(kThreads)
-gemm_f32_kernel(GemmArgs p) {
-    __shared__ float As[FBK][FBM + 4];
-    __shared__ float Bs[FBK][FBNB + 4];
-    __shared__ float Cs[FBM][FBNB + 1];
-    const int nt_r = MODE == 1 ? static_cast<int>(ceil_div(p.inter, 32)) : static_cast<int>(ceil_div(p.d, 64));
-    const int nt_s = MODE == 1 ? static_cast<int>(ceil_div(p.shared_inter, 32)) : nt_r;
-    Tile t;
-    if (!decode_tile(p.work, p.off, p.E, p.T, FBM, nt_r, nt_s, p.part, t)) return;
-    const bool shared = t.g == p.E;
-    const int tid = threadIdx.x;
-    int K, n_out;
-    const float* Abase;
-    const float* Bbase;
-    int64_t a_ld;
-    if constexpr (MODE == 1) {
-        K = p.d;
-        n_out = shared ? p.shared_inter : p.inter;
-        Abase = static_cast<const float*>(p.x);
-        a_ld = p.d;
-        Bbase = shared ? static_cast<const float*>(p.ws13)
-                       : static_cast<const float*>(p.w13) + static_cast<int64_t>(t.g) * 2 * p.inter * p.d;
-    } else {
-        K = shared ? p.shared_inter : p.inter;
-        n_out = p.d;
-        Abase = shared ? static_cast<const float*>(p.h_s) : static_cast<const float*>(p.h_r);
-        a_ld = K;
-        Bbase = shared ? static_cast<const float*>(p.ws2)
-                       : static_cast<const float*>(p.w2) + static_cast<int64_t>(t.g) * p.d * p.inter;
-    }
-    // loaders: 64 rows x 16 k per tile, 4 elements per thread
-    const int lr = tid >> 2;         // row 0..63
-    const int lk = (tid & 3) * 4;    // k 0,4,8,12
-    const int rr = lr < t.rows ? lr : 0;
-    int64_t asrc;
-    if (MODE == 1 && !shared) asrc = p.perm_token[t.row0 + rr];
-    else asrc = t.row0 + rr;
-    const float* arow = Abase + asrc * a_ld;
-    int64_t bidx;
-    if constexpr (MODE == 1) {
-        int c = t.nt * 32 + (lr & 31);
-        if (c >= n_out) c = 0;
-        bidx = lr < 32 ? c : n_out + c;
-    } else {
-        int c = t.nt * 64 + lr;
-        if (c >= n_out) c = 0;
-        bidx = c;
-    }
-    const float* brow = Bbase + bidx * K;
-    const int ty = tid >> 4, tx = tid & 15;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += FBK) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int kk = k0 + lk + q;
-            As[lk + q][lr] = kk < K ? arow[kk] : 0.0f;
-            Bs[lk + q][lr] = kk < K ? brow[kk] : 0.0f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < FBK; ++kk) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) Cs[ty * 4 + i][tx * 4 + j] = acc[i][j];
-    __syncthreads();
-    if constexpr (MODE == 1) {
-        float* H = shared ? static_cast<float*>(p.h_s) : static_cast<float*>(p.h_r);
-        for (int q = tid; q < FBM * 32; q += kThreads) {
-            const int r = q / 32, c = q % 32;
-            const int col = t.nt * 32 + c;
-            if (r < t.rows && col < n_out)
-                H[(t.row0 + r) * n_out + col] = silu(Cs[r][c]) * Cs[r][32 + c];
-        }
-    } else {
-        float* Y = shared ? static_cast<float*>(p.y_s) : static_cast<float*>(p.y_r);
-        for (int q = tid; q < FBM * FBNB; q += kThreads) {
-            const int r = q / FBNB, c = q % FBNB;
-            const int col = t.nt * 64 + c;
-            if (r < t.rows && col < n_out) Y[(t.row0 + r) * n_out + col] = Cs[r][c];
-        }
-    }
-}
-
-// ============================================================== f32 FMA backward
-
-// Backward of fp32 layers and of bf16 layers whose weights are row-major: the
-// same contractions as the forward's f32 tiles (64 x 64 outputs per block, 4 x 4
-// per thread, K steps of 16 through LDS), with float32 intermediates. Steps:
-//   GB_AB   [A | B] = X W13^T          rows: routed rows (x gathered) / tokens
+// ============================================================== row-major matrix tiles
+//
+// Float32 layers (forward and backward) and the backward of bf16 layers whose
+// weights are row-major. Products and sums are float32: float32 operands run
+// on v_mfma_f32_32x32x2_f32. A bf16 layer runs on v_mfma_f32_32x32x16_bf16: its
+// own tensors (x, dout, the weights) are exact bf16 operands, and a float32
+// intermediate (dA dB, w H) enters as three bf16 terms cut off its mantissa (8
+// bits each: their sum is the float32 value), so every product is exact and
+// only the float32 accumulation rounds, as on the vector ALUs. Steps:
+//   RM_FW1  H = silu(X W1^T) * (X W3^T)          rows: routed rows (x gathered) / tokens
+//   RM_FW2  Y = H W2^T
+//   GB_AB   [A | B] = X W13^T
 //   GB_DH   dH = w dout W2, then the SwiGLU backward: dA, dB and w H
 //   GB_DX   dX = [dA dB] W13
 //   GB_DW2  dW2[n][c]  = sum over the group's rows of dout[tok][n] (w H)[c]
 //   GB_DW13 dW13[m][n] = sum over the group's rows of [dA dB][m] x[tok][n]
-// Row steps take their tiles from the work table (decode_tile, both parts);
-// weight steps run one block per (output tile, group), group E the shared
-// experts. An expert without rows gets a zero gradient.
-enum { GB_AB = 0, GB_DH = 1, GB_DX = 2, GB_DW2 = 3, GB_DW13 = 4 };
+// Row steps take their tiles from the work table (decode_tile); weight steps
+// run one block per (output tile, group), group E the shared experts. An
+// expert without rows gets a zero gradient.
+//
+// Tiles: 64 indices of the F operand (the one that may be float32 in a bf16
+// layer) x 64 or 128 of the H operand, 4 waves of 32 x 32 NH. A K step is eight
+// 16-byte chunks per index (64 bf16 or 32 float32): each thread loads its
+// chunks of both operands into registers one step ahead, turns an operand
+// whose memory runs along the index into chunks along K, and writes them to
+// the other of two LDS buffers while the current one is multiplied: one
+// barrier per step. In a float32 layer the matrix cores bound a tile (64
+// cycles per 4096 flops), and 64 x 64 gives small layers enough tiles; in a
+// bf16 layer the LDS reads do (four fragments per three products at 64 x 64,
+// five per six at 64 x 128, hence NH = 2).
+// Against float32 vector-ALU tiles (64 x 64, K steps of 16): at 1000 tokens x
+// 1024, 16 experts of 512, top-4, one shared, row-major bf16, GB_AB / DH / DX /
+// DW2 / DW13 343 / 177 / 264 / 151 / 228 -> 28 / 35 / 59 / 57 / 90 us; the
+// forward of the 512 x 256 float32 layer with 8 experts of 512, top-2, 44 + 58
+// -> 17 + 16 us.
+enum { GB_AB = 0, GB_DH = 1, GB_DX = 2, GB_DW2 = 3, GB_DW13 = 4, RM_FW1 = 5, RM_FW2 = 6 };
 
-struct GenBwdArgs {
+struct RmArgs {
     int64_t T;
-    int d, E, inter, shared_inter;
+    int d, E, inter, shared_inter, part;
     const int32_t* off;
     const int32_t* perm_token;
     const int32_t* work;
@@ -1132,6 +1056,10 @@ struct GenBwdArgs {
     const void* w2;    // [E][d][inter]
     const void* ws13;  // [2 shared_inter][d]
     const void* ws2;   // [d][shared_inter]
+    float* h_r;        // [R][inter] (RM_FW1 writes, RM_FW2 reads)
+    float* h_s;        // [T][shared_inter]
+    float* y_r;        // [R][d]
+    float* y_s;        // [T][d]
     float* ab_r;       // [R][2 inter]
     float* ab_s;       // [T][2 shared_inter]
     float* dab_r;
@@ -1147,182 +1075,376 @@ struct GenBwdArgs {
     void* dws2;
 };
 
-template <bool BF16>
-__device__ __forceinline__ float ldv(const void* p, int64_t i) {
-    if constexpr (BF16) return bf16_to_f32(static_cast<const uint16_t*>(p)[i]);
-    else return static_cast<const float*>(p)[i];
-}
+// H indices per tile: 128 for bf16 operands, 64 for float32
+__host__ __device__ constexpr int rm_nh(bool bf16) { return bf16 ? 2 : 1; }
 
 // output column tiles of a row step for a group with n_out inner columns
-__host__ __device__ __forceinline__ int gb_row_tiles(int mode, int n_out, int d) {
-    return static_cast<int>(ceil_div(mode == GB_AB ? 2 * n_out : mode == GB_DH ? n_out : d, FBNB));
+__host__ __device__ __forceinline__ int rm_row_tiles(int mode, int n_out, int d, bool bf16) {
+    if (mode == RM_FW1) return static_cast<int>(ceil_div(n_out, 32));  // 32 gate + 32 up rows
+    return static_cast<int>(ceil_div(mode == GB_AB ? 2 * n_out : mode == GB_DH ? n_out : d, 64 * rm_nh(bf16)));
 }
 
+// vector loads at the alignment of one element (rows start at multiples of 8
+// elements, the tensors themselves wherever the caller put them)
+template <bool B16>
+struct RmVec {
+    typedef uint32_t v1 __attribute__((aligned(4)));
+    typedef uint32_t v2 __attribute__((ext_vector_type(2), aligned(4)));
+    typedef uint32_t v4 __attribute__((ext_vector_type(4), aligned(4)));
+};
+template <>
+struct RmVec<true> {
+    typedef uint32_t v1 __attribute__((aligned(2)));
+    typedef uint32_t v2 __attribute__((ext_vector_type(2), aligned(2)));
+    typedef uint32_t v4 __attribute__((ext_vector_type(4), aligned(2)));
+};
+template <bool B16, int N>
+__device__ __forceinline__ void rm_load_words(const void* p, uint32_t (&w)[N]) {
+    if constexpr (N == 1) {
+        w[0] = *static_cast<const typename RmVec<B16>::v1*>(p);
+    } else if constexpr (N == 2) {
+        const auto v = *static_cast<const typename RmVec<B16>::v2*>(p);
+        w[0] = v.x;
+        w[1] = v.y;
+    } else {
+        static_assert(N % 4 == 0, "whole 16-byte loads");
+#pragma unroll
+        for (int i = 0; i < N / 4; ++i) {
+            const auto v = static_cast<const typename RmVec<B16>::v4*>(p)[i];
+            w[4 * i] = v.x;
+            w[4 * i + 1] = v.y;
+            w[4 * i + 2] = v.z;
+            w[4 * i + 3] = v.w;
+        }
+    }
+}
+
+// One operand's share of a thread: NC chunks of CK elements along K.
+//   SRC16: bf16 in memory (else float32). KC: memory runs along K (row pointers
+//   fixed, K moves), else along the index (CK rows of NC adjacent indices).
+//   P: bf16 terms a float32 element is cut into (0: it stays float32).
+template <bool SRC16, bool KC, int NC, int CK, int P>
+struct RmOperand {
+    static constexpr int OUTER = KC ? NC : CK;                       // separately addressed pieces
+    static constexpr int WORDS = (KC ? CK : NC) * (SRC16 ? 2 : 4) / 4;  // 32-bit words of a piece
+    static constexpr int PLANES = SRC16 || P == 0 ? 1 : P;
+    uint32_t raw[OUTER][WORDS];
+
+    static __device__ __forceinline__ int lds_row(int u) {
+        return KC ? static_cast<int>(threadIdx.x >> 3) + 32 * u : NC * static_cast<int>(threadIdx.x & 31) + u;
+    }
+    static __device__ __forceinline__ int lds_chunk() { return KC ? threadIdx.x & 7 : threadIdx.x >> 5; }
+
+    // zero the elements whose K index (this thread's chunk starts at kk) is past K
+    __device__ __forceinline__ void cut(int kk, int K) {
+#pragma unroll
+        for (int o = 0; o < OUTER; ++o)
+#pragma unroll
+            for (int w = 0; w < WORDS; ++w)
+                if ((KC ? kk : kk + o) >= K) raw[o][w] = 0;  // K % 8 == 0 where memory runs along it
+    }
+    // chunks of plane q of plane_bytes each, row pitch 128 bytes, swizzled
+    __device__ __forceinline__ void put(uint8_t* base, int plane_bytes) const {
+        const int c = lds_chunk();
+#pragma unroll
+        for (int u = 0; u < NC; ++u) {
+            const int R = lds_row(u);
+            uint8_t* dst = base + R * 128 + ((c ^ (((R >> 1) ^ (R >> 4)) & 7)) * 16);
+            if constexpr (SRC16) {
+                uint32_t o[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if constexpr (KC) o[i] = raw[u][i];
+                    else o[i] = __builtin_amdgcn_perm(raw[2 * i + 1][u / 2], raw[2 * i][u / 2], u & 1 ? 0x07060302 : 0x05040100);
+                }
+                *reinterpret_cast<uint4*>(dst) = make_uint4(o[0], o[1], o[2], o[3]);
+            } else if constexpr (P == 0) {
+                uint32_t o[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) o[i] = KC ? raw[u][i] : raw[i][u];
+                *reinterpret_cast<uint4*>(dst) = make_uint4(o[0], o[1], o[2], o[3]);
+            } else {
+                // hi = the upper 16 bits, then the same of the exact remainders; an
+                // infinity keeps its first term alone
+                uint32_t o[3][4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    uint32_t t0[2], t1[2], t2[2];
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const int e = 2 * i + h;
+                        const uint32_t v = KC ? raw[u][e] : raw[e][u];
+                        t0[h] = v;
+                        float r = __uint_as_float(v) - __uint_as_float(v & 0xffff0000u);
+                        r = (v & 0x7fffffffu) == 0x7f800000u ? 0.0f : r;
+                        t1[h] = __float_as_uint(r);
+                        t2[h] = __float_as_uint(r - __uint_as_float(t1[h] & 0xffff0000u));
+                    }
+                    o[0][i] = __builtin_amdgcn_perm(t0[1], t0[0], 0x07060302);
+                    o[1][i] = __builtin_amdgcn_perm(t1[1], t1[0], 0x07060302);
+                    o[2][i] = __builtin_amdgcn_perm(t2[1], t2[0], 0x07060302);
+                }
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+                    *reinterpret_cast<uint4*>(dst + q * plane_bytes) = make_uint4(o[q][0], o[q][1], o[q][2], o[q][3]);
+            }
+        }
+    }
+};
+
 template <int MODE, bool BF16>
-__global__ void __launch_bounds__(kThreads)
-gemm_f32_bwd_kernel(GenBwdArgs p) {
-    __shared__ __align__(16) float As[FBK][FBM + 4];
-    __shared__ __align__(16) float Bs[FBK][FBNB + 4];
-    constexpr bool kRows = MODE <= GB_DX;
+__global__ void __launch_bounds__(kThreads, 2)
+gemm_rm_kernel(RmArgs p) {
+    constexpr bool kRows = MODE != GB_DW2 && MODE != GB_DW13;
+    constexpr bool kFwd = MODE == RM_FW1 || MODE == RM_FW2;
+    constexpr int NH = rm_nh(BF16), BH = 64 * NH;
+    constexpr int CK = BF16 ? 8 : 4, KS = 8 * CK, ES = BF16 ? 2 : 4;
+    // F: rows of x / dout / H (along K), [dA dB] (rows: along K; weight steps: along the index), w H
+    constexpr bool kF16 = BF16 && (MODE == GB_AB || MODE == GB_DH);
+    constexpr bool kHkc = MODE == GB_AB || kFwd;  // H: W13 / W2 rows along K, else along the index
+    using OpF = RmOperand<kF16, kRows, 2, CK, BF16 ? 3 : 0>;
+    using OpH = RmOperand<BF16, kHkc, 2 * NH, CK, 0>;
+    constexpr int F_BYTES = 64 * 128, H_BYTES = BH * 128;
+    constexpr int BUF = OpF::PLANES * F_BYTES + H_BYTES;
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[2][BUF];
+
     const int tid = threadIdx.x;
-    int g, m0, n0, M, N, K, rows = 0;
+    int g, f0, h0, NF, N, K;
     int64_t row0;
     if constexpr (kRows) {
         Tile t;
-        if (!decode_tile(p.work, p.off, p.E, p.T, FBM, gb_row_tiles(MODE, p.inter, p.d),
-                         gb_row_tiles(MODE, p.shared_inter, p.d), 0, t))
+        if (!decode_tile(p.work, p.off, p.E, p.T, 64, rm_row_tiles(MODE, p.inter, p.d, BF16),
+                         rm_row_tiles(MODE, p.shared_inter, p.d, BF16), p.part, t))
             return;
         g = t.g;
         row0 = t.row0;
-        rows = t.rows;
-        m0 = 0;
-        n0 = t.nt * FBNB;
-        const int n_out = g == p.E ? p.shared_inter : p.inter;
-        M = rows;
-        N = MODE == GB_AB ? 2 * n_out : MODE == GB_DH ? n_out : p.d;
-        K = MODE == GB_DX ? 2 * n_out : p.d;
+        const int n = g == p.E ? p.shared_inter : p.inter;
+        f0 = 0;
+        NF = t.rows;
+        h0 = t.nt * (MODE == RM_FW1 ? 32 : BH);
+        N = MODE == GB_AB ? 2 * n : (MODE == GB_DH || MODE == RM_FW1) ? n : p.d;
+        K = MODE == GB_DX ? 2 * n : MODE == RM_FW2 ? n : p.d;
     } else {
         g = blockIdx.y;
-        const int n_out = g == p.E ? p.shared_inter : p.inter;
-        M = MODE == GB_DW2 ? p.d : 2 * n_out;
-        N = MODE == GB_DW2 ? n_out : p.d;
-        const int tn = static_cast<int>(ceil_div(N, FBNB));
-        if (static_cast<int>(blockIdx.x) >= static_cast<int>(ceil_div(M, FBM)) * tn) return;
-        m0 = static_cast<int>(blockIdx.x) / tn * FBM;
-        n0 = static_cast<int>(blockIdx.x) % tn * FBNB;
+        const int n = g == p.E ? p.shared_inter : p.inter;
+        NF = MODE == GB_DW2 ? n : 2 * n;
+        N = p.d;
+        const int th = static_cast<int>(ceil_div(N, BH));
+        if (static_cast<int>(blockIdx.x) >= static_cast<int>(ceil_div(NF, 64)) * th) return;
+        f0 = static_cast<int>(blockIdx.x) / th * 64;
+        h0 = static_cast<int>(blockIdx.x) % th * BH;
         row0 = g == p.E ? 0 : p.off[g];
         K = g == p.E ? static_cast<int>(p.T) : p.off[g + 1] - p.off[g];
     }
     const bool shared = g == p.E;
     const int n_out = shared ? p.shared_inter : p.inter;
     const int ldab = 2 * n_out;
-    const void* W13 = shared ? p.ws13
-                             : static_cast<const char*>(p.w13) + (BF16 ? 2 : 4) * static_cast<int64_t>(g) * 2 * p.inter * p.d;
-    const void* W2 = shared ? p.ws2
-                            : static_cast<const char*>(p.w2) + (BF16 ? 2 : 4) * static_cast<int64_t>(g) * p.d * p.inter;
+    const char* W13 = shared ? static_cast<const char*>(p.ws13)
+                             : static_cast<const char*>(p.w13) + ES * static_cast<int64_t>(g) * 2 * p.inter * p.d;
+    const char* W2 = shared ? static_cast<const char*>(p.ws2)
+                            : static_cast<const char*>(p.w2) + ES * static_cast<int64_t>(g) * p.d * p.inter;
     float* ab = shared ? p.ab_s : p.ab_r;
     float* dab = shared ? p.dab_s : p.dab_r;
     float* wh = shared ? p.wh_s : p.wh_r;
-    // token of row r (row space of this group: routed rows in expert order, or tokens)
-    auto token = [&](int64_t r) -> int64_t { return shared ? r : p.perm_token[r]; };
 
-    // loader coordinates: "kc" operands are contiguous along K (thread: one row, 4 k),
-    // "ic" operands along the output index (thread: one k, 4 indices)
-    const int kc_i = tid >> 2, kc_k = (tid & 3) * 4;
-    const int ic_k = tid >> 4, ic_i = (tid & 15) * 4;
-    // row-step A operand (kc): x / dout gathered by token, or [dA dB] by row
-    int64_t a_base = 0;
-    const bool a_ok = kc_i < rows;
+    // Indices past the tile read index 0 (their outputs are not written), K
+    // past its end reads K index 0 and is zeroed, so every load is in bounds.
+    constexpr int EF = kF16 ? 2 : 4;
+    const char* fp[OpF::OUTER];  // kRows: the row of each chunk; else fp[0]: this thread's columns of row row0
     if constexpr (kRows) {
-        if (a_ok) a_base = MODE == GB_DX ? (row0 + kc_i) * ldab : token(row0 + kc_i) * p.d;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int r = OpF::lds_row(u) < NF ? OpF::lds_row(u) : 0;
+            if constexpr (MODE == GB_DX) fp[u] = reinterpret_cast<const char*>(dab + (row0 + r) * ldab);
+            else if constexpr (MODE == RM_FW2)
+                fp[u] = reinterpret_cast<const char*>((shared ? p.h_s : p.h_r) + (row0 + r) * n_out);
+            else {
+                const int64_t tok = shared ? row0 + r : p.perm_token[row0 + r];
+                fp[u] = static_cast<const char*>(MODE == GB_DH ? p.dout : p.x) + EF * tok * p.d;
+            }
+        }
+    } else {
+        const int i = f0 + 2 * (tid & 31) < NF ? f0 + 2 * (tid & 31) : f0;
+        fp[0] = reinterpret_cast<const char*>(MODE == GB_DW2 ? wh + row0 * n_out + i : dab + row0 * ldab + i);
     }
-    // GB_AB B operand (kc): row n0 + kc_i of W13
-    const bool b_kc_ok = n0 + kc_i < N;
-    const int64_t b_kc_base = static_cast<int64_t>(n0 + kc_i) * p.d;
+    const char* hp[OpH::OUTER];  // kHkc: the weight row of each chunk; else hp[0]: this thread's columns of row 0
+    if constexpr (kHkc) {
+#pragma unroll
+        for (int u = 0; u < 2 * NH; ++u) {
+            const int R = OpH::lds_row(u);
+            int64_t wr;
+            if constexpr (MODE == RM_FW1) {  // 32 gate rows, then the matching up rows
+                const int c = h0 + (R & 31) < N ? h0 + (R & 31) : 0;
+                wr = R < 32 ? c : n_out + c;
+            } else {
+                wr = h0 + R < N ? h0 + R : 0;
+            }
+            hp[u] = MODE == RM_FW2 ? W2 + ES * wr * n_out : W13 + ES * wr * p.d;
+        }
+    } else {
+        const int i = h0 + 2 * NH * (tid & 31) < N ? h0 + 2 * NH * (tid & 31) : h0;
+        const char* b = MODE == GB_DH ? W2 : MODE == GB_DX ? W13 : static_cast<const char*>(MODE == GB_DW2 ? p.dout : p.x);
+        hp[0] = b + ES * static_cast<int64_t>(i);
+    }
+    const int64_t f_ld = 4 * static_cast<int64_t>(MODE == GB_DW2 ? n_out : ldab);
+    const int64_t h_ld = ES * static_cast<int64_t>(MODE == GB_DH ? n_out : p.d);
 
-    const int ty = tid >> 4, tx = tid & 15;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += FBK) {
-        float a[4], b[4];
+    const int nk = static_cast<int>(ceil_div(K, KS));
+    // tokens of this thread's K rows of one step (weight steps: dout / x rows), loaded a step ahead
+    int tok[CK];
+    auto load_tok = [&](int s) {
+        if constexpr (!kRows) {
+#pragma unroll
+            for (int e = 0; e < CK; ++e) {
+                int kk = s * KS + OpH::lds_chunk() * CK + e;
+                kk = kk < K ? kk : 0;
+                tok[e] = shared ? kk : p.perm_token[row0 + kk];
+            }
+        }
+    };
+    OpF opf;
+    OpH oph;
+    auto load = [&](int s) {
+        const int kf = s * KS + OpF::lds_chunk() * CK, kh = s * KS + OpH::lds_chunk() * CK;
         if constexpr (kRows) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int kk = k0 + kc_k + q;
-                const bool ok = a_ok && kk < K;
-                if constexpr (MODE == GB_DX) a[q] = ok ? dab[a_base + kk] : 0.0f;
-                else if constexpr (MODE == GB_AB) a[q] = ok ? ldv<BF16>(p.x, a_base + kk) : 0.0f;
-                else a[q] = ok ? ldv<BF16>(p.dout, a_base + kk) : 0.0f;
-            }
-            if constexpr (MODE == GB_AB) {
+            for (int u = 0; u < 2; ++u) rm_load_words<kF16>(fp[u] + EF * (kf < K ? kf : 0), opf.raw[u]);
+        } else {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int kk = k0 + kc_k + q;
-                    b[q] = b_kc_ok && kk < K ? ldv<BF16>(W13, b_kc_base + kk) : 0.0f;
-                }
+            for (int e = 0; e < CK; ++e) rm_load_words<kF16>(fp[0] + f_ld * (kf + e < K ? kf + e : 0), opf.raw[e]);
+        }
+        if constexpr (kHkc) {
+#pragma unroll
+            for (int u = 0; u < 2 * NH; ++u) rm_load_words<BF16>(hp[u] + ES * (kh < K ? kh : 0), oph.raw[u]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < CK; ++e) {
+                const int64_t r = kRows ? (kh + e < K ? kh + e : 0) : tok[e];
+                rm_load_words<BF16>(hp[0] + h_ld * r, oph.raw[e]);
+            }
+        }
+    };
+    auto store = [&](int s) {
+        if ((s + 1) * KS > K) {
+            opf.cut(s * KS + OpF::lds_chunk() * CK, K);
+            oph.cut(s * KS + OpH::lds_chunk() * CK, K);
+        }
+        uint8_t* b = lds[s & 1];
+        opf.put(b, F_BYTES);
+        oph.put(b + OpF::PLANES * F_BYTES, H_BYTES);
+    };
+
+    const int wave = tid / kWave, lane = lane_id();
+    const int wf = wave >> 1, wh_ = wave & 1, half = lane >> 5, l32 = lane & 31;
+    // acc[j]: 32 F indices (rows; GB_DW2: columns) x 32 H indices
+    f32x16_t acc[NH];
+#pragma unroll
+    for (int j = 0; j < NH; ++j) acc[j] = f32x16_t{};
+    auto compute = [&](int s) {
+        const uint8_t* b = lds[s & 1];
+        auto frag = [&](const uint8_t* base, int R, int c) {
+            return *reinterpret_cast<const uint4*>(base + R * 128 + ((c ^ (((R >> 1) ^ (R >> 4)) & 7)) * 16));
+        };
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            const int c = 2 * ks + half;
+            uint4 f[OpF::PLANES], h[NH];
+#pragma unroll
+            for (int q = 0; q < OpF::PLANES; ++q) f[q] = frag(b + q * F_BYTES, 32 * wf + l32, c);
+#pragma unroll
+            for (int j = 0; j < NH; ++j) h[j] = frag(b + OpF::PLANES * F_BYTES, 32 * (NH * wh_ + j) + l32, c);
+            if constexpr (BF16) {
+#pragma unroll
+                for (int q = OpF::PLANES - 1; q >= 0; --q)  // smallest terms first
+#pragma unroll
+                    for (int j = 0; j < NH; ++j) {
+                        const bf16x8_t fv = __builtin_bit_cast(bf16x8_t, f[q]), hv = __builtin_bit_cast(bf16x8_t, h[j]);
+                        acc[j] = MODE == GB_DW2 ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(hv, fv, acc[j], 0, 0, 0)
+                                                : __builtin_amdgcn_mfma_f32_32x32x16_bf16(fv, hv, acc[j], 0, 0, 0);
+                    }
             } else {
-                // B(j, kk) = W2[kk][j] (dH) or W13[kk][j] (dX): contiguous along j
-                const int kk = k0 + ic_k;
-                const int ld = MODE == GB_DH ? n_out : p.d;
-                const void* Wb = MODE == GB_DH ? W2 : W13;
+                const f32x4_t fv = __builtin_bit_cast(f32x4_t, f[0]), hv = __builtin_bit_cast(f32x4_t, h[0]);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int j = n0 + ic_i + q;
-                    b[q] = kk < K && j < N ? ldv<BF16>(Wb, static_cast<int64_t>(kk) * ld + j) : 0.0f;
-                }
-            }
-        } else {
-            // contraction over the group's rows: row k0 + ic_k
-            const int kk = k0 + ic_k;
-            const bool rok = kk < K;
-            const int64_t r = row0 + (rok ? kk : 0);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int i = m0 + ic_i + q, j = n0 + ic_i + q;
-                if constexpr (MODE == GB_DW2) {
-                    a[q] = rok && i < M ? ldv<BF16>(p.dout, token(r) * p.d + i) : 0.0f;
-                    b[q] = rok && j < N ? wh[r * n_out + j] : 0.0f;
-                } else {
-                    a[q] = rok && i < M ? dab[r * ldab + i] : 0.0f;
-                    b[q] = rok && j < N ? ldv<BF16>(p.x, token(r) * p.d + j) : 0.0f;
-                }
+                for (int e = 0; e < 4; ++e)
+                    acc[0] = MODE == GB_DW2 ? __builtin_amdgcn_mfma_f32_32x32x2f32(hv[e], fv[e], acc[0], 0, 0, 0)
+                                            : __builtin_amdgcn_mfma_f32_32x32x2f32(fv[e], hv[e], acc[0], 0, 0, 0);
             }
         }
-        if constexpr (kRows) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) As[kc_k + q][kc_i] = a[q];
-        } else {
-            *reinterpret_cast<float4*>(&As[ic_k][ic_i]) = make_float4(a[0], a[1], a[2], a[3]);
-        }
-        if constexpr (MODE == GB_AB) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) Bs[kc_k + q][kc_i] = b[q];
-        } else {
-            *reinterpret_cast<float4*>(&Bs[ic_k][ic_i]) = make_float4(b[0], b[1], b[2], b[3]);
-        }
+    };
+    if (nk > 0) {
+        load_tok(0);
+        load(0);
+        load_tok(1);
+        store(0);
+        if (nk > 1) load(1);
+        load_tok(2);
         __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < FBK; ++kk) {
-            const float4 av = *reinterpret_cast<const float4*>(&As[kk][ty * 4]);
-            const float4 bv = *reinterpret_cast<const float4*>(&Bs[kk][tx * 4]);
-            const float ar[4] = {av.x, av.y, av.z, av.w}, br[4] = {bv.x, bv.y, bv.z, bv.w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(ar[i], br[j], acc[i][j]);
+        for (int s = 0; s < nk; ++s) {
+            // the buffer written here was last read before the barrier that ended step s - 1
+            if (s + 1 < nk) store(s + 1);
+            if (s + 2 < nk) {
+                load(s + 2);
+                load_tok(s + 3);
+            }
+            compute(s);
+            __syncthreads();
         }
+    }
+
+    // element v of a 32 x 32 tile: row 8 (v / 4) + 4 half + v % 4, column l32
+    if constexpr (MODE == RM_FW1) {
+        // gate and up sit in different waves: through LDS, then whole rows of 32 columns
+        float* C = reinterpret_cast<float*>(lds);
+        static_assert(64 * 65 * 4 <= 2 * BUF, "the output tile fits the operand buffers");
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            C[(32 * wf + 8 * (v >> 2) + 4 * half + (v & 3)) * 65 + 32 * wh_ + l32] = acc[0][v];
         __syncthreads();
+        float* H = shared ? p.h_s : p.h_r;
+        for (int q = tid; q < 64 * 32; q += kThreads) {
+            const int r = q / 32, c = q % 32, col = h0 + c;
+            if (r < NF && col < N) H[(row0 + r) * n_out + col] = silu(C[r * 65 + c]) * C[r * 65 + 32 + c];
+        }
+        return;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int rr = m0 + ty * 4 + i;
-        if (rr >= M) continue;
+    for (int j = 0; j < NH; ++j) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int col = n0 + tx * 4 + j;
-            if (col >= N) continue;
-            const float v = acc[i][j];
-            if constexpr (MODE == GB_AB) {
-                ab[(row0 + rr) * ldab + col] = v;
-            } else if constexpr (MODE == GB_DH) {
-                // SwiGLU backward of h = silu(a) b with dh = w (dout W2)
-                const int64_t r = row0 + rr;
-                const float w = shared ? 1.0f : p.wrow[r];
-                const float dh = w * v;
-                const float av = ab[r * ldab + col], bv = ab[r * ldab + n_out + col];
-                const float sg = 1.0f / (1.0f + expf(-av));
-                const float sa = av * sg;
-                dab[r * ldab + col] = dh * bv * sg * (1.0f + av * (1.0f - sg));
-                dab[r * ldab + n_out + col] = dh * sa;
-                wh[r * n_out + col] = w * sa * bv;
-            } else if constexpr (MODE == GB_DX) {
-                (shared ? p.dx_s : p.dx_r)[(row0 + rr) * p.d + col] = v;
+        for (int v = 0; v < 16; ++v) {
+            const int tr = 8 * (v >> 2) + 4 * half + (v & 3);
+            const float a = acc[j][v];
+            if constexpr (MODE == GB_DW2) {
+                const int n = h0 + 32 * (NH * wh_ + j) + tr, c = f0 + 32 * wf + l32;
+                if (n >= N || c >= NF) continue;
+                const int64_t e = (shared ? 0 : static_cast<int64_t>(g) * p.d * p.inter) + static_cast<int64_t>(n) * NF + c;
+                void* out = shared ? p.dws2 : p.dw2;
+                if constexpr (BF16) static_cast<uint16_t*>(out)[e] = f32_to_bf16(a);
+                else static_cast<float*>(out)[e] = a;
             } else {
-                const int64_t gi = MODE == GB_DW2 ? static_cast<int64_t>(g) * p.d * p.inter
-                                                  : static_cast<int64_t>(g) * 2 * p.inter * p.d;
-                void* out = shared ? (MODE == GB_DW2 ? p.dws2 : p.dws13) : (MODE == GB_DW2 ? p.dw2 : p.dw13);
-                const int64_t e = (shared ? 0 : gi) + static_cast<int64_t>(rr) * N + col;
-                if constexpr (BF16) static_cast<uint16_t*>(out)[e] = f32_to_bf16(v);
-                else static_cast<float*>(out)[e] = v;
+                const int rr = f0 + 32 * wf + tr, col = h0 + 32 * (NH * wh_ + j) + l32;
+                if (rr >= NF || col >= N) continue;
+                if constexpr (MODE == GB_AB) {
+                    ab[(row0 + rr) * ldab + col] = a;
+                } else if constexpr (MODE == GB_DH) {
+                    // SwiGLU backward of h = silu(a) b with dh = w (dout W2)
+                    const int64_t r = row0 + rr;
+                    const float w = shared ? 1.0f : p.wrow[r];
+                    const float dh = w * a;
+                    const float av = ab[r * ldab + col], bv = ab[r * ldab + n_out + col];
+                    const float sg = 1.0f / (1.0f + expf(-av));
+                    const float sa = av * sg;
+                    dab[r * ldab + col] = dh * bv * sg * (1.0f + av * (1.0f - sg));
+                    dab[r * ldab + n_out + col] = dh * sa;
+                    wh[r * n_out + col] = w * sa * bv;
+                } else if constexpr (MODE == GB_DX || MODE == RM_FW2) {
+                    float* o = MODE == GB_DX ? (shared ? p.dx_s : p.dx_r) : (shared ? p.y_s : p.y_r);
+                    o[(row0 + rr) * p.d + col] = a;
+                } else {
+                    const int64_t e = (shared ? 0 : static_cast<int64_t>(g) * 2 * p.inter * p.d) + static_cast<int64_t>(rr) * N + col;
+                    void* out = shared ? p.dws13 : p.dw13;
+                    if constexpr (BF16) static_cast<uint16_t*>(out)[e] = f32_to_bf16(a);
+                    else static_cast<float*>(out)[e] = a;
+                }
             }
         }
     }
@@ -1404,6 +1526,30 @@ GemmArgs make_args(const ExpertArgs& a, const ExpWs& w, const int32_t* work, int
     return g;
 }
 
+// the forward of a float32 layer
+RmArgs rm_fwd_args(const GemmArgs& a) {
+    RmArgs r{};
+    r.T = a.T;
+    r.d = a.d;
+    r.E = a.E;
+    r.inter = a.inter;
+    r.shared_inter = a.shared_inter;
+    r.part = a.part;
+    r.off = a.off;
+    r.perm_token = a.perm_token;
+    r.work = a.work;
+    r.x = a.x;
+    r.w13 = a.w13;
+    r.w2 = a.w2;
+    r.ws13 = a.ws13;
+    r.ws2 = a.ws2;
+    r.h_r = static_cast<float*>(a.h_r);
+    r.h_s = static_cast<float*>(a.h_s);
+    r.y_r = static_cast<float*>(a.y_r);
+    r.y_s = static_cast<float*>(a.y_s);
+    return r;
+}
+
 // Grid size: 8 XCD ranges, each at most a bound on the routed items over 8
 // plus the shared items over 8 (host side; the exact split is made on the device).
 int64_t work_bound(int64_t T, int k, int E, int bm, int nt_r, int nt_s, bool has_shared, int part) {
@@ -1471,9 +1617,10 @@ hipError_t launch_experts_gemm1(const ExpertArgs& a, void* ws, int part, hipStre
     else if (a.act_dtype == 1)
         hipLaunchKernelGGL((gemm_bf16_dma_kernel<1, DCfg>), grid, dim3(DCfg::THREADS), 0, stream, g);
     else
-        hipLaunchKernelGGL(gemm_f32_kernel<1>, grid, dim3(kThreads), 0, stream, g);
+        hipLaunchKernelGGL((gemm_rm_kernel<RM_FW1, false>), grid, dim3(kThreads), 0, stream, rm_fwd_args(g));
     return hipGetLastError();
 }
+
 
 hipError_t launch_experts_gemm2_combine(const ExpertArgs& a, void* ws, hipStream_t stream) {
     if (!(a.act_dtype == 1 && a.packed && a.shared_inter > 0)) return hipErrorInvalidValue;
@@ -1497,7 +1644,7 @@ hipError_t launch_experts_gemm2(const ExpertArgs& a, void* ws, int part, hipStre
     else if (a.act_dtype == 1)
         hipLaunchKernelGGL((gemm_bf16_dma_kernel<2, DCfg>), grid, dim3(DCfg::THREADS), 0, stream, g);
     else
-        hipLaunchKernelGGL(gemm_f32_kernel<2>, grid, dim3(kThreads), 0, stream, g);
+        hipLaunchKernelGGL((gemm_rm_kernel<RM_FW2, false>), grid, dim3(kThreads), 0, stream, rm_fwd_args(g));
     return hipGetLastError();
 }
 
@@ -1583,7 +1730,7 @@ hipError_t launch_bwd_gemm(int mode, const ExpertArgs& a, void* fwd_ws, const Bw
 }
 
 hipError_t launch_generic_bwd(int step, const ExpertArgs& a, const GenericBwdPtrs& bp, hipStream_t stream) {
-    GenBwdArgs g;
+    RmArgs g{};
     g.T = a.T;
     g.d = a.d;
     g.E = a.E;
@@ -1615,7 +1762,7 @@ hipError_t launch_generic_bwd(int step, const ExpertArgs& a, const GenericBwdPtr
     const bool has_shared = a.shared_inter > 0;
     dim3 grid;
     if (step <= GB_DX) {
-        const int nt_r = gb_row_tiles(step, a.inter, a.d), nt_s = gb_row_tiles(step, a.shared_inter, a.d);
+        const int nt_r = rm_row_tiles(step, a.inter, a.d, bf16), nt_s = rm_row_tiles(step, a.shared_inter, a.d, bf16);
         hipLaunchKernelGGL(bwd_work_kernel, dim3(1), dim3(256), 0, stream, a.expert_offsets, a.E, a.T, FBM, nt_r, nt_s,
                            has_shared ? 1 : 0, bp.work);
         const hipError_t e = hipGetLastError();
@@ -1623,8 +1770,7 @@ hipError_t launch_generic_bwd(int step, const ExpertArgs& a, const GenericBwdPtr
         grid = dim3(static_cast<unsigned>(work_bound(a.T, a.k, a.E, FBM, nt_r, nt_s, has_shared, 0)));
     } else {
         auto tiles = [&](int n_out) {
-            const int64_t M = step == GB_DW2 ? a.d : 2 * n_out, N = step == GB_DW2 ? n_out : a.d;
-            return ceil_div(M, FBM) * ceil_div(N, FBNB);
+            return ceil_div(step == GB_DW2 ? n_out : 2 * n_out, 64) * ceil_div(a.d, 64 * rm_nh(bf16));
         };
         const int64_t t_r = tiles(a.inter), t_s = has_shared ? tiles(a.shared_inter) : 0;
         grid = dim3(static_cast<unsigned>(t_r > t_s ? t_r : t_s), static_cast<unsigned>(a.E + (has_shared ? 1 : 0)));
@@ -1632,8 +1778,8 @@ hipError_t launch_generic_bwd(int step, const ExpertArgs& a, const GenericBwdPtr
     if (grid.x == 0) return hipSuccess;
 #define SMOES_GB(M)                                                                                    \
     do {                                                                                               \
-        if (bf16) hipLaunchKernelGGL((gemm_f32_bwd_kernel<M, true>), grid, dim3(kThreads), 0, stream, g);  \
-        else hipLaunchKernelGGL((gemm_f32_bwd_kernel<M, false>), grid, dim3(kThreads), 0, stream, g);      \
+        if (bf16) hipLaunchKernelGGL((gemm_rm_kernel<M, true>), grid, dim3(kThreads), 0, stream, g);  \
+        else hipLaunchKernelGGL((gemm_rm_kernel<M, false>), grid, dim3(kThreads), 0, stream, g);      \
     } while (0)
     switch (step) {
         case GB_AB: SMOES_GB(GB_AB); break;
