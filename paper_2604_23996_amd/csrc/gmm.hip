@@ -11,9 +11,18 @@
 //     the score (Eq. 9 over the per-modality log-sum-exp) or the
 //     responsibilities of the token's own modality (the E-step).
 //  update (stepwise EM): gmm_partial sums r (x - shift), r (x - shift)^2 and r
-//     per chunk of 64 tokens in fp64 (shift = the component's previous mean),
-//     gmm_merge adds the chunks in order and applies Eq. 5-7 with the weighted
-//     batch count, mean and centred sum of squares.
+//     per chunk of 64 tokens in fp64 (shift = the component's previous mean,
+//     rounded to float32: any constant near the mean will do), gmm_merge adds
+//     the chunks in a fixed order, applies Eq. 5-7 with the weighted batch
+//     count, mean and centred sum of squares, and writes the score's
+//     coefficients of the new state, as gmm_prep does for the old one.
+// At 8192 x 2048 bf16 and K = 2 (33.6 MB) an update and a score take 4 + 18 + 24
+// + 10 + 16 us, bound by latency and by the address unit (the coefficients come
+// through L1 once per wave, so a wave takes four tokens). Before, 5 + 27 + 42 +
+// 21 + 5 + 25: gmm_partial read every row's label before it loaded the row, once
+// per modality, and its LDS tree had all lanes on one bank; gmm_merge walked
+// 128 chunks with 8 loads in flight; gmm_loglik kept one 512-column stripe of
+// two rows in flight and ran its float64 logarithms once per wave.
 #include "common.h"
 #include "kernels.h"
 
@@ -22,15 +31,18 @@ namespace smoes {
 namespace {
 
 constexpr int kGChunk = 64;         // tokens per gmm_partial block
-constexpr int kGPartCols = 256;     // columns per gmm_partial block (64 lanes x 4)
 constexpr int kGPrepThreads = 256;  // columns per gmm_prep block
-constexpr int kGMaxParts = 64;      // SMOES_D_MAX / kGPrepThreads
-constexpr int kGTokPerWave = 2;
+constexpr int kGMergeCols = 64;     // columns per gmm_merge block
+constexpr int kGMergeGroups = 8;    // chunk groups per column
+constexpr int kGMaxParts = 256;     // SMOES_D_MAX / kGMergeCols: parts of a log-variance sum
+constexpr int kGTokPerWave = 4;
 constexpr int kGThreads = 256;
+// columns per lane of gmm_partial: 4, or 2 where the sums of 6 or 8 components would not leave two waves a SIMD
+constexpr int gmm_part_cols(int K) { return K <= 2 ? 4 : 2; }
 
 struct GmmWs {
     float* coef;      // [2K][2][d]: mu, 1 / sigma^2
-    double* cst;      // [2K][kGMaxParts]: per column block, sum log sigma^2
+    double* cst;      // [2K][kGMaxParts]: per block of 256 (gmm_prep) or 64 (gmm_merge) columns, sum log sigma^2
     double* n_old;    // [2K]
     float* resp;      // [T][K] (when the caller passes none)
     double* wsum;     // [nchunk][2K]
@@ -58,6 +70,20 @@ GmmWs gmm_carve(void* ws, int64_t T, int d, int K) {
     return w;
 }
 
+// Score coefficients of one component's column (mean 0, variance 1 without a
+// count); returns log sigma^2.
+__device__ __forceinline__ double gmm_coef(double n, double smu, double ssig, double var_floor, int d, int mc, int col,
+                                           float* __restrict__ coef) {
+    double mu = 0.0, var = 1.0;
+    if (n > 0.0) {
+        mu = smu / n;
+        var = fmax(ssig / n, var_floor);
+    }
+    coef[(static_cast<int64_t>(mc) * 2) * d + col] = static_cast<float>(mu);
+    coef[(static_cast<int64_t>(mc) * 2 + 1) * d + col] = static_cast<float>(1.0 / var);
+    return log(var);
+}
+
 __global__ void __launch_bounds__(kGPrepThreads)
 gmm_prep_kernel(int d, int K, const float* __restrict__ gn, const float* __restrict__ gsmu,
                 const float* __restrict__ gssig, float var_floor, float* __restrict__ coef,
@@ -67,16 +93,9 @@ gmm_prep_kernel(int d, int K, const float* __restrict__ gn, const float* __restr
     const double n = gn[mc];
     const int col = blockIdx.x * kGPrepThreads + threadIdx.x;
     double acc = 0.0;
-    if (col < d) {
-        double mu = 0.0, var = 1.0;
-        if (n > 0.0) {
-            mu = gsmu[static_cast<int64_t>(mc) * d + col] / n;
-            var = fmax(static_cast<double>(gssig[static_cast<int64_t>(mc) * d + col]) / n, static_cast<double>(var_floor));
-        }
-        coef[(static_cast<int64_t>(mc) * 2) * d + col] = static_cast<float>(mu);
-        coef[(static_cast<int64_t>(mc) * 2 + 1) * d + col] = static_cast<float>(1.0 / var);
-        acc = log(var);
-    }
+    if (col < d)
+        acc = gmm_coef(n, gsmu[static_cast<int64_t>(mc) * d + col], gssig[static_cast<int64_t>(mc) * d + col], var_floor,
+                       d, mc, col, coef);
     part[threadIdx.x] = acc;
     __syncthreads();
     for (int s = kGPrepThreads / 2; s > 0; s >>= 1) {
@@ -88,30 +107,67 @@ gmm_prep_kernel(int d, int K, const float* __restrict__ gn, const float* __restr
 
 // mode 0: scores M[T][2]; mode 1: responsibilities resp[T][K] of each token's own modality.
 template <bool BF16, int K>
-__global__ void __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+__global__ void __launch_bounds__(kGThreads)
 gmm_loglik_kernel(const void* __restrict__ x, int64_t T, int d, const uint8_t* __restrict__ mid,
                   const float* __restrict__ coef, const double* __restrict__ cst, int n_part,
                   const float* __restrict__ gn, double inv_tau, int mode, float* __restrict__ M,
                   float* __restrict__ resp) {
     constexpr int MC = 2 * K;
-    static_assert(kGTokPerWave == 2, "the token select below assumes two tokens per wave");
-    const int wave = threadIdx.x / kWave;
+    constexpr int NT = kGTokPerWave;
+    __shared__ double q_s[kGThreads / kWave][NT][MC];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int lane = lane_id();
-    const int64_t tok0 = (static_cast<int64_t>(blockIdx.x) * (kGThreads / kWave) + wave) * kGTokPerWave;
-    if (tok0 >= T) return;  // whole waves: the reduction below is wave-local
-    int64_t rows[kGTokPerWave];
+    const int64_t blk0 = static_cast<int64_t>(blockIdx.x) * (kGThreads / kWave) * NT;
+    const int64_t tok0 = blk0 + wave * NT;
+    int64_t rows[NT];
 #pragma unroll
-    for (int t = 0; t < kGTokPerWave; ++t) rows[t] = tok0 + t < T ? tok0 + t : T - 1;
-    double acc[kGTokPerWave][MC];
+    for (int t = 0; t < NT; ++t) rows[t] = tok0 + t < T ? tok0 + t : T - 1;
+    // lane j < MC: -2 log pi_mc, pi_mc = N_mc / sum_c N_mc (uniform when the modality has no count)
+    double lp = 0.0;
+    if (lane < MC) {
+        double tot = 0.0;
 #pragma unroll
-    for (int t = 0; t < kGTokPerWave; ++t)
+        for (int c = 0; c < K; ++c) tot += static_cast<double>(gn[lane / K * K + c]);
+        lp = -2.0 * (tot > 0.0 ? log(static_cast<double>(gn[lane]) / tot) : -log(static_cast<double>(K)));
+    }
+    // a lane's partial sums start from its parts of sum log sigma^2 - 2 log pi
+    double acc[NT][MC];
 #pragma unroll
-        for (int j = 0; j < MC; ++j) acc[t][j] = 0.0;
-#pragma unroll 1
-    for (int c0 = lane * 8; c0 < d; c0 += kWave * 8) {
+    for (int j = 0; j < MC; ++j) {
+        double slv = lane == j ? lp : 0.0;
+        for (int b = lane; b < n_part; b += kWave) slv += cst[j * kGMaxParts + b];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t][j] = slv;
+    }
+    // the rows' next S stripes of 512 columns (8 per lane) are loaded before any is used
+    constexpr int S = BF16 ? 4 : 2;
+    constexpr int Q = BF16 ? 1 : 2;
+    for (int g = lane * 8; g < d; g += S * kWave * 8) {
+        uint4 raw[kGTokPerWave][S][Q];
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const int c0 = g + s * kWave * 8 < d ? g + s * kWave * 8 : 0;
+#pragma unroll
+            for (int t = 0; t < kGTokPerWave; ++t) {
+                const int64_t e = rows[t] * d + c0;
+                const uint4* q = BF16 ? reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(x) + e)
+                                      : reinterpret_cast<const uint4*>(static_cast<const float*>(x) + e);
+#pragma unroll
+                for (int i = 0; i < Q; ++i) raw[t][s][i] = q[i];
+            }
+        }
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const int c0 = g + s * kWave * 8;
+        if (c0 >= d) break;
         float v[kGTokPerWave][8];
 #pragma unroll
-        for (int t = 0; t < kGTokPerWave; ++t) load8<BF16>(x, rows[t] * d + c0, v[t]);
+        for (int t = 0; t < kGTokPerWave; ++t) {
+            const uint32_t* w = reinterpret_cast<const uint32_t*>(&raw[t][s][0]);
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                v[t][i] = BF16 ? __uint_as_float(i & 1 ? w[i / 2] & 0xffff0000u : w[i / 2] << 16) : __uint_as_float(w[i]);
+        }
 #pragma unroll
         for (int j = 0; j < MC; ++j) {
             float mu[8], iv[8];
@@ -132,35 +188,24 @@ gmm_loglik_kernel(const void* __restrict__ x, int64_t T, int d, const uint8_t* _
                 acc[t][j] += static_cast<double>(part);
             }
         }
+      }
     }
-    // lane partials -> per (token, component) sums: a fixed butterfly, the same in every lane
+    // lane partials -> per (token, component) sums by a fixed butterfly; then one
+    // lane per token of the block turns them into its result (the float64
+    // logarithms and exponentials cost a wave the same for one token as for 64)
 #pragma unroll
-    for (int t = 0; t < kGTokPerWave; ++t)
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int j = 0; j < MC; ++j) acc[t][j] = wave_sum_u(acc[t][j]);
-    if (lane >= kGTokPerWave) return;
-    const int t = lane;
-    if (tok0 + t >= T) return;
-    double q[MC];
-#pragma unroll
-    for (int j = 0; j < MC; ++j) q[j] = t == 0 ? acc[0][j] : acc[kGTokPerWave - 1][j];
+        for (int j = 0; j < MC; ++j) {
+            const double v = wave_sum_u(acc[t][j]);
+            if (lane == 0) q_s[wave][t][j] = v;
+        }
+    __syncthreads();
+    const int64_t j = blk0 + threadIdx.x;
+    if (threadIdx.x >= (kGThreads / kWave) * NT || j >= T) return;
     double ll[MC];
-    for (int j = 0; j < MC; ++j) {
-        double slv = 0.0;
-        for (int b = 0; b < n_part; ++b) slv += cst[j * kGMaxParts + b];
-        ll[j] = -0.5 * (slv + q[j]);
-    }
-    // mixture weights pi_mc = N_mc / sum_c N_mc (uniform when the modality has no count)
 #pragma unroll
-    for (int m = 0; m < 2; ++m) {
-        double tot = 0.0;
-#pragma unroll
-        for (int c = 0; c < K; ++c) tot += static_cast<double>(gn[m * K + c]);
-#pragma unroll
-        for (int c = 0; c < K; ++c)
-            ll[m * K + c] += tot > 0.0 ? log(static_cast<double>(gn[m * K + c]) / tot) : -log(static_cast<double>(K));
-    }
-    const int64_t j = tok0 + t;
+    for (int c = 0; c < MC; ++c) ll[c] = -0.5 * q_s[threadIdx.x / NT][threadIdx.x % NT][c];
     if (mode == 0) {
         double lse[2];
 #pragma unroll
@@ -202,147 +247,214 @@ gmm_loglik_kernel(const void* __restrict__ x, int64_t T, int d, const uint8_t* _
     }
 }
 
-// Weighted sums of one modality (blockIdx.z) over a chunk of tokens: 4 waves
-// split the rows, each lane owns 4 columns; fixed-order tree over the waves.
+// The constant subtracted from a component's column before it is summed: its
+// previous mean, rounded to float32 (gmm_partial and gmm_merge agree on it).
+__device__ __forceinline__ float gmm_shift(double smu, double n) { return n > 0.0 ? static_cast<float>(smu / n) : 0.0f; }
+
+// Weighted sums over a chunk of tokens: 4 waves split the rows, each lane owns
+// two or four columns and sums every row into the components of the row's modality
+// (uniform per row: the labels are one bit each); a group of eight rows is
+// loaded before it is added. Fixed-order tree over the waves, lanes adjacent.
 template <bool BF16, int K>
 __global__ void __launch_bounds__(256)
 gmm_partial_kernel(const void* __restrict__ x, int64_t T, int d, const uint8_t* __restrict__ mid,
                    const float* __restrict__ resp, const float* __restrict__ gn, const float* __restrict__ gsmu,
                    double* __restrict__ wsum, double* __restrict__ s1g, double* __restrict__ s2g,
                    double* __restrict__ n_old) {
-    constexpr int NV = K * 4 * 2;
-    __shared__ double red[2][kWave][NV];
-    __shared__ double wred[4][K];
-    const int wave = threadIdx.x / kWave;
+    constexpr int MC = 2 * K;
+    constexpr int CPL = gmm_part_cols(K);
+    constexpr int NV = K * CPL * 2;  // sums of one modality
+    __shared__ double red[2][NV][kWave];
+    __shared__ float resp_s[kGChunk][K];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int lane = lane_id();
-    const int m = blockIdx.z;
     const int64_t chunk = blockIdx.x;
-    const int col0 = blockIdx.y * kGPartCols + lane * 4;
+    const int col0 = (blockIdx.y * kWave + lane) * CPL;
     const bool active = col0 < d;
-    if (chunk == 0 && blockIdx.y == 0 && m == 0 && threadIdx.x < 2 * K) n_old[threadIdx.x] = gn[threadIdx.x];
-    double sh[K][4], s1[K][4], s2[K][4], ws[K];
+    const int c0 = active ? col0 : 0;  // lanes past d read column 0 and write nothing
+    if (chunk == 0 && blockIdx.y == 0 && threadIdx.x < MC) n_old[threadIdx.x] = gn[threadIdx.x];
+    const int64_t r0 = chunk * kGChunk;
+    const int nr = static_cast<int>(T - r0 < kGChunk ? T - r0 : kGChunk);
+    static_assert(kGChunk == kWave, "one label per lane");
+    const uint64_t text = __ballot(lane < nr && mid[r0 + (lane < nr ? lane : 0)] != 0);
+    for (int i = threadIdx.x; i < nr * K; i += 256) resp_s[i / K][i % K] = resp[r0 * K + i];
+
+    constexpr int U = 8, NG = kGChunk / (4 * U);
+    constexpr int NW = BF16 ? CPL / 2 : CPL;
+    uint32_t v[U][NW];
+    auto load = [&](int g) {
 #pragma unroll
-    for (int c = 0; c < K; ++c) {
-        const double n = gn[m * K + c];
-        ws[c] = 0.0;
+        for (int u = 0; u < U; ++u) {
+            const int r = wave + 4 * (g * U + u);
+            const int64_t e = (r0 + (r < nr ? r : 0)) * d + c0;
+            const uint32_t* q = BF16 ? reinterpret_cast<const uint32_t*>(static_cast<const uint16_t*>(x) + e)
+                                     : reinterpret_cast<const uint32_t*>(static_cast<const float*>(x) + e);
+            if constexpr (NW == 1) {
+                v[u][0] = q[0];
+            } else if constexpr (NW == 2) {
+                const uint2 w = *reinterpret_cast<const uint2*>(q);
+                v[u][0] = w.x;
+                v[u][1] = w.y;
+            } else {
+                const uint4 w = *reinterpret_cast<const uint4*>(q);
+                v[u][0] = w.x;
+                v[u][1] = w.y;
+                v[u][2] = w.z;
+                v[u][3] = w.w;
+            }
+        }
+    };
+    load(0);
+    float sh[MC][CPL];
+    double s1[MC][CPL], s2[MC][CPL], ws[MC];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            sh[c][i] = (active && n > 0.0) ? static_cast<double>(gsmu[static_cast<int64_t>(m * K + c) * d + col0 + i]) / n : 0.0;
-            s1[c][i] = s2[c][i] = 0.0;
+    for (int j = 0; j < MC; ++j) {
+        const double n = gn[j];
+        ws[j] = 0.0;
+#pragma unroll
+        for (int i = 0; i < CPL; ++i) {
+            sh[j][i] = gmm_shift(gsmu[static_cast<int64_t>(j) * d + c0 + i], n);
+            s1[j][i] = s2[j][i] = 0.0;
         }
     }
-    const int64_t r0 = chunk * kGChunk;
-    const int64_t r1 = r0 + kGChunk < T ? r0 + kGChunk : T;
-#pragma unroll 4
-    for (int64_t r = r0 + wave; r < r1; r += 4) {
-        if ((mid[r] ? 1 : 0) != m) continue;
-        double w[K];
+    __syncthreads();
+    auto add_row = [&](auto m_c, int u, int r) {
+        constexpr int m = decltype(m_c)::value;
+        float xv[CPL];
+#pragma unroll
+        for (int i = 0; i < CPL; ++i)
+            xv[i] = BF16 ? __uint_as_float(i & 1 ? v[u][i / 2] & 0xffff0000u : v[u][i / 2] << 16)
+                         : __uint_as_float(v[u][i]);
 #pragma unroll
         for (int c = 0; c < K; ++c) {
-            w[c] = static_cast<double>(resp[r * K + c]);
-            ws[c] += w[c];
-        }
-        if (!active) continue;
-        float v[4];
-        if constexpr (BF16) {
-            const uint2 q = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(x) + r * d + col0);
-            v[0] = __uint_as_float(q.x << 16);
-            v[1] = __uint_as_float(q.x & 0xffff0000u);
-            v[2] = __uint_as_float(q.y << 16);
-            v[3] = __uint_as_float(q.y & 0xffff0000u);
-        } else {
-            const float4 q = *reinterpret_cast<const float4*>(static_cast<const float*>(x) + r * d + col0);
-            v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
-        }
+            const double w = static_cast<double>(resp_s[r][c]);
+            ws[m * K + c] += w;
 #pragma unroll
-        for (int c = 0; c < K; ++c)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const double y = static_cast<double>(v[i]) - sh[c][i];
-                const double wy = w[c] * y;
-                s1[c][i] += wy;
-                s2[c][i] = fma(wy, y, s2[c][i]);
+            for (int i = 0; i < CPL; ++i) {
+                const double y = static_cast<double>(xv[i]) - static_cast<double>(sh[m * K + c][i]);
+                const double wy = w * y;
+                s1[m * K + c][i] += wy;
+                s2[m * K + c][i] = fma(wy, y, s2[m * K + c][i]);
             }
+        }
+    };
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+        if (wave + 4 * g * U >= nr) break;  // uniform
+        if (g > 0) load(g);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int r = wave + 4 * (g * U + u);
+            if (r >= nr) break;  // uniform
+            if ((text >> r) & 1ull) add_row(std::integral_constant<int, 1>{}, u, r);
+            else add_row(std::integral_constant<int, 0>{}, u, r);
+        }
     }
-    auto put = [&](int slot) {
+    // per modality: (w0 + w2) + (w1 + w3)
 #pragma unroll
-        for (int c = 0; c < K; ++c)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                red[slot][lane][(c * 4 + i) * 2] = s1[c][i];
-                red[slot][lane][(c * 4 + i) * 2 + 1] = s2[c][i];
-            }
-    };
-    auto add = [&](int slot) {
-#pragma unroll
-        for (int c = 0; c < K; ++c)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                s1[c][i] += red[slot][lane][(c * 4 + i) * 2];
-                s2[c][i] += red[slot][lane][(c * 4 + i) * 2 + 1];
-            }
-    };
-    if (wave >= 2) put(wave - 2);
-    __syncthreads();
-    if (wave < 2) add(wave);
-    __syncthreads();
-    if (wave == 1) put(0);
-    __syncthreads();
-    if (wave == 0) {
-        add(0);
-        if (active) {
+    for (int m = 0; m < 2; ++m) {
+        auto put = [&](int slot) {
 #pragma unroll
             for (int c = 0; c < K; ++c)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int64_t o = (chunk * 2 * K + m * K + c) * d + col0 + i;
-                    s1g[o] = s1[c][i];
-                    s2g[o] = s2[c][i];
+                for (int i = 0; i < CPL; ++i) {
+                    red[slot][(c * CPL + i) * 2][lane] = s1[m * K + c][i];
+                    red[slot][(c * CPL + i) * 2 + 1][lane] = s2[m * K + c][i];
                 }
+        };
+        auto add = [&](int slot) {
+#pragma unroll
+            for (int c = 0; c < K; ++c)
+#pragma unroll
+                for (int i = 0; i < CPL; ++i) {
+                    s1[m * K + c][i] += red[slot][(c * CPL + i) * 2][lane];
+                    s2[m * K + c][i] += red[slot][(c * CPL + i) * 2 + 1][lane];
+                }
+        };
+        if (wave >= 2) put(wave - 2);
+        __syncthreads();
+        if (wave < 2) add(wave);
+        __syncthreads();
+        if (wave == 1) put(0);
+        __syncthreads();
+        if (wave == 0) {
+            add(0);
+            if (active) {
+#pragma unroll
+                for (int c = 0; c < K; ++c)
+#pragma unroll
+                    for (int i = 0; i < CPL; ++i) {
+                        const int64_t o = (chunk * MC + m * K + c) * d + col0 + i;
+                        s1g[o] = s1[m * K + c][i];
+                        s2g[o] = s2[m * K + c][i];
+                    }
+            }
         }
+        __syncthreads();
     }
     // weight sums: every lane of a wave saw the same rows; lane 0 reports
+    double(*wred)[MC] = reinterpret_cast<double(*)[MC]>(&red[0][0][0]);
     if (lane == 0) {
 #pragma unroll
-        for (int c = 0; c < K; ++c) wred[wave][c] = ws[c];
+        for (int j = 0; j < MC; ++j) wred[wave][j] = ws[j];
     }
     __syncthreads();
-    if (blockIdx.y == 0 && threadIdx.x < K)
-        wsum[chunk * 2 * K + m * K + threadIdx.x] = (wred[0][threadIdx.x] + wred[2][threadIdx.x]) +
-                                                    (wred[1][threadIdx.x] + wred[3][threadIdx.x]);
+    if (blockIdx.y == 0 && threadIdx.x < MC)
+        wsum[chunk * MC + threadIdx.x] = (wred[0][threadIdx.x] + wred[2][threadIdx.x]) +
+                                         (wred[1][threadIdx.x] + wred[3][threadIdx.x]);
 }
 
-__global__ void gmm_merge_kernel(int d, int K, int64_t nchunk, const double* __restrict__ wsum,
-                                 const double* __restrict__ s1g, const double* __restrict__ s2g,
-                                 const double* __restrict__ n_old, float beta, float* __restrict__ gn,
-                                 float* __restrict__ gsmu, float* __restrict__ gssig) {
+// One component (blockIdx.y) x 64 columns: eight thread groups add their share
+// of the chunks in chunk order, then the groups in order.
+__global__ void __launch_bounds__(kGMergeCols * kGMergeGroups)
+gmm_merge_kernel(int d, int K, int64_t nchunk, const double* __restrict__ wsum,
+                 const double* __restrict__ s1g, const double* __restrict__ s2g,
+                 const double* __restrict__ n_old, float beta, float var_floor, float* __restrict__ gn,
+                 float* __restrict__ gsmu, float* __restrict__ gssig, float* __restrict__ coef,
+                 double* __restrict__ cst) {
+    __shared__ double red[3][kGMergeGroups][kGMergeCols];
     const int mc = blockIdx.y;
-    const int col = blockIdx.x * blockDim.x + threadIdx.x;
-    if (col >= d) return;
+    const int cl = threadIdx.x % kGMergeCols, grp = threadIdx.x / kGMergeCols;
+    const int col = blockIdx.x * kGMergeCols + cl;
+    const int cr = col < d ? col : d - 1;
+    const int64_t len = ceil_div(nchunk, kGMergeGroups);
+    const int64_t lo = grp * len, hi = lo + len < nchunk ? lo + len : nchunk;
     double n = 0.0, S1 = 0.0, S2 = 0.0;
-    constexpr int B = 8;  // chunk loads in flight; the sums still run in chunk order
-    for (int64_t c0 = 0; c0 < nchunk; c0 += B) {
+    constexpr int B = 16;  // chunk loads in flight; the sums still run in chunk order
+    for (int64_t c0 = lo; c0 < hi; c0 += B) {
         double vn[B], v1[B], v2[B];
 #pragma unroll
         for (int q = 0; q < B; ++q) {
-            const int64_t ch = c0 + q < nchunk ? c0 + q : c0;
+            const int64_t ch = c0 + q < hi ? c0 + q : c0;
             vn[q] = wsum[ch * 2 * K + mc];
-            v1[q] = s1g[(ch * 2 * K + mc) * d + col];
-            v2[q] = s2g[(ch * 2 * K + mc) * d + col];
+            v1[q] = s1g[(ch * 2 * K + mc) * d + cr];
+            v2[q] = s2g[(ch * 2 * K + mc) * d + cr];
         }
 #pragma unroll
         for (int q = 0; q < B; ++q)
-            if (c0 + q < nchunk) {
+            if (c0 + q < hi) {
                 n += vn[q];
                 S1 += v1[q];
                 S2 += v2[q];
             }
     }
+    red[0][grp][cl] = n;
+    red[1][grp][cl] = S1;
+    red[2][grp][cl] = S2;
+    __syncthreads();
+    if (grp != 0) return;  // whole waves
+    n = S1 = S2 = 0.0;
+#pragma unroll
+    for (int g = 0; g < kGMergeGroups; ++g) {
+        n += red[0][g][cl];
+        S1 += red[1][g][cl];
+        S2 += red[2][g][cl];
+    }
     const double nprev = n_old[mc];
-    const int64_t o = static_cast<int64_t>(mc) * d + col;
+    const int64_t o = static_cast<int64_t>(mc) * d + cr;
     const double smu_old = gsmu[o];
     const double ssig_old = gssig[o];
-    const double shift = nprev > 0.0 ? smu_old / nprev : 0.0;
+    const double shift = gmm_shift(smu_old, nprev);
     const double b = static_cast<double>(beta);
     double mean_T = 0.0, m2_T = 0.0, cross = 0.0;
     if (n > 0.0) {
@@ -350,13 +462,22 @@ __global__ void gmm_merge_kernel(int d, int K, int64_t nchunk, const double* __r
         m2_T = S2 - S1 * (S1 / n);
         if (m2_T < 0.0) m2_T = 0.0;
         if (nprev > 0.0) {
-            const double dm = mean_T - shift;
+            const double dm = mean_T - smu_old / nprev;
             cross = dm * dm * (b * nprev * n) / (b * nprev + n);
         }
     }
-    gsmu[o] = static_cast<float>(b * smu_old + n * mean_T);
-    gssig[o] = static_cast<float>(b * ssig_old + m2_T + cross);
-    if (col == 0) gn[mc] = static_cast<float>(b * nprev + n);
+    const float n_new = static_cast<float>(b * nprev + n);
+    const float smu_new = static_cast<float>(b * smu_old + n * mean_T);
+    const float ssig_new = static_cast<float>(b * ssig_old + m2_T + cross);
+    double acc = 0.0;
+    if (col < d) {
+        gsmu[o] = smu_new;
+        gssig[o] = ssig_new;
+        if (col == 0) gn[mc] = n_new;
+        acc = gmm_coef(n_new, smu_new, ssig_new, var_floor, d, mc, col, coef);
+    }
+    acc = wave_sum_u(acc);
+    if (cl == 0) cst[mc * kGMaxParts + blockIdx.x] = acc;
 }
 
 template <bool BF16, int K>
@@ -364,7 +485,7 @@ hipError_t gmm_run(const void* x, int64_t T, int d, const uint8_t* mid, float* g
                    int update, float beta, float tau, float var_floor, float* M, float* resp_out, const GmmWs& w,
                    hipStream_t stream) {
     hipError_t err;
-    const int n_part = static_cast<int>(ceil_div(d, kGPrepThreads));
+    int n_part = static_cast<int>(ceil_div(d, kGPrepThreads));
     const dim3 pgrid(static_cast<unsigned>(n_part), 2 * K);
     const int64_t tok_per_block = static_cast<int64_t>(kGThreads / kWave) * kGTokPerWave;
     const dim3 lgrid(static_cast<unsigned>(ceil_div(T, tok_per_block)));
@@ -380,17 +501,20 @@ hipError_t gmm_run(const void* x, int64_t T, int d, const uint8_t* mid, float* g
     }
     if (update) {
         const int64_t nchunk = ceil_div(T, kGChunk);
-        const dim3 grid(static_cast<unsigned>(nchunk), static_cast<unsigned>(ceil_div(d, kGPartCols)), 2);
+        const dim3 grid(static_cast<unsigned>(nchunk), static_cast<unsigned>(ceil_div(d, kWave * gmm_part_cols(K))));
         hipLaunchKernelGGL((gmm_partial_kernel<BF16, K>), grid, dim3(256), 0, stream, x, T, d, mid, resp, gn, gsmu,
                            w.wsum, w.s1, w.s2, w.n_old);
         if ((err = hipGetLastError()) != hipSuccess) return err;
-        hipLaunchKernelGGL(gmm_merge_kernel, dim3(static_cast<unsigned>(ceil_div(d, 256)), 2 * K), dim3(256), 0,
-                           stream, d, K, nchunk, w.wsum, w.s1, w.s2, w.n_old, beta, gn, gsmu, gssig);
+        hipLaunchKernelGGL(gmm_merge_kernel, dim3(static_cast<unsigned>(ceil_div(d, kGMergeCols)), 2 * K),
+                           dim3(kGMergeCols * kGMergeGroups), 0, stream, d, K, nchunk, w.wsum, w.s1, w.s2, w.n_old,
+                           beta, var_floor, gn, gsmu, gssig, w.coef, w.cst);
+        if ((err = hipGetLastError()) != hipSuccess) return err;
+        n_part = static_cast<int>(ceil_div(d, kGMergeCols));
+    } else if (resp_out == nullptr) {  // else the E-step's coefficients are the score's
+        hipLaunchKernelGGL(gmm_prep_kernel, pgrid, dim3(kGPrepThreads), 0, stream, d, K, gn, gsmu, gssig, var_floor,
+                           w.coef, w.cst);
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }
-    hipLaunchKernelGGL(gmm_prep_kernel, pgrid, dim3(kGPrepThreads), 0, stream, d, K, gn, gsmu, gssig, var_floor,
-                       w.coef, w.cst);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
     hipLaunchKernelGGL((gmm_loglik_kernel<BF16, K>), lgrid, dim3(kGThreads), 0, stream, x, T, d, mid, w.coef, w.cst,
                        n_part, gn, 1.0 / t, 0, M, resp);
     return hipGetLastError();
