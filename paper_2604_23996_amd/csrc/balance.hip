@@ -3,13 +3,17 @@
 // specialization index (Sec. 4.1, Eq. 18-19) of one layer, from one batch's
 // routing.
 //
-//   bal_partial : per 256-token chunk: per token the bins its top-k reaches
+//   bal_partial : per 64-token chunk: per token the bins its top-k reaches
 //                 (kept for the gradient), counts C[m][e] of hard label m with
-//                 e in the token's top-k and tokens routed to each bin (wave
-//                 ballots and popcounts, summed over the four waves in wave
-//                 order: no atomics), and per expert the gate mass over the tokens
-//                 routed to its bin (fp64, fixed order).
-//   bal_finalize: one block; sums the chunk partials in chunk order, then
+//                 e in the token's top-k and tokens routed to each bin
+//                 (popcounts of transposed bit masks: no atomics), and per expert the gate
+//                 mass over the tokens routed to its bin (fp64, fixed order).
+//                 64 tokens, because the kernel is latency-bound: at 4096
+//                 tokens x 64 experts 10 us, with 256 tokens (16 blocks) and a
+//                 ballot per expert 32 us; bal_finalize then has four times the
+//                 chunks to add (9 -> 12 us).
+//   bal_finalize: one block; four thread groups sum their share of the chunk
+//                 partials in chunk order, then the groups in order; then
 //                 L_bal = sum_e N_B (n_e / T_k)(S_e / T_k), the gradient
 //                 coefficients N_B n_e / T_k^2, the EMA of the expert loads
 //                 (fp64, products rounded before the sum), f_spec, the stable
@@ -28,10 +32,12 @@ namespace smoes {
 
 namespace {
 
-constexpr int kBalChunk = 256;    // tokens per partial block
+constexpr int kBalChunk = 64;     // tokens per partial block: one per lane
 constexpr int kBalThreads = 256;  // 4 waves
 constexpr int kBalWaves = kBalThreads / kWave;
-static_assert(kBalWaves == 4, "per-wave counts are summed as four terms");
+constexpr int kFinGroups = 4;     // chunk groups of bal_finalize
+constexpr int kFinThreads = kFinGroups * 256;
+static_assert(kBalWaves == 4, "wave w counts experts 64 w .. 64 w + 63");
 
 struct BalWs {
     int32_t* cnt;    // [nchunk][2][E]
@@ -56,88 +62,52 @@ BalWs carve(void* ws, int64_t nchunk, int E, int n_bins) {
     return w;
 }
 
-// Phase 1, one thread per token of the chunk: its top-k row (k loads in
-// flight), the bins it reaches as a bit mask (n_bins <= 64, bin map in LDS);
-// counts by label and expert and tokens per bin from wave ballots (lane t of a
-// wave ends with the count of expert e0 + t, or of bin t) and popcounts, one
-// LDS row per wave. Phase 2, one wave per token with lanes over experts: gate
+// Phase 1, every wave over the chunk's tokens, one per lane: the token's top-k
+// row (k loads in flight), the bins it reaches as a bit mask (n_bins <= 64, bin
+// map in LDS); wave w counts experts 64 w .. by label, and one wave the tokens
+// per bin, as popcounts of the transposed choice bits. Phase 2, one wave per token with lanes over experts: gate
 // mass of each expert over the tokens routed to its bin (fp64, fixed order).
 __global__ void __launch_bounds__(kBalThreads)
 bal_partial_kernel(const float* __restrict__ probs, const int32_t* __restrict__ idx,
                    const uint8_t* __restrict__ mid, int64_t T, int E, int k, const int32_t* __restrict__ e2b,
                    int n_bins, int32_t* __restrict__ cnt_out, int32_t* __restrict__ tk_out,
                    double* __restrict__ mass_out, uint64_t* __restrict__ mask_out) {
-    __shared__ int32_t cnt[kBalWaves][2][256];
-    __shared__ int32_t tk[kBalWaves][64];
     __shared__ int32_t bin_s[256];
-    __shared__ uint64_t mask_s[kBalChunk];
     __shared__ double mass[kBalWaves][256];
-    const int wave = threadIdx.x / kWave, lane = lane_id();
-    for (int e = threadIdx.x; e < E; e += kBalThreads) bin_s[e] = e2b[e];
-    __syncthreads();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = lane_id();
     const int64_t j0 = static_cast<int64_t>(blockIdx.x) * kBalChunk;
     const int n = static_cast<int>(T - j0 < kBalChunk ? T - j0 : kBalChunk);
-    {
-        const int r = threadIdx.x;
-        uint64_t m = 0;
-        uint64_t b0 = 0, b1 = 0, b2 = 0, b3 = 0;  // experts chosen: bit e & 63 of word e >> 6
-        int lab = 0;
-        if (r < n) {
-            const int64_t j = j0 + r;
-            int ex[SMOES_K_MAX_DEV];
+    const int64_t j = j0 + (lane < n ? lane : 0);
+    int ex[SMOES_K_MAX_DEV];
 #pragma unroll
-            for (int s = 0; s < SMOES_K_MAX_DEV; ++s) ex[s] = s < k ? idx[j * k + s] : 0;
-            lab = mid[j] ? 1 : 0;
-#pragma unroll
-            for (int s = 0; s < SMOES_K_MAX_DEV; ++s) {
-                if (s < k) {
-                    const int e = ex[s];
-                    m |= 1ull << bin_s[e];
-                    const uint64_t bit = 1ull << (e & 63);
-                    const int blk = e >> 6;
-                    b0 |= blk == 0 ? bit : 0ull;
-                    b1 |= blk == 1 ? bit : 0ull;
-                    b2 |= blk == 2 ? bit : 0ull;
-                    b3 |= blk == 3 ? bit : 0ull;
-                }
-            }
-            mask_out[j] = m;
-        }
-        mask_s[r] = m;
-        const uint64_t eb[4] = {b0, b1, b2, b3};
-        const uint32_t l1 = static_cast<uint32_t>(lab), l0 = l1 ^ 1u;
-        // lane t ends with the counts of expert e0 + t (experts past E are never chosen)
-#pragma unroll
-        for (int blk = 0; blk < 4; ++blk) {
-            const int e0 = blk * 64;
-            if (e0 >= E) break;
-            const uint32_t lo = static_cast<uint32_t>(eb[blk]), hi = static_cast<uint32_t>(eb[blk] >> 32);
-            int c0 = 0, c1 = 0;
-#pragma unroll
-            for (int t = 0; t < 64; ++t) {
-                const uint32_t bit = t < 32 ? (lo >> t) & 1u : (hi >> (t - 32)) & 1u;
-                const int n0 = __popcll(__ballot(static_cast<int>(bit & l0)));  // every lane takes part
-                const int n1 = __popcll(__ballot(static_cast<int>(bit & l1)));
-                c0 = lane == t ? n0 : c0;
-                c1 = lane == t ? n1 : c1;
-            }
-            if (e0 + lane < E) {
-                cnt[wave][0][e0 + lane] = c0;
-                cnt[wave][1][e0 + lane] = c1;
-            }
-        }
-        // lane b ends with the tokens routed to bin b (bins past n_bins are never reached)
-        const uint32_t mlo = static_cast<uint32_t>(m), mhi = static_cast<uint32_t>(m >> 32);
-        int cb = 0;
-#pragma unroll
-        for (int b = 0; b < 64; ++b) {
-            const uint32_t bit = b < 32 ? (mlo >> b) & 1u : (mhi >> (b - 32)) & 1u;
-            const int nb = __popcll(__ballot(static_cast<int>(bit)));  // every lane takes part
-            cb = lane == b ? nb : cb;
-        }
-        if (lane < n_bins) tk[wave][lane] = cb;
-    }
+    for (int s = 0; s < SMOES_K_MAX_DEV; ++s) ex[s] = s < k ? idx[j * k + s] : 0;
+    const uint64_t text = __ballot(mid[j] != 0);  // lanes past the chunk chose nothing
+    for (int e = threadIdx.x; e < E; e += kBalThreads) bin_s[e] = e2b[e];
     __syncthreads();
+    uint64_t m = 0, mine = 0;  // bins reached; experts 64 wave .. chosen
+#pragma unroll
+    for (int s = 0; s < SMOES_K_MAX_DEV; ++s) {
+        if (s < k) {
+            m |= 1ull << bin_s[ex[s]];
+            mine |= (ex[s] >> 6) == wave ? 1ull << (ex[s] & 63) : 0ull;
+        }
+    }
+    if (lane >= n) m = mine = 0;
+    if (wave == 0 && lane < n) mask_out[j] = m;
+    if (wave * 64 < E) {
+        // lane t: the tokens that chose expert 64 wave + t, by label
+        const uint64_t chose = wave_transpose_bits(mine);
+        const int c1 = __popcll(chose & text), c0 = __popcll(chose & ~text);
+        const int e = wave * 64 + lane;
+        if (e < E) {
+            cnt_out[static_cast<int64_t>(blockIdx.x) * 2 * E + e] = c0;
+            cnt_out[static_cast<int64_t>(blockIdx.x) * 2 * E + E + e] = c1;
+        }
+    }
+    if (wave == kBalWaves - 1) {  // the wave with the fewest experts
+        const int cb = __popcll(wave_transpose_bits(m));  // tokens routed to bin `lane`
+        if (lane < n_bins) tk_out[static_cast<int64_t>(blockIdx.x) * n_bins + lane] = cb;
+    }
     int bin_of[4];
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -145,27 +115,33 @@ bal_partial_kernel(const float* __restrict__ probs, const int32_t* __restrict__ 
         const int e = lane + q * kWave;
         bin_of[q] = e < E ? bin_s[e] : 0;
     }
-#pragma unroll 4
-    for (int r = wave; r < n; r += kBalWaves) {
-        const uint64_t bins = mask_s[r];
-        const float* row = probs + (j0 + r) * E;
+    // tokens wave, wave + 4, ... four at a time: their rows are loaded before they are added
+    constexpr int U = 4;
+    for (int r0 = wave; r0 < n; r0 += U * kBalWaves) {
+        float g[U][4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int e = lane + q * kWave;
-            if (e < E && ((bins >> bin_of[q]) & 1ull)) acc[q] += static_cast<double>(row[e]);
+        for (int u = 0; u < U; ++u) {
+            const int r = r0 + u * kBalWaves < n ? r0 + u * kBalWaves : r0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int e = lane + q * kWave;
+                g[u][q] = q * kWave < E ? probs[(j0 + r) * E + (e < E ? e : 0)] : 0.0f;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int r = r0 + u * kBalWaves;
+            if (r >= n) break;  // uniform
+            const uint64_t bins = (static_cast<uint64_t>(__builtin_amdgcn_readlane(static_cast<int>(m >> 32), r)) << 32) |
+                                  static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(m), r));
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (q * kWave < E && ((bins >> bin_of[q]) & 1ull)) acc[q] += static_cast<double>(g[u][q]);
         }
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) mass[wave][lane + q * kWave] = acc[q];
     __syncthreads();
-    int32_t* co = cnt_out + static_cast<int64_t>(blockIdx.x) * 2 * E;
-    for (int i = threadIdx.x; i < 2 * E; i += kBalThreads) {
-        const int l = i / E, e = i % E;
-        co[i] = (cnt[0][l][e] + cnt[1][l][e]) + (cnt[2][l][e] + cnt[3][l][e]);
-    }
-    if (threadIdx.x < n_bins)
-        tk_out[static_cast<int64_t>(blockIdx.x) * n_bins + threadIdx.x] =
-            (tk[0][threadIdx.x] + tk[1][threadIdx.x]) + (tk[2][threadIdx.x] + tk[3][threadIdx.x]);
     for (int e = threadIdx.x; e < E; e += kBalThreads) {
         double sum = 0.0;
         for (int w = 0; w < kBalWaves; ++w) sum += mass[w][e];  // wave order
@@ -173,68 +149,78 @@ bal_partial_kernel(const float* __restrict__ probs, const int32_t* __restrict__ 
     }
 }
 
-// Fixed-order sum of one double per thread over the block (256 threads).
+// Fixed-order sum of one double per thread over the block's first four waves
+// (the other threads pass 0); sh holds four doubles.
 __device__ __forceinline__ double block_sum_f64(double v, double* sh) {
-    sh[threadIdx.x] = v;
+    const double w = wave_sum_u(v);
+    if (threadIdx.x < 256 && lane_id() == 0) sh[threadIdx.x / kWave] = w;
     __syncthreads();
-    for (int s = kBalThreads / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-        __syncthreads();
-    }
-    const double r = sh[0];
+    const double r = (sh[0] + sh[1]) + (sh[2] + sh[3]);
     __syncthreads();
     return r;
 }
 
-__global__ void __launch_bounds__(kBalThreads)
+__global__ void __launch_bounds__(kFinThreads)
 bal_finalize_kernel(int64_t nchunk, int E, int n_bins, const int32_t* __restrict__ cnt_in,
                     const int32_t* __restrict__ tk_in, const double* __restrict__ mass_in, double beta,
                     double* __restrict__ load_ema, int32_t* __restrict__ counts, double* __restrict__ fspec_out,
                     int32_t* __restrict__ e2b_next, const int32_t* __restrict__ e2b, float* __restrict__ bal_loss,
                     float* __restrict__ msi_out, double* __restrict__ coef) {
+    __shared__ int32_t tk_g[kFinGroups][64];
+    __shared__ int32_t cnt_g[kFinGroups][2][256];
+    __shared__ double mass_g[kFinGroups][256];
     __shared__ int32_t tk[64];
     __shared__ double fs[256];
-    __shared__ double red[kBalThreads];
-    const int e = threadIdx.x;  // E <= 256 = blockDim
+    __shared__ double red[4];
+    const int e = threadIdx.x & 255, grp = threadIdx.x >> 8;  // E <= 256
+    const bool first = grp == 0;
     const int NB = E / n_bins;
+    const int64_t len = ceil_div(nchunk, kFinGroups);
+    const int64_t lo = grp * len, hi = lo + len < nchunk ? lo + len : nchunk;
     constexpr int B = 8;  // chunk loads in flight; the sums still run in chunk order
-    if (e < n_bins) {
-        int32_t s = 0;
-        for (int64_t c0 = 0; c0 < nchunk; c0 += B) {
-            int32_t v[B];
-#pragma unroll
-            for (int q = 0; q < B; ++q) v[q] = c0 + q < nchunk ? tk_in[(c0 + q) * n_bins + e] : 0;
-#pragma unroll
-            for (int q = 0; q < B; ++q) s += v[q];
-        }
-        tk[e] = s;
-    }
-    int32_t cv = 0, ct = 0;
+    int32_t cv = 0, ct = 0, tb = 0;
     double S = 0.0;
-    if (e < E) {
-        for (int64_t c0 = 0; c0 < nchunk; c0 += B) {
-            int32_t vv[B], vt[B];
-            double vm[B];
+    const int er = e < E ? e : 0, br = e < n_bins ? e : 0;
+    for (int64_t c0 = lo; c0 < hi; c0 += B) {
+        int32_t vv[B], vt[B], vb[B];
+        double vm[B];
 #pragma unroll
-            for (int q = 0; q < B; ++q) {
-                const int64_t c = c0 + q < nchunk ? c0 + q : c0;
-                vv[q] = cnt_in[c * 2 * E + e];
-                vt[q] = cnt_in[c * 2 * E + E + e];
-                vm[q] = mass_in[c * E + e];
+        for (int q = 0; q < B; ++q) {
+            const int64_t c = c0 + q < hi ? c0 + q : c0;
+            vv[q] = cnt_in[c * 2 * E + er];
+            vt[q] = cnt_in[c * 2 * E + E + er];
+            vm[q] = mass_in[c * E + er];
+            vb[q] = tk_in[c * n_bins + br];
+        }
+#pragma unroll
+        for (int q = 0; q < B; ++q)
+            if (c0 + q < hi) {
+                cv += vv[q];
+                ct += vt[q];
+                S += vm[q];
+                tb += vb[q];
             }
+    }
+    cnt_g[grp][0][e] = cv;
+    cnt_g[grp][1][e] = ct;
+    mass_g[grp][e] = S;
+    if (e < 64) tk_g[grp][e] = tb;
+    __syncthreads();
+    cv = ct = 0;
+    S = 0.0;
+    if (first && e < E) {
 #pragma unroll
-            for (int q = 0; q < B; ++q)
-                if (c0 + q < nchunk) {
-                    cv += vv[q];
-                    ct += vt[q];
-                    S += vm[q];
-                }
+        for (int g = 0; g < kFinGroups; ++g) {
+            cv += cnt_g[g][0][e];
+            ct += cnt_g[g][1][e];
+            S += mass_g[g][e];
         }
     }
+    if (first && e < n_bins) tk[e] = (tk_g[0][e] + tk_g[1][e]) + (tk_g[2][e] + tk_g[3][e]);
     __syncthreads();
     // Eq. 16 and its gradient coefficients
     double term = 0.0;
-    if (e < E) {
+    if (first && e < E) {
         const int32_t Tk = tk[e2b[e]];
         const double n_e = static_cast<double>(cv) + static_cast<double>(ct);
         double c = 0.0;
@@ -250,10 +236,10 @@ bal_finalize_kernel(int64_t nchunk, int E, int n_bins, const int32_t* __restrict
         }
     }
     const double L = block_sum_f64(term, red);
-    if (e == 0 && bal_loss != nullptr) bal_loss[0] = static_cast<float>(L);
+    if (threadIdx.x == 0 && bal_loss != nullptr) bal_loss[0] = static_cast<float>(L);
     // Eq. 10: EMA of the expert loads (rows: vision, text), products rounded before the sum
     double f = 0.5;
-    if (e < E) {
+    if (first && e < E) {
         double lv = cv, lt = ct;
         if (load_ema != nullptr) {
             const double a = 1.0 - beta;
@@ -268,17 +254,24 @@ bal_finalize_kernel(int64_t nchunk, int E, int n_bins, const int32_t* __restrict
         if (fspec_out != nullptr) fspec_out[e] = f;
     }
     __syncthreads();
-    // stable ascending rank -> consecutive bins of N_B
-    if (e < E && e2b_next != nullptr) {
+    // stable ascending rank -> consecutive bins of N_B; each group ranks a quarter of the pairs
+    if (e2b_next != nullptr) {
         int rank = 0;
-        for (int q = 0; q < E; ++q) rank += (fs[q] < f || (fs[q] == f && q < e)) ? 1 : 0;
-        e2b_next[e] = rank / NB;
+        if (e < E) {
+            const double fe = fs[e];
+            const int q0 = grp * 64, q1 = q0 + 64 < E ? q0 + 64 : E;
+            for (int q = q0; q < q1; ++q) rank += (fs[q] < fe || (fs[q] == fe && q < e)) ? 1 : 0;
+        }
+        cnt_g[grp][0][e] = rank;
+        __syncthreads();
+        if (first && e < E)
+            e2b_next[e] = ((cnt_g[0][0][e] + cnt_g[1][0][e]) + (cnt_g[2][0][e] + cnt_g[3][0][e])) / NB;
     }
-    // Eq. 18-19 on this batch's counts
-    const double tot_v = block_sum_f64(e < E ? static_cast<double>(cv) : 0.0, red);
-    const double tot_t = block_sum_f64(e < E ? static_cast<double>(ct) : 0.0, red);
+    // Eq. 18-19 on this batch's counts (integers: exact in any order)
+    const double tot_v = block_sum_f64(static_cast<double>(cv), red);
+    const double tot_t = block_sum_f64(static_cast<double>(ct), red);
     double dev = 0.0;
-    if (e < E) {
+    if (first && e < E) {
         const double nv = tot_v > 0.0 ? cv / tot_v : 0.0;
         const double nt = tot_t > 0.0 ? ct / tot_t : 0.0;
         const double den = nt + nv;
@@ -286,7 +279,7 @@ bal_finalize_kernel(int64_t nchunk, int E, int n_bins, const int32_t* __restrict
         dev = 2.0 * fabs(c_text - 0.5);
     }
     const double msi = block_sum_f64(dev, red) / E;
-    if (e == 0 && msi_out != nullptr) msi_out[0] = static_cast<float>(msi);
+    if (threadIdx.x == 0 && msi_out != nullptr) msi_out[0] = static_cast<float>(msi);
 }
 
 __global__ void __launch_bounds__(kBalThreads)
@@ -350,7 +343,7 @@ hipError_t launch_binning(const float* probs, const int32_t* topk_idx, const uin
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }
     const double b = static_cast<double>(beta);
-    hipLaunchKernelGGL(bal_finalize_kernel, dim3(1), dim3(kBalThreads), 0, stream, nchunk, E, n_bins, w.cnt,
+    hipLaunchKernelGGL(bal_finalize_kernel, dim3(1), dim3(kFinThreads), 0, stream, nchunk, E, n_bins, w.cnt,
                        w.tk, w.mass, b, load_ema, counts, f_spec, expert_to_bin_next, expert_to_bin, bal_loss,
                        msi, w.coef);
     if ((err = hipGetLastError()) != hipSuccess) return err;

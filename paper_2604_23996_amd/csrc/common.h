@@ -127,6 +127,26 @@ __device__ __forceinline__ int wave_min_u(int v) {
     return ab < cd ? ab : cd;
 }
 
+// Transpose of the wave's 64 x 64 bit matrix (lane l's word is row l): lane t
+// ends with the mask of the lanes whose bit t was set. Six exchanges, where a
+// ballot per bit takes 64 and one lane select each. Needs all 64 lanes active.
+__device__ __forceinline__ uint64_t wave_transpose_bits(uint64_t w) {
+    const int lane = lane_id();
+    auto step = [&](int j, uint64_t low) {  // low: the bit positions whose bit j is clear
+        const uint32_t plo = static_cast<uint32_t>(__shfl_xor(static_cast<int>(w), j, kWave));
+        const uint32_t phi = static_cast<uint32_t>(__shfl_xor(static_cast<int>(w >> 32), j, kWave));
+        const uint64_t p = (static_cast<uint64_t>(phi) << 32) | plo;
+        w = (lane & j) == 0 ? (w & low) | ((p & low) << j) : (w & ~low) | ((p & ~low) >> j);
+    };
+    step(32, 0x00000000ffffffffull);
+    step(16, 0x0000ffff0000ffffull);
+    step(8, 0x00ff00ff00ff00ffull);
+    step(4, 0x0f0f0f0f0f0f0f0full);
+    step(2, 0x3333333333333333ull);
+    step(1, 0x5555555555555555ull);
+    return w;
+}
+
 __host__ __device__ __forceinline__ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 __host__ __device__ __forceinline__ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }

@@ -1,18 +1,22 @@
 // Expert-contiguous permutation of the routed (token, slot) pairs: a stable
 // counting sort by expert with tokens ascending inside each expert.
 //
-//   perm_count  : per 256-token chunk, per-expert counts: for every expert a
-//                 wave ballot of the lanes (tokens) that chose it and a
-//                 popcount, the four waves' counts summed in wave order.
+//   perm_count  : per 256-token chunk, per-expert counts: the choices of a
+//                 wave's 64 tokens as a bit matrix, transposed, so that each
+//                 expert has the mask of the lanes (tokens) that chose it, and
+//                 a popcount; the four waves' counts summed in wave order.
 //   perm_scatter: per chunk; every block sums the chunk counts itself (per
 //                 expert: the total and the part before its chunk), scans the
-//                 totals over experts, and places its rows: for every expert a
-//                 wave ballot marks the lanes (tokens) that chose it, so the
-//                 rank of a token among the chunk's earlier tokens is a
-//                 popcount. Counts and row order come from ballots and
+//                 totals over experts, and places its rows: the same masks
+//                 make the rank of a token among the chunk's earlier tokens a
+//                 popcount. Counts and row order come from bit masks and
 //                 prefix sums only, never from atomics. Block 0 also writes
 //                 expert_offsets and, when asked, the grouped GEMMs' work
-//                 tables.
+//                 tables. Up to 256 tokens (one chunk, as in a decode step) the
+//                 totals are the block's own popcounts and perm_count is not
+//                 launched: 6 us at 32 tokens x 64 experts, where the two
+//                 dependent launches took 5 + 10 us. At 4096 tokens 4 + 7 us
+//                 (with one ballot and one LDS store per expert 6 + 11 us).
 // Row gathers (x_perm) copy 16-byte vectors with consecutive lanes on
 // consecutive addresses of one row.
 #include "common.h"
@@ -67,20 +71,12 @@ perm_count_kernel(const int32_t* __restrict__ idx, int64_t T, int E, int k, int3
     const int64_t j = static_cast<int64_t>(blockIdx.x) * kChunk + threadIdx.x;
     int sel[SMOES_K_MAX_DEV];
     const ExpertBits eb = chosen_bits(idx, j, j < T, k, sel);
-    // lane t of the wave ends with the count of expert e0 + t (experts past E
-    // are never chosen: their ballots are empty)
+    // lane t of the wave: the count of expert e0 + t
 #pragma unroll
     for (int blk = 0; blk < 4; ++blk) {
         const int e0 = blk * 64;
         if (e0 >= E) break;
-        const uint32_t lo = static_cast<uint32_t>(eb.w[blk]), hi = static_cast<uint32_t>(eb.w[blk] >> 32);
-        int c = 0;
-#pragma unroll
-        for (int t = 0; t < 64; ++t) {
-            const uint32_t bit = t < 32 ? (lo >> t) & 1u : (hi >> (t - 32)) & 1u;
-            const int n = __popcll(__ballot(static_cast<int>(bit)));  // every lane takes part in the ballot
-            c = lane == t ? n : c;
-        }
+        const int c = __popcll(wave_transpose_bits(eb.w[blk]));
         if (e0 + lane < E) cnt[wave][e0 + lane] = c;
     }
     __syncthreads();
@@ -112,6 +108,7 @@ __device__ __forceinline__ int block_scan_incl(int v, int32_t* sc) {
     return v + add;
 }
 
+template <bool ONE>  // ONE: a single chunk, hist is not read
 __global__ void __launch_bounds__(kChunk)
 perm_scatter_kernel(const int32_t* __restrict__ idx, int64_t T, int E, int k, int64_t nchunk,
                     const int32_t* __restrict__ hist, int32_t* __restrict__ expert_offsets,
@@ -121,63 +118,61 @@ perm_scatter_kernel(const int32_t* __restrict__ idx, int64_t T, int E, int k, in
     __shared__ int32_t sc[kChunk];
     const int wave = threadIdx.x / kWave;
     const int lane = lane_id();
-    {
-        // per expert: total over all chunks and the part before this chunk (fixed order)
-        const int e = threadIdx.x;
-        int tot = 0, pre = 0;
-        if (e < E) {
-            // 32 independent loads in flight, summed in chunk order
-            for (int64_t c0 = 0; c0 < nchunk; c0 += 32) {
-                int h[32];
-#pragma unroll
-                for (int q = 0; q < 32; ++q) h[q] = c0 + q < nchunk ? hist[(c0 + q) * E + e] : 0;
-#pragma unroll
-                for (int q = 0; q < 32; ++q) {
-                    tot += h[q];
-                    pre += c0 + q < blockIdx.x ? h[q] : 0;
-                }
-            }
-        }
-        const int incl = block_scan_incl(tot, sc);
-        const int excl = incl - tot;
-        if (e < E) base_s[e] = excl + pre;
-        if (blockIdx.x == 0) {
-            if (e < E) expert_offsets[e] = excl;
-            if (e == E - 1) expert_offsets[E] = incl;
-            if (wt.work1 != nullptr) {
-                // GEMM work tables: work[g + 1] = work[g] + m_tiles(g) * n_tiles
-                const int mt = e < E ? static_cast<int>(ceil_div(tot, wt.bm)) : 0;
-                const int mt_incl = block_scan_incl(mt, sc);
-                const int shared_mt = wt.has_shared ? static_cast<int>(ceil_div(T, wt.bm)) : 0;
-                if (e == 0) {
-                    wt.work1[0] = 0;
-                    wt.work2[0] = 0;
-                }
-                if (e < E) {
-                    wt.work1[e + 1] = mt_incl * wt.nt1_r;
-                    wt.work2[e + 1] = mt_incl * wt.nt2;
-                }
-                if (e == E - 1) {
-                    wt.work1[E + 1] = mt_incl * wt.nt1_r + shared_mt * wt.nt1_s;
-                    wt.work2[E + 1] = mt_incl * wt.nt2 + shared_mt * wt.nt2;
-                }
-            }
-        }
-    }
     const int64_t j = static_cast<int64_t>(blockIdx.x) * kChunk + threadIdx.x;
     const bool live = j < T;
     int sel[SMOES_K_MAX_DEV];
     const ExpertBits eb = chosen_bits(idx, j, live, k, sel);
-    // one ballot per expert: which tokens of this wave chose it
+    // per expert: total over all chunks and the part before this chunk (fixed order)
+    const int e = threadIdx.x;
+    int tot = 0, pre = 0;
+    if (!ONE && e < E) {
+        // 32 independent loads in flight, summed in chunk order
+        for (int64_t c0 = 0; c0 < nchunk; c0 += 32) {
+            int h[32];
+#pragma unroll
+            for (int q = 0; q < 32; ++q) h[q] = hist[(c0 + q < nchunk ? c0 + q : c0) * E + e];
+#pragma unroll
+            for (int q = 0; q < 32; ++q) {
+                tot += h[q] & -static_cast<int>(c0 + q < nchunk);
+                pre += h[q] & -static_cast<int>(c0 + q < blockIdx.x);
+            }
+        }
+    }
+    // per expert (lane t: expert e0 + t): which tokens of this wave chose it
 #pragma unroll
     for (int blk = 0; blk < 4; ++blk) {
         const int e0 = blk * 64;
         if (e0 >= E) break;
-        const int ne = E - e0 < 64 ? E - e0 : 64;
-        const uint64_t mine = eb.w[blk];
-        for (int t = 0; t < ne; ++t) {
-            const uint64_t m = __ballot(static_cast<int>((mine >> t) & 1ull));
-            if (lane == 0) masks[wave][e0 + t] = m;
+        masks[wave][e0 + lane] = wave_transpose_bits(eb.w[blk]);
+    }
+    if constexpr (ONE) {
+        __syncthreads();
+        if (e < E)
+            tot = (__popcll(masks[0][e]) + __popcll(masks[1][e])) + (__popcll(masks[2][e]) + __popcll(masks[3][e]));
+    }
+    const int incl = block_scan_incl(tot, sc);
+    const int excl = incl - tot;
+    if (e < E) base_s[e] = excl + pre;
+    if (blockIdx.x == 0) {
+        if (e < E) expert_offsets[e] = excl;
+        if (e == E - 1) expert_offsets[E] = incl;
+        if (wt.work1 != nullptr) {
+            // GEMM work tables: work[g + 1] = work[g] + m_tiles(g) * n_tiles
+            const int mt = e < E ? static_cast<int>(ceil_div(tot, wt.bm)) : 0;
+            const int mt_incl = block_scan_incl(mt, sc);
+            const int shared_mt = wt.has_shared ? static_cast<int>(ceil_div(T, wt.bm)) : 0;
+            if (e == 0) {
+                wt.work1[0] = 0;
+                wt.work2[0] = 0;
+            }
+            if (e < E) {
+                wt.work1[e + 1] = mt_incl * wt.nt1_r;
+                wt.work2[e + 1] = mt_incl * wt.nt2;
+            }
+            if (e == E - 1) {
+                wt.work1[E + 1] = mt_incl * wt.nt1_r + shared_mt * wt.nt1_s;
+                wt.work2[E + 1] = mt_incl * wt.nt2 + shared_mt * wt.nt2;
+            }
         }
     }
     __syncthreads();
@@ -233,10 +228,15 @@ hipError_t launch_permute(const int32_t* topk_idx, int64_t T, int E, int k,
     WorkTables wt{};
     if (work != nullptr) wt = *work;
     hipError_t err;
+    if (nchunk == 1) {
+        hipLaunchKernelGGL(perm_scatter_kernel<true>, dim3(1), dim3(kChunk), 0, stream, topk_idx, T, E, k, nchunk,
+                           w.hist, expert_offsets, perm_token, perm_inv, wt);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(perm_count_kernel, dim3(static_cast<unsigned>(nchunk)), dim3(kChunk), 0, stream,
                        topk_idx, T, E, k, w.hist);
     if ((err = hipGetLastError()) != hipSuccess) return err;
-    hipLaunchKernelGGL(perm_scatter_kernel, dim3(static_cast<unsigned>(nchunk)), dim3(kChunk), 0, stream,
+    hipLaunchKernelGGL(perm_scatter_kernel<false>, dim3(static_cast<unsigned>(nchunk)), dim3(kChunk), 0, stream,
                        topk_idx, T, E, k, nchunk, w.hist, expert_offsets, perm_token, perm_inv, wt);
     return hipGetLastError();
 }
