@@ -43,7 +43,7 @@ def stage_work(cfg, T, merged=False, fused=False):
     """Algorithmic flops and HBM bytes of every stage for T tokens. merged:
     the GEMM1 / GEMM2 stages cover the routed and the shared experts in one
     launch (the schedule with side streams); the *_shared stages are empty.
-    fused (with merged: bf16 packed layers with shared experts): GEMM2 covers
+    fused (with merged: bf16 packed layers with shared experts of many tiles): GEMM2 covers
     the routed experts only and GEMM2_SHARED is the shared down GEMM with the
     combine in its epilogue (no shared output to HBM); the combine is empty."""
     s = 2 if cfg.dtype == "bf16" else 4
@@ -389,7 +389,8 @@ def main():
     work = stage_work(cfg, cfg.T)  # one launch per GEMM part (the serial schedule)
     # the timed schedule: routed + shared per GEMM launch, or the shared down
     # GEMM with the combine in its epilogue (bf16 packed layers with shared experts)
-    fused = spec.act_dtype == S.SMOES_BF16 and bool(spec.weights_packed) and cfg.shared_inter > 0
+    fused = (spec.act_dtype == S.SMOES_BF16 and bool(spec.weights_packed) and cfg.shared_inter > 0
+             and -(-cfg.T // 128) * -(-cfg.d // 256) >= 512)  # the library's rule (smoes.h, enum smoes_stage)
     work_m = stage_work(cfg, cfg.T, merged=True, fused=fused)
     stages = {}
     for name in S.STAGES:

@@ -346,7 +346,8 @@ typedef struct smoes_layer_io {
  * *_SHARED stages are then empty event pairs), MODALITY and then MI (after
  * ROUTE) on side[0]; the caller's stream waits for side[0] before the
  * call's work is complete. Exception, with io->streams and a bf16 layer with
- * packed weights and shared experts: GEMM2 covers the routed experts only,
+ * packed weights and shared experts of at least 512 tiles of 128 tokens x 256
+ * hidden columns (ceil(T / 128) * ceil(d / 256)): GEMM2 covers the routed experts only,
  * then GEMM2_SHARED runs the shared experts' down GEMM with the combine in
  * its epilogue (COMBINE is an empty pair, and SMOES_BUF_Y_SHARED is not
  * written); the output has the same bits as the separate combine's. */

@@ -49,6 +49,13 @@ int check_mi_shape(int64_t T, int E, int n_batch, int n_bins) {
     return SMOES_OK;
 }
 
+// Output tiles (128 tokens x 256 columns) of the shared down GEMM from which the
+// combine runs in its epilogue: two per CU. With fewer, its few long tiles run
+// better inside the routed down GEMM's launch, and the combine on its own. Layer
+// forward, fused / apart: 32 tokens x 2048 (8 tiles) 276 / 234 us, 4096 x 2048
+// (256 tiles) 668 / 660 us, 16384 x 4096 (2048 tiles) 4871 / 4906 us.
+constexpr int64_t kFuseCombineTiles = 512;
+
 // Total workspace of the standalone entry points (max alignment slack included).
 size_t route_ws(int64_t T, int d, int E, int x_dtype) {
     return router_workspace_bytes(T, d, E, x_dtype) + 2 * kAlign;
@@ -423,13 +430,14 @@ int smoes_moe_forward(const smoes_layer* L, const smoes_layer_io* io, void* work
     // GEMM covers the routed and the shared experts in one launch on s
     // (route -> permute -> GEMM1 -> GEMM2 -> combine): two concurrent GEMM
     // launches slow each other down more than they gain from overlapping.
-    // For bf16 layers with packed weights and shared experts the GEMM2 stage
-    // then runs the routed experts alone and the shared experts' GEMM2 follows
+    // For bf16 layers with packed weights and enough shared-expert tiles
+    // (kFuseCombineTiles) the GEMM2 stage then runs the routed experts alone and the shared experts' GEMM2 follows
     // with the combine in its epilogue (the shared output never goes to HBM;
     // the combine stage is an empty pair).
     const smoes_streams* sides = io->streams;
     const bool merged = sides != nullptr;
-    const bool fuse = merged && L->act_dtype == SMOES_BF16 && L->weights_packed && L->shared_inter > 0;
+    const bool fuse = merged && L->act_dtype == SMOES_BF16 && L->weights_packed && L->shared_inter > 0 &&
+                      experts_shared_down_tiles(T, L->d) >= kFuseCombineTiles;
     hipStream_t b = s;
     hipEvent_t e_fork = nullptr, e_routed = nullptr, e_join = nullptr;
     if (sides != nullptr) {

@@ -1621,6 +1621,7 @@ hipError_t launch_experts_gemm1(const ExpertArgs& a, void* ws, int part, hipStre
     return hipGetLastError();
 }
 
+int64_t experts_shared_down_tiles(int64_t T, int d) { return ceil_div(T, PK_BM) * ceil_div(d, pk_tile_cols(7)); }
 
 hipError_t launch_experts_gemm2_combine(const ExpertArgs& a, void* ws, hipStream_t stream) {
     if (!(a.act_dtype == 1 && a.packed && a.shared_inter > 0)) return hipErrorInvalidValue;

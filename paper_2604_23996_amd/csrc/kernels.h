@@ -78,6 +78,7 @@ hipError_t launch_experts_gemm2(const ExpertArgs& a, void* ws, int part, hipStre
 // The shared experts' GEMM2 with the combine in its epilogue (bf16, packed
 // weights, shared experts present): writes `out`, not Y_s; every routed row
 // of Y_r must be written before it runs.
+int64_t experts_shared_down_tiles(int64_t T, int d);  // its output tiles
 hipError_t launch_experts_gemm2_combine(const ExpertArgs& a, void* ws, hipStream_t stream);
 hipError_t launch_experts_combine(const ExpertArgs& a, void* ws, hipStream_t stream);
 // packed bf16 expert weights: elements of `batch` packed n x k matrices
