@@ -3,7 +3,7 @@
 // attn_fwd_kernel: causal softmax attention inside each sample, one
 // workgroup per (128 query rows, query head), with the modality scores of the
 // keys carried along as two extra value channels (the supplementary
-// implementation note) — here in fp32 on the vector ALUs next to the bf16
+// implementation note) — here as float32 matrix products next to the bf16
 // MFMA product of the values, so the aggregated scores keep fp32 accuracy.
 // Outputs: O[T][H][d_head] = Attn_h V (bf16) and m_heads[T][H][2] = Attn_h M
 // (Eq. 3 per head). attn_update_kernel averages m_heads over heads (Eq. 3)
@@ -34,6 +34,7 @@ namespace {
 constexpr int AT_BQ = 128;  // query rows per workgroup (4 waves x 32)
 constexpr int AT_BK = 64;   // keys per block
 constexpr int AT_THREADS = 256;
+constexpr int AT_MP = AT_BK + 8;  // pitch of the score channels' rows: four rows x two halves on distinct banks
 constexpr int kAtBufFlags = 0x00020000;
 constexpr uint32_t kAtOob = 0x80000000u;  // a byte offset past any buffer: reads return 0
 
@@ -80,17 +81,16 @@ __device__ __forceinline__ void attn_fwd_body(const uint16_t* __restrict__ q, co
     constexpr int VP = DH + 32;  // V row pitch (elements)
     __shared__ __attribute__((aligned(16))) uint16_t k_lds[AT_BK * KP];
     __shared__ __attribute__((aligned(16))) uint16_t v_lds[AT_BK * VP];
-    __shared__ __attribute__((aligned(16))) float mv_lds[2][AT_BK];
+    __shared__ __attribute__((aligned(16))) float mv_lds[4 * AT_MP];
 
     const int nqb = static_cast<int>(ceil_div(T, AT_BQ));
-    const int hq = blockIdx.y;
-    // Two workgroups share a CU: those L and L + N / 2 in dispatch order (N =
-    // all of them), i.e. heads h and h + H / 2 at the same blockIdx.x. The
-    // lower half of the heads takes the query blocks from the last (longest
-    // causal range) down, the upper half from the first up, so a CU holds a
-    // long and a short block rather than two of the same length.
-    const int qb = 2 * hq < static_cast<int>(gridDim.y) ? nqb - 1 - static_cast<int>(blockIdx.x)
-                                                      : static_cast<int>(blockIdx.x);
+    // Heads run fastest and the query blocks from the last one down, so the
+    // blocks that start last are the shortest causal ranges of the first sample
+    // and the launch ends evenly. Block b runs on XCD b % 8: a multiple of eight
+    // heads is dealt so that an XCD gets adjacent heads, which share KV heads.
+    const int hi = static_cast<int>(blockIdx.x) % H;
+    const int hq = H % 8 == 0 ? (hi % 8) * (H / 8) + hi / 8 : hi;
+    const int qb = nqb - 1 - static_cast<int>(blockIdx.x) / H;
     const int hk = hq / (H / Hkv);
     const int wave = threadIdx.x / kWave, lane = lane_id();
     const int half = lane >> 5, l32 = lane & 31;
@@ -174,8 +174,8 @@ __device__ __forceinline__ void attn_fwd_body(const uint16_t* __restrict__ q, co
             *reinterpret_cast<at_i32x4*>(vst + key * VP + c * 8) = vr[i];
         }
         if (threadIdx.x < AT_BK) {
-            mv_lds[0][threadIdx.x] = mr.x;
-            mv_lds[1][threadIdx.x] = mr.y;
+            mv_lds[threadIdx.x] = mr.x;
+            mv_lds[AT_MP + threadIdx.x] = mr.y;
         }
     };
 
@@ -183,6 +183,11 @@ __device__ __forceinline__ void attn_fwd_body(const uint16_t* __restrict__ q, co
 #pragma unroll
     for (int i = 0; i < DT; ++i) oacc[i] = f32x16_t{};
     float m_run = -INFINITY, l_run = 0.f, a0 = 0.f, a1 = 0.f;
+
+    // rows 2 and 3 of the score channels: ones (the softmax denominator) and zeros
+    if (threadIdx.x < 2 * AT_MP) mv_lds[2 * AT_MP + threadIdx.x] = threadIdx.x < AT_MP ? 1.f : 0.f;
+    // keys that some query of this wave may see
+    const int wk_lo = __builtin_amdgcn_readlane(qstart, 0), wk_hi = wq0 + 31;
 
     const int nkb = static_cast<int>(ceil_div(kend - kstart, AT_BK));
     load_block(kstart);
@@ -192,13 +197,14 @@ __device__ __forceinline__ void attn_fwd_body(const uint16_t* __restrict__ q, co
         store_block();
         __syncthreads();
         if (b + 1 < nkb) load_block(kb0 + AT_BK);  // next block's loads fly during this block's math
+        if (kb0 > wk_hi || kb0 + AT_BK <= wk_lo) continue;  // uniform; the barriers are above
         // LDS addresses are rebuilt inside the loop from an opaque zero: hoisting
         // all of them out of the loop would not fit the register budget
         int lz = 0;
         asm volatile("" : "+v"(lz));
         const uint16_t* kl = k_lds + lz;
         const uint16_t* vl = v_lds + lz;
-        const float* ml = &mv_lds[0][0] + lz;
+        const float* ml = mv_lds + (lane & 3) * AT_MP + lz;
 
         // S^T = K Q^T for the two 32-key tiles; K fragments read one slice ahead
         // (the scheduling barriers keep the compiler from hoisting every LDS
@@ -260,28 +266,31 @@ __device__ __forceinline__ void attn_fwd_body(const uint16_t* __restrict__ q, co
             for (int i = 0; i < DT; ++i) oacc[i] *= alpha;
         }
         const float m_use = m_run == -INFINITY ? 0.f : m_run;
-        float ls = 0.f, s0 = 0.f, s1 = 0.f;
+        // The score channels and the softmax denominator in float32 on the
+        // matrix cores beside the exponentials: v_mfma_f32_4x4x1 treats each
+        // group of four lanes by itself, so with lane c of a group holding
+        // channel c of a key (vision, text, 1, 0) and every lane the key's
+        // probability for its own query, element c of a lane's result is its
+        // query's sum of channel c. (Three FMAs per probability on the vector
+        // ALUs, which bound the block, became one 8-cycle matrix instruction.)
+        f32x4_t sc[2] = {f32x4_t{}, f32x4_t{}};
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 __builtin_amdgcn_sched_barrier(0);
                 const int kk = t * 32 + 8 * g + 4 * half;  // four consecutive keys of this lane
-                const float4 mv = *reinterpret_cast<const float4*>(ml + kk);
-                const float4 mt = *reinterpret_cast<const float4*>(ml + AT_BK + kk);
-                const float mva[4] = {mv.x, mv.y, mv.z, mv.w}, mta[4] = {mt.x, mt.y, mt.z, mt.w};
+                const f32x4_t mc = *reinterpret_cast<const f32x4_t*>(ml + kk);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const float p = __builtin_amdgcn_exp2f(fmaf(s[t][4 * g + e], scale_log2, -m_use));
                     s[t][4 * g + e] = p;
-                    ls += p;
-                    s0 = fmaf(p, mva[e], s0);
-                    s1 = fmaf(p, mta[e], s1);
+                    sc[t] = __builtin_amdgcn_mfma_f32_4x4x1f32(mc[e], p, sc[t], 0, 0, 0);
                 }
             }
-        l_run += ls;
-        a0 += s0;
-        a1 += s1;
+        a0 += sc[0][0] + sc[1][0];
+        a1 += sc[0][1] + sc[1][1];
+        l_run += sc[0][2] + sc[1][2];
         // O^T += V^T P^T over four 16-key slices
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -398,7 +407,7 @@ hipError_t launch_attention(const void* q, const void* k, const void* v, int64_t
                             const int32_t* sample_offsets, int n_batch, const float* m_in, float scale, void* o,
                             float* m_heads, hipStream_t stream) {
     if (T == 0) return hipSuccess;
-    const dim3 grid(static_cast<unsigned>(ceil_div(T, AT_BQ)), static_cast<unsigned>(H));
+    const dim3 grid(static_cast<unsigned>(ceil_div(T, AT_BQ) * H));
     const float scale_log2 = scale * 1.4426950408889634f;
     if (head_dim == 128)
         hipLaunchKernelGGL(attn_fwd_kernel_d128, grid, dim3(AT_THREADS), 0, stream, static_cast<const uint16_t*>(q),
