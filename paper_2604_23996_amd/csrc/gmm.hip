@@ -16,7 +16,7 @@
 //     the chunks in a fixed order, applies Eq. 5-7 with the weighted batch
 //     count, mean and centred sum of squares, and writes the score's
 //     coefficients of the new state, as gmm_prep does for the old one.
-// At 8192 x 2048 bf16 and K = 2 (33.6 MB) an update and a score take 4 + 18 + 24
+// At 8192 x 2048 bf16 and K = 2 (33.6 MB) an update and a score take 4 + 18 + 18
 // + 10 + 16 us, bound by latency and by the address unit (the coefficients come
 // through L1 once per wave, so a wave takes four tokens). Before, 5 + 27 + 42 +
 // 21 + 5 + 25: gmm_partial read every row's label before it loaded the row, once
@@ -37,7 +37,7 @@ constexpr int kGMergeGroups = 8;    // chunk groups per column
 constexpr int kGMaxParts = 256;     // SMOES_D_MAX / kGMergeCols: parts of a log-variance sum
 constexpr int kGTokPerWave = 4;
 constexpr int kGThreads = 256;
-// columns per lane of gmm_partial: 4, or 2 where the sums of 6 or 8 components would not leave two waves a SIMD
+// columns per lane of gmm_partial: 4, or 2 where the sums of 3 or 4 components would not leave four waves a SIMD
 constexpr int gmm_part_cols(int K) { return K <= 2 ? 4 : 2; }
 
 struct GmmWs {
@@ -252,9 +252,10 @@ gmm_loglik_kernel(const void* __restrict__ x, int64_t T, int d, const uint8_t* _
 __device__ __forceinline__ float gmm_shift(double smu, double n) { return n > 0.0 ? static_cast<float>(smu / n) : 0.0f; }
 
 // Weighted sums over a chunk of tokens: 4 waves split the rows, each lane owns
-// two or four columns and sums every row into the components of the row's modality
-// (uniform per row: the labels are one bit each); a group of eight rows is
-// loaded before it is added. Fixed-order tree over the waves, lanes adjacent.
+// CPL columns. One modality after the other (the labels are one bit each), so
+// that one modality's sums are live: the wave's rows of the modality in groups
+// of eight, loaded together, then added in row order. Fixed-order tree over
+// the waves, lanes adjacent.
 template <bool BF16, int K>
 __global__ void __launch_bounds__(256)
 gmm_partial_kernel(const void* __restrict__ x, int64_t T, int d, const uint8_t* __restrict__ mid,
@@ -265,6 +266,7 @@ gmm_partial_kernel(const void* __restrict__ x, int64_t T, int d, const uint8_t* 
     constexpr int CPL = gmm_part_cols(K);
     constexpr int NV = K * CPL * 2;  // sums of one modality
     __shared__ double red[2][NV][kWave];
+    __shared__ double wred[4][MC];
     __shared__ float resp_s[kGChunk][K];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int lane = lane_id();
@@ -278,88 +280,83 @@ gmm_partial_kernel(const void* __restrict__ x, int64_t T, int d, const uint8_t* 
     static_assert(kGChunk == kWave, "one label per lane");
     const uint64_t text = __ballot(lane < nr && mid[r0 + (lane < nr ? lane : 0)] != 0);
     for (int i = threadIdx.x; i < nr * K; i += 256) resp_s[i / K][i % K] = resp[r0 * K + i];
-
-    constexpr int U = 8, NG = kGChunk / (4 * U);
-    constexpr int NW = BF16 ? CPL / 2 : CPL;
-    uint32_t v[U][NW];
-    auto load = [&](int g) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int r = wave + 4 * (g * U + u);
-            const int64_t e = (r0 + (r < nr ? r : 0)) * d + c0;
-            const uint32_t* q = BF16 ? reinterpret_cast<const uint32_t*>(static_cast<const uint16_t*>(x) + e)
-                                     : reinterpret_cast<const uint32_t*>(static_cast<const float*>(x) + e);
-            if constexpr (NW == 1) {
-                v[u][0] = q[0];
-            } else if constexpr (NW == 2) {
-                const uint2 w = *reinterpret_cast<const uint2*>(q);
-                v[u][0] = w.x;
-                v[u][1] = w.y;
-            } else {
-                const uint4 w = *reinterpret_cast<const uint4*>(q);
-                v[u][0] = w.x;
-                v[u][1] = w.y;
-                v[u][2] = w.z;
-                v[u][3] = w.w;
-            }
-        }
-    };
-    load(0);
-    float sh[MC][CPL];
-    double s1[MC][CPL], s2[MC][CPL], ws[MC];
-#pragma unroll
-    for (int j = 0; j < MC; ++j) {
-        const double n = gn[j];
-        ws[j] = 0.0;
-#pragma unroll
-        for (int i = 0; i < CPL; ++i) {
-            sh[j][i] = gmm_shift(gsmu[static_cast<int64_t>(j) * d + c0 + i], n);
-            s1[j][i] = s2[j][i] = 0.0;
-        }
-    }
     __syncthreads();
-    auto add_row = [&](auto m_c, int u, int r) {
-        constexpr int m = decltype(m_c)::value;
-        float xv[CPL];
-#pragma unroll
-        for (int i = 0; i < CPL; ++i)
-            xv[i] = BF16 ? __uint_as_float(i & 1 ? v[u][i / 2] & 0xffff0000u : v[u][i / 2] << 16)
-                         : __uint_as_float(v[u][i]);
+
+    constexpr int U = 8;
+    constexpr int NW = BF16 ? CPL / 2 : CPL;
+    const uint64_t mine = (0x1111111111111111ull << wave) & (nr == kGChunk ? ~0ull : (1ull << nr) - 1);
+#pragma unroll 1
+    for (int m = 0; m < 2; ++m) {
+        uint64_t left = mine & (m ? text : ~text);
+        float sh[K][CPL];
+        double s1[K][CPL], s2[K][CPL], ws[K];
 #pragma unroll
         for (int c = 0; c < K; ++c) {
-            const double w = static_cast<double>(resp_s[r][c]);
-            ws[m * K + c] += w;
+            const double n = gn[m * K + c];
+            ws[c] = 0.0;
 #pragma unroll
             for (int i = 0; i < CPL; ++i) {
-                const double y = static_cast<double>(xv[i]) - static_cast<double>(sh[m * K + c][i]);
-                const double wy = w * y;
-                s1[m * K + c][i] += wy;
-                s2[m * K + c][i] = fma(wy, y, s2[m * K + c][i]);
+                sh[c][i] = gmm_shift(gsmu[static_cast<int64_t>(m * K + c) * d + c0 + i], n);
+                s1[c][i] = s2[c][i] = 0.0;
             }
         }
-    };
+        while (left != 0) {  // uniform
+            uint32_t v[U][NW];
+            int row[U];
+            int n = 0;
 #pragma unroll
-    for (int g = 0; g < NG; ++g) {
-        if (wave + 4 * g * U >= nr) break;  // uniform
-        if (g > 0) load(g);
+            for (int u = 0; u < U; ++u) {
+                if (left == 0) break;
+                row[u] = __builtin_ctzll(left);
+                left &= left - 1;
+                ++n;
+                const int64_t e = (r0 + row[u]) * d + c0;
+                const uint32_t* q = BF16 ? reinterpret_cast<const uint32_t*>(static_cast<const uint16_t*>(x) + e)
+                                         : reinterpret_cast<const uint32_t*>(static_cast<const float*>(x) + e);
+                if constexpr (NW == 1) {
+                    v[u][0] = q[0];
+                } else if constexpr (NW == 2) {
+                    const uint2 w = *reinterpret_cast<const uint2*>(q);
+                    v[u][0] = w.x;
+                    v[u][1] = w.y;
+                } else {
+                    const uint4 w = *reinterpret_cast<const uint4*>(q);
+                    v[u][0] = w.x;
+                    v[u][1] = w.y;
+                    v[u][2] = w.z;
+                    v[u][3] = w.w;
+                }
+            }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int r = wave + 4 * (g * U + u);
-            if (r >= nr) break;  // uniform
-            if ((text >> r) & 1ull) add_row(std::integral_constant<int, 1>{}, u, r);
-            else add_row(std::integral_constant<int, 0>{}, u, r);
+            for (int u = 0; u < U; ++u) {
+                if (u >= n) break;
+                float xv[CPL];
+#pragma unroll
+                for (int i = 0; i < CPL; ++i)
+                    xv[i] = BF16 ? __uint_as_float(i & 1 ? v[u][i / 2] & 0xffff0000u : v[u][i / 2] << 16)
+                                 : __uint_as_float(v[u][i]);
+#pragma unroll
+                for (int c = 0; c < K; ++c) {
+                    const double w = static_cast<double>(resp_s[row[u]][c]);
+                    ws[c] += w;
+#pragma unroll
+                    for (int i = 0; i < CPL; ++i) {
+                        const double y = static_cast<double>(xv[i]) - static_cast<double>(sh[c][i]);
+                        const double wy = w * y;
+                        s1[c][i] += wy;
+                        s2[c][i] = fma(wy, y, s2[c][i]);
+                    }
+                }
+            }
         }
-    }
-    // per modality: (w0 + w2) + (w1 + w3)
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {
+        // (w0 + w2) + (w1 + w3)
         auto put = [&](int slot) {
 #pragma unroll
             for (int c = 0; c < K; ++c)
 #pragma unroll
                 for (int i = 0; i < CPL; ++i) {
-                    red[slot][(c * CPL + i) * 2][lane] = s1[m * K + c][i];
-                    red[slot][(c * CPL + i) * 2 + 1][lane] = s2[m * K + c][i];
+                    red[slot][(c * CPL + i) * 2][lane] = s1[c][i];
+                    red[slot][(c * CPL + i) * 2 + 1][lane] = s2[c][i];
                 }
         };
         auto add = [&](int slot) {
@@ -367,10 +364,15 @@ gmm_partial_kernel(const void* __restrict__ x, int64_t T, int d, const uint8_t* 
             for (int c = 0; c < K; ++c)
 #pragma unroll
                 for (int i = 0; i < CPL; ++i) {
-                    s1[m * K + c][i] += red[slot][(c * CPL + i) * 2][lane];
-                    s2[m * K + c][i] += red[slot][(c * CPL + i) * 2 + 1][lane];
+                    s1[c][i] += red[slot][(c * CPL + i) * 2][lane];
+                    s2[c][i] += red[slot][(c * CPL + i) * 2 + 1][lane];
                 }
         };
+        // weight sums: every lane of a wave saw the same rows; lane 0 reports
+        if (lane == 0) {
+#pragma unroll
+            for (int c = 0; c < K; ++c) wred[wave][m * K + c] = ws[c];
+        }
         if (wave >= 2) put(wave - 2);
         __syncthreads();
         if (wave < 2) add(wave);
@@ -385,20 +387,13 @@ gmm_partial_kernel(const void* __restrict__ x, int64_t T, int d, const uint8_t* 
 #pragma unroll
                     for (int i = 0; i < CPL; ++i) {
                         const int64_t o = (chunk * MC + m * K + c) * d + col0 + i;
-                        s1g[o] = s1[m * K + c][i];
-                        s2g[o] = s2[m * K + c][i];
+                        s1g[o] = s1[c][i];
+                        s2g[o] = s2[c][i];
                     }
             }
         }
         __syncthreads();
     }
-    // weight sums: every lane of a wave saw the same rows; lane 0 reports
-    double(*wred)[MC] = reinterpret_cast<double(*)[MC]>(&red[0][0][0]);
-    if (lane == 0) {
-#pragma unroll
-        for (int j = 0; j < MC; ++j) wred[wave][j] = ws[j];
-    }
-    __syncthreads();
     if (blockIdx.y == 0 && threadIdx.x < MC)
         wsum[chunk * MC + threadIdx.x] = (wred[0][threadIdx.x] + wred[2][threadIdx.x]) +
                                          (wred[1][threadIdx.x] + wred[3][threadIdx.x]);

@@ -7,11 +7,13 @@
 //       (x - shift) and (x - shift)^2, where the shift is the previous mean
 //       (rounded to float32: any constant near the mean will do), then a
 //       fixed-order LDS tree, lanes adjacent (bank-conflict free).
-//     gauss_merge: 64 columns per block; for each modality eight thread groups
+//     gauss_merge: 32 columns per block; for each modality sixteen thread groups
 //       add their share of the chunk partials in chunk order, then the groups
 //       in order; the EMA update; and, since both modalities' new statistics
 //       are at hand, the score coefficients of gauss_prep.
-//     At 16384 x 2048 bf16 (67 MB) an update and a score take 27 + 14 + 16 us;
+//     At 16384 x 2048 bf16 (67 MB) an update and a score take 22 + 8 + 16 us
+//     (27 + 14 with both modalities' sums live, which left two waves a SIMD,
+//     and 64 columns per merge block);
 //     with an LDS tree that had all lanes on one bank, a merge of 64 one-wave
 //     blocks that walked 256 chunks with 16 loads in flight, a gauss_prep of
 //     its own and one stripe of the score in flight, 40 + 32 + 5 + 22 us.
@@ -37,13 +39,13 @@ constexpr int kColsPerBlock = 512; // 64 lanes x 8 columns
 constexpr int kScoreTokPerWave = 2;
 constexpr int kScoreThreads = 256;
 constexpr int kPrepThreads = 256;   // columns per gauss_prep block
-constexpr int kMergeCols = 64;      // columns per gauss_merge block
-constexpr int kMergeGroups = 8;     // chunk groups per column and modality
-constexpr int kCstMax = 256;        // SMOES_D_MAX / kMergeCols: parts of the score constant
+constexpr int kMergeCols = 32;      // columns per gauss_merge block
+constexpr int kMergeGroups = 16;    // chunk groups per column and modality
+constexpr int kCstMax = 512;        // SMOES_D_MAX / kMergeCols: parts of the score constant
 
 struct ModalityWs {
     float* coef;       // [4][d]: mu_v, 1/s2_v, mu_t, 1/s2_t
-    double* cst;       // per block of 64 (gauss_merge) or 256 (gauss_prep) columns: sum (log s2_v - log s2_t)
+    double* cst;       // per block of 32 (gauss_merge) or 256 (gauss_prep) columns: sum (log s2_v - log s2_t)
     double* n_old;     // [2]: state counts before the update
     int32_t* counts;   // [nchunk][2]
     double* s1;        // [nchunk][2][d]
@@ -80,7 +82,7 @@ gauss_partial_kernel(const void* __restrict__ x, int64_t T, int d, const uint8_t
                      const float* __restrict__ gauss_n, const float* __restrict__ gauss_smu,
                      int32_t* __restrict__ counts, double* __restrict__ s1g, double* __restrict__ s2g,
                      double* __restrict__ n_old) {
-    __shared__ double red[2][32][kWave];
+    __shared__ double red[2][16][kWave];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int lane = lane_id();
     const int64_t chunk = blockIdx.x;
@@ -94,105 +96,84 @@ gauss_partial_kernel(const void* __restrict__ x, int64_t T, int d, const uint8_t
     static_assert(kChunkRows == kWave, "one label per lane");
     const uint64_t text = __ballot(lane < nr && mid[r0 + (lane < nr ? lane : 0)] != 0);
 
-    // rows wave, wave + 4, ... of the chunk in groups of U: a group's loads go
-    // out together (rows past the end read row 0), then are added in row order
+    // One modality after the other, so that one set of sums is live: this wave's
+    // rows (wave, wave + 4, ...) of the modality in groups of U, whose loads go
+    // out together and are then added in row order.
     constexpr int U = 8;
-    constexpr int NG = kChunkRows / (4 * U);
     constexpr int Q = BF16 ? 1 : 2;
-    uint4 v[U][Q];
-    auto load = [&](int g) {
+    const uint64_t mine = (0x1111111111111111ull << wave) & (nr == kChunkRows ? ~0ull : (1ull << nr) - 1);
+    const double n_prev[2] = {gauss_n[0], gauss_n[1]};
+#pragma unroll 1
+    for (int m = 0; m < 2; ++m) {
+        uint64_t left = mine & (m ? text : ~text);
+        float sh[8];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int r = wave + 4 * (g * U + u);
-            const int64_t e = (r0 + (r < nr ? r : 0)) * d + c0;
-            const uint4* q = BF16 ? reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(x) + e)
-                                  : reinterpret_cast<const uint4*>(static_cast<const float*>(x) + e);
+        for (int i = 0; i < 8; ++i) sh[i] = shift_of(gauss_smu[static_cast<int64_t>(m) * d + c0 + i], n_prev[m]);
+        double s1[8], s2[8];
 #pragma unroll
-            for (int i = 0; i < Q; ++i) v[u][i] = q[i];
-        }
-    };
-    load(0);
-    float sh[2][8];
-    {
-        const double n0 = gauss_n[0], n1 = gauss_n[1];
+        for (int i = 0; i < 8; ++i) s1[i] = s2[i] = 0.0;
+        while (left != 0) {  // uniform
+            uint4 v[U][Q];
+            int n = 0;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            sh[0][i] = shift_of(gauss_smu[c0 + i], n0);
-            sh[1][i] = shift_of(gauss_smu[d + c0 + i], n1);
-        }
-    }
-    double s1[2][8], s2[2][8];
+            for (int u = 0; u < U; ++u) {
+                if (left == 0) break;
+                const int r = __builtin_ctzll(left);
+                left &= left - 1;
+                ++n;
+                const int64_t e = (r0 + r) * d + c0;
+                const uint4* q = BF16 ? reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(x) + e)
+                                      : reinterpret_cast<const uint4*>(static_cast<const float*>(x) + e);
 #pragma unroll
-    for (int m = 0; m < 2; ++m)
+                for (int i = 0; i < Q; ++i) v[u][i] = q[i];
+            }
 #pragma unroll
-        for (int i = 0; i < 8; ++i) s1[m][i] = s2[m][i] = 0.0;
-    auto value = [&](int u, int i) -> float {
-        const uint32_t* w = reinterpret_cast<const uint32_t*>(&v[u][0]);
-        if constexpr (BF16) return __uint_as_float(i & 1 ? w[i / 2] & 0xffff0000u : w[i / 2] << 16);
-        else return __uint_as_float(w[i]);
-    };
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-        if (wave + 4 * g * U >= nr) break;  // uniform
-        if (g > 0) load(g);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int r = wave + 4 * (g * U + u);
-            if (r >= nr) break;  // uniform
-            if ((text >> r) & 1ull) {
+            for (int u = 0; u < U; ++u) {
+                if (u >= n) break;
+                const uint32_t* w = reinterpret_cast<const uint32_t*>(&v[u][0]);
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    const double y = static_cast<double>(value(u, i)) - static_cast<double>(sh[1][i]);
-                    s1[1][i] += y;
-                    s2[1][i] = fma(y, y, s2[1][i]);
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const double y = static_cast<double>(value(u, i)) - static_cast<double>(sh[0][i]);
-                    s1[0][i] += y;
-                    s2[0][i] = fma(y, y, s2[0][i]);
+                    const float xv = BF16 ? __uint_as_float(i & 1 ? w[i / 2] & 0xffff0000u : w[i / 2] << 16)
+                                          : __uint_as_float(w[i]);
+                    const double y = static_cast<double>(xv) - static_cast<double>(sh[i]);
+                    s1[i] += y;
+                    s2[i] = fma(y, y, s2[i]);
                 }
             }
         }
-    }
-    // fixed-order tree over the waves: (w0 + w2) + (w1 + w3)
-    auto put = [&](int slot) {
-#pragma unroll
-        for (int m = 0; m < 2; ++m)
+        // fixed-order tree over the waves: (w0 + w2) + (w1 + w3)
+        auto put = [&](int slot) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                red[slot][m * 8 + i][lane] = s1[m][i];
-                red[slot][16 + m * 8 + i][lane] = s2[m][i];
+                red[slot][i][lane] = s1[i];
+                red[slot][8 + i][lane] = s2[i];
             }
-    };
-    auto add = [&](int slot) {
-#pragma unroll
-        for (int m = 0; m < 2; ++m)
+        };
+        auto add = [&](int slot) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                s1[m][i] += red[slot][m * 8 + i][lane];
-                s2[m][i] += red[slot][16 + m * 8 + i][lane];
+                s1[i] += red[slot][i][lane];
+                s2[i] += red[slot][8 + i][lane];
             }
-    };
-    if (wave >= 2) put(wave - 2);
-    __syncthreads();
-    if (wave < 2) add(wave);
-    __syncthreads();
-    if (wave == 1) put(0);
-    __syncthreads();
-    if (wave == 0) {
-        add(0);
-        if (active) {
-#pragma unroll
-            for (int m = 0; m < 2; ++m)
+        };
+        if (wave >= 2) put(wave - 2);
+        __syncthreads();
+        if (wave < 2) add(wave);
+        __syncthreads();
+        if (wave == 1) put(0);
+        __syncthreads();
+        if (wave == 0) {
+            add(0);
+            if (active) {
+                const int64_t o = (chunk * 2 + m) * d + col0;
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    const int64_t o = (chunk * 2 + m) * d + col0 + i;
-                    s1g[o] = s1[m][i];
-                    s2g[o] = s2[m][i];
+                    s1g[o + i] = s1[i];
+                    s2g[o + i] = s2[i];
                 }
+            }
         }
+        __syncthreads();
     }
     if (blockIdx.y == 0 && threadIdx.x == 0) {
         const int nt = __popcll(text);
@@ -287,9 +268,10 @@ gauss_merge_kernel(int d, int64_t nchunk, const int32_t* __restrict__ counts,
         mean_var(n_new, smu_new, ssig_new, var_floor, mv[0][m][cl], mv[1][m][cl]);
     }
     __syncthreads();
-    if (threadIdx.x < kMergeCols) {  // one wave: the coefficients, and their constant's part
+    static_assert(kMergeCols <= kWave, "one wave writes the coefficients");
+    if (threadIdx.x < kWave) {  // the coefficients, and their constant's part
         double acc = 0.0;
-        if (col < d) {
+        if (threadIdx.x < kMergeCols && col < d) {
             coef[col] = static_cast<float>(mv[0][0][cl]);
             coef[d + col] = static_cast<float>(1.0 / mv[1][0][cl]);
             coef[2 * d + col] = static_cast<float>(mv[0][1][cl]);
@@ -297,7 +279,7 @@ gauss_merge_kernel(int d, int64_t nchunk, const int32_t* __restrict__ counts,
             acc = log(mv[1][0][cl]) - log(mv[1][1][cl]);
         }
         acc = wave_sum_u(acc);
-        if (cl == 0) cst_part[blockIdx.x] = acc;
+        if (threadIdx.x == 0) cst_part[blockIdx.x] = acc;
     }
 }
 
