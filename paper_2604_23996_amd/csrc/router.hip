@@ -19,8 +19,8 @@
 //     the KS partials in range order, add the bias, and run the softmax and
 //     the top-k (lane j holds experts j + 16 q; DPP reductions inside the
 //     16-lane row).
-// fp32 activations: one kernel, dot products accumulated in fp64, then the
-// same per-token softmax and top-k.
+// fp32 activations: one kernel, products and sums in fp64 on the matrix cores,
+// then the same per-token softmax and top-k.
 #include "common.h"
 #include "kernels.h"
 
@@ -28,13 +28,12 @@ namespace smoes {
 
 namespace {
 
-constexpr int kRouterTokens = 16;  // tokens per fp32-path workgroup
-constexpr int kRouterWaves = 8;    // fp32 path
+constexpr int kRouterWaves = 8;    // fp32 path: each wave takes an eighth of the hidden dimension
 constexpr int kRouterThreads = kRouterWaves * 64;
 constexpr int kLogitWaves = 4;     // bf16 logits kernel: expert half x token half
 constexpr int kLogitTT = 4;        // 16-token tiles per wave: 128 tokens per workgroup
 constexpr int kLogitTokens = 2 * kLogitTT * 16;
-constexpr int kTopkWaves = 4;      // top-k kernel: one wave per token
+constexpr int kTopkWaves = 4;      // top-k kernel: four tokens per wave
 
 __host__ __device__ inline int router_epad(int E) { return static_cast<int>(ceil_div(E, 16) * 16); }
 
@@ -49,15 +48,21 @@ __host__ __device__ constexpr int router_ring(int ne) {
 }
 
 // KS ranges of the hidden dimension of `steps` 32-wide k-steps each (the last
-// may be shorter): about one workgroup per CU, each range at least 8 k-steps.
+// may be shorter): as many workgroups as the chip holds (two per CU where two
+// rings fit its LDS: up to 64 experts), each range at least 8 k-steps. At 8000
+// x 2048, 64 experts 63 x 8 workgroups route in 24.8 us, 63 x 5 (one per CU,
+// 59 CUs with two) in 25.4; with one ring per CU twice the ranges only add
+// planes of partial sums (16384 x 4096, 160 experts: layer 4756 against 4739 us).
 struct RouterPlan {
     int ks, steps;
 };
-RouterPlan router_plan(int64_t T, int d, int /*E*/) {
+RouterPlan router_plan(int64_t T, int d, int E) {
     RouterPlan p;
     const int64_t tiles = ceil_div(T, kLogitTokens);
     const int nsteps = static_cast<int>(ceil_div(d, 32));
-    int ks = static_cast<int>(ceil_div(256, tiles > 0 ? tiles : 1));
+    const int ne = router_ne(E);
+    const int64_t fill = 2 * router_ring(ne) * router_slot_bytes(ne) <= 160 * 1024 ? 512 : 256;
+    int ks = static_cast<int>(ceil_div(fill, tiles > 0 ? tiles : 1));
     const int ks_max = nsteps / 8 > 1 ? nsteps / 8 : 1;
     ks = ks < 1 ? 1 : (ks > ks_max ? ks_max : ks);
     p.steps = static_cast<int>(ceil_div(nsteps, ks));
@@ -259,88 +264,16 @@ router_logits_kernel(const uint16_t* __restrict__ x, int64_t T, int d, const uin
     }
 }
 
-// Softmax and top-k of one token by one wave: lane l holds experts l + 64 q
-// (z[q], -inf past E). Each top-k round takes the wave maximum of the
-// untaken logits and then the lowest expert index that holds it (ties to the
-// lower index).
+// Softmax and top-k of the tokens of a wave, 16 lanes per token (four tokens):
+// lane j of a row holds the logits z[q] of experts j + 16 q (-inf past E). The
+// softmax and the top-k rounds reduce inside the row with DPP moves only (no
+// cross-row reads), ties to the lower expert index. live is uniform in a row;
+// every lane takes part in the reductions.
 template <int Q>
-__device__ __forceinline__ void softmax_topk_token(const float (&z)[Q], int64_t tok, int E, int k, int renorm,
-                                                   float* __restrict__ logits, float* __restrict__ probs,
-                                                   int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
-    const int lane = lane_id();
-    float lm = -INFINITY;
-#pragma unroll
-    for (int q = 0; q < Q; ++q) lm = fmaxf(lm, z[q]);
-    const float m = wave_max_u(lm);
-    float ls = 0.0f, g[Q];
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        const int e = lane + q * kWave;
-        g[q] = e < E ? expf(z[q] - m) : 0.0f;
-        ls += g[q];
-    }
-    const float inv = 1.0f / wave_sum_u(ls);
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        const int e = lane + q * kWave;
-        if (e < E) {
-            probs[tok * E + e] = g[q] * inv;
-            if (logits != nullptr) logits[tok * E + e] = z[q];
-        }
-    }
-    unsigned taken = 0;
-    int my_i = 0;
-    float my_w = 0.0f;
-    for (int rr = 0; rr < k; ++rr) {
-        float bv = -INFINITY;
-        int bi = 0x7fffffff;
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const int e = lane + q * kWave;
-            if (e < E && !((taken >> q) & 1u) && (bi == 0x7fffffff || z[q] > bv)) {
-                bv = z[q];
-                bi = e;
-            }
-        }
-        const float gm = wave_max_u(bi == 0x7fffffff ? -INFINITY : bv);
-        const int gi = wave_min_u(bi != 0x7fffffff && bv == gm ? bi : 0x7fffffff);
-        if ((gi % kWave) == lane) taken |= 1u << (gi / kWave);
-        if (lane == rr) {
-            my_i = gi;
-            my_w = expf(gm - m) * inv;  // the chosen expert's gate value, as in probs
-        }
-    }
-    if (renorm) my_w = my_w / wave_sum_u(lane < k ? my_w : 0.0f);
-    if (lane < k) {
-        topk_idx[tok * k + lane] = my_i;
-        topk_w[tok * k + lane] = my_w;
-    }
-}
-
-// bf16 path, 16 lanes per token (four tokens per wave): lane j of a row holds
-// experts j + 16 q. z = the KS partial logits summed in range order plus the
-// bias; the softmax and the top-k rounds reduce inside the row with DPP
-// moves only (no cross-row reads), ties to the lower expert index.
-template <int Q>
-__global__ void __launch_bounds__(kTopkWaves * 64)
-router_topk_row_kernel(const float* __restrict__ part, int ks_n, int64_t T, int E, int E_pad,
-                       const float* __restrict__ bias, int k, int renorm, float* __restrict__ logits,
-                       float* __restrict__ probs, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
-    const int lane = lane_id(), l16 = lane & 15;
-    const int64_t tok = (static_cast<int64_t>(blockIdx.x) * kTopkWaves + threadIdx.x / kWave) * 4 + (lane >> 4);
-    const bool live = tok < T;  // uniform in the row; every lane takes part in the row reductions
-    float z[Q];
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        const int e = l16 + 16 * q;
-        float v = -INFINITY;
-        if (live && e < E) {
-            v = part[tok * E_pad + e];
-            for (int ks = 1; ks < ks_n; ++ks) v += part[(static_cast<int64_t>(ks) * T + tok) * E_pad + e];
-            v += bias != nullptr ? bias[e] : 0.0f;
-        }
-        z[q] = v;
-    }
+__device__ __forceinline__ void softmax_topk_rows(const float (&z)[Q], bool live, int64_t tok, int E, int k, int renorm,
+                                                  float* __restrict__ logits, float* __restrict__ probs,
+                                                  int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
+    const int l16 = lane_id() & 15;
     float lm = -INFINITY;
 #pragma unroll
     for (int q = 0; q < Q; ++q) lm = fmaxf(lm, z[q]);
@@ -392,41 +325,179 @@ router_topk_row_kernel(const float* __restrict__ part, int ks_n, int64_t T, int 
     }
 }
 
-// fp32 activations: 16 tokens per workgroup, dot products in fp64 into an
-// LDS tile [16][E_pad + 1] (odd pitch), then one wave per token runs the
-// softmax and the top-k.
+// bf16 path: z = the KS partial logits summed in range order plus the bias, the
+// loads of four ranges in flight (one range at a time the kernel waited for KS
+// dependent loads: 14 against 9 us in a layer of 4096 tokens, KS = 8).
+template <int Q>
+__global__ void __launch_bounds__(kTopkWaves * 64)
+router_topk_row_kernel(const float* __restrict__ part, int ks_n, int64_t T, int E, int E_pad,
+                       const float* __restrict__ bias, int k, int renorm, float* __restrict__ logits,
+                       float* __restrict__ probs, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
+    const int lane = lane_id(), l16 = lane & 15;
+    const int64_t tok = (static_cast<int64_t>(blockIdx.x) * kTopkWaves + threadIdx.x / kWave) * 4 + (lane >> 4);
+    const bool live = tok < T;
+    const float* row = part + (live ? tok : 0) * E_pad + l16;
+    constexpr int U = 4;
+    float z[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) z[q] = 0.0f;
+    for (int k0 = 0; k0 < ks_n; k0 += U) {
+        float p[U][Q];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float* pr = row + static_cast<int64_t>(k0 + u < ks_n ? k0 + u : k0) * T * E_pad;
+#pragma unroll
+            for (int q = 0; q < Q; ++q) p[u][q] = pr[16 * q];  // E_pad = 16 Q
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            // ranges past the last leave z as it is (a branch would pull their loads into it)
+#pragma unroll
+            for (int q = 0; q < Q; ++q) z[q] = k0 + u < ks_n ? z[q] + p[u][q] : z[q];
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int e = l16 + 16 * q;
+        z[q] = live && e < E ? z[q] + (bias != nullptr ? bias[e] : 0.0f) : -INFINITY;
+    }
+    softmax_topk_rows<Q>(z, live, tok, E, k, renorm, logits, probs, topk_idx, topk_w);
+}
+
+// fp32 activations: 16 TT tokens per workgroup. v_mfma_f64_16x16x4_f64 on the
+// exactly widened operands (experts as rows, tokens as columns); each of the
+// eight waves takes an eighth of the hidden dimension, 64 experts at a time,
+// and the waves' float64 sums are added through LDS in a fixed order, rounded
+// to the float32 logits once. Fragments go straight from memory into registers,
+// 16 bytes per lane: the four contraction steps of a slice of 16 columns use
+// columns 4 (l / 16) + 0..3 of the slice, the same in both operands. One slice
+// is loaded ahead. (One thread per (token, expert) walking both rows: 23
+// against 6 us at 512 x 256, 8 experts.) Then the row softmax and top-k.
+// 16x16x4 operands: lane l holds row (A) / column (B) l % 16 at k = l / 16;
+// result element i of lane l sits at row 4 i + l / 16, column l % 16.
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
+template <int TT>
 __global__ void __launch_bounds__(kRouterThreads)
 router_f32_kernel(const float* __restrict__ x, int64_t T, int d, const float* __restrict__ w_gate,
                   const float* __restrict__ bias, int E, int E_pad, int k, int renorm, float* __restrict__ logits,
                   float* __restrict__ probs, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
-    extern __shared__ float smem[];
-    const int zp = E_pad + 1;
-    const int wave = threadIdx.x / kWave;
-    const int64_t tok0 = static_cast<int64_t>(blockIdx.x) * kRouterTokens;
-    const int ntok = static_cast<int>(T - tok0 < kRouterTokens ? T - tok0 : kRouterTokens);
-    for (int i = threadIdx.x; i < kRouterTokens * E_pad; i += kRouterThreads) {
-        const int t = i / E_pad, e = i % E_pad;
-        float z = 0.0f;
-        if (t < ntok && e < E) {
-            const float* xr = x + (tok0 + t) * d;
-            const float* wr = w_gate + static_cast<int64_t>(e) * d;
-            double acc = 0.0;
-            for (int c = 0; c < d; ++c) acc = fma(static_cast<double>(xr[c]), static_cast<double>(wr[c]), acc);
-            z = static_cast<float>(acc);
+    constexpr int NT = 16 * TT, NE = 4;  // tokens; expert tiles per pass
+    // float64 sums of four waves, [wave][expert tile][token tile][element][lane]; then the logits [token][expert]
+    __shared__ double red[4][NE][TT][4][kWave];
+    constexpr int zp = 256 + 1;  // SMOES_E_MAX
+    __shared__ float zs[NT * zp];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = lane_id();
+    const int quad = lane >> 4, r = lane & 15;
+    const int64_t tok0 = static_cast<int64_t>(blockIdx.x) * NT;
+    const int nsl = static_cast<int>(ceil_div(d, 16));  // 16-column slices
+    const int per = static_cast<int>(ceil_div(nsl, kRouterWaves));
+    const int s0 = wave * per, s1 = s0 + per < nsl ? s0 + per : nsl;
+    const float* xr[TT];
+#pragma unroll
+    for (int i = 0; i < TT; ++i) {  // tokens past T read the last one; their logits are not used
+        const int64_t tok = tok0 + 16 * i + r;
+        xr[i] = x + (tok < T ? tok : T - 1) * d;
+    }
+    for (int e0 = 0; e0 < E_pad; e0 += 16 * NE) {
+        const float* wr[NE];
+#pragma unroll
+        for (int n = 0; n < NE; ++n) {  // experts past E read the last one
+            const int e = e0 + 16 * n + r;
+            wr[n] = w_gate + static_cast<int64_t>(e < E ? e : E - 1) * d;
         }
-        smem[t * zp + e] = z;
+        f64x4_t acc[NE][TT];
+#pragma unroll
+        for (int n = 0; n < NE; ++n)
+#pragma unroll
+            for (int i = 0; i < TT; ++i) acc[n][i] = f64x4_t{};
+        f32x4u_t xa[TT], wa[NE];
+        auto load = [&](int s) {
+            const int c = 16 * s + 4 * quad;
+            const int cc = c < d ? c : 0;  // d % 8 == 0: a lane's four columns are all in or all out
+#pragma unroll
+            for (int i = 0; i < TT; ++i) {
+                xa[i] = *reinterpret_cast<const f32x4u_t*>(xr[i] + cc);
+                if (c >= d) xa[i] = f32x4u_t{0.0f, 0.0f, 0.0f, 0.0f};
+            }
+#pragma unroll
+            for (int n = 0; n < NE; ++n) {
+                wa[n] = *reinterpret_cast<const f32x4u_t*>(wr[n] + cc);
+                if (c >= d) wa[n] = f32x4u_t{0.0f, 0.0f, 0.0f, 0.0f};
+            }
+        };
+        if (s0 < s1) load(s0);
+        for (int s = s0; s < s1; ++s) {
+            f32x4u_t xc[TT], wc[NE];
+#pragma unroll
+            for (int i = 0; i < TT; ++i) xc[i] = xa[i];
+#pragma unroll
+            for (int n = 0; n < NE; ++n) wc[n] = wa[n];
+            if (s + 1 < s1) load(s + 1);
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int n = 0; n < NE; ++n) {
+                    if (e0 + 16 * n >= E_pad) break;  // uniform
+#pragma unroll
+                    for (int i = 0; i < TT; ++i)
+                        acc[n][i] = __builtin_amdgcn_mfma_f64_16x16x4f64(static_cast<double>(wc[n][c]),
+                                                                        static_cast<double>(xc[i][c]), acc[n][i], 0, 0, 0);
+                }
+        }
+        // fixed-order tree over the waves: waves 4 w .. + 3 -> 0 .. 3, then 2, 3 -> 0, 1, then 1 -> 0
+#pragma unroll
+        for (int half = 4; half > 0; half >>= 1) {
+            if (wave >= half && wave < 2 * half) {
+#pragma unroll
+                for (int n = 0; n < NE; ++n)
+#pragma unroll
+                    for (int i = 0; i < TT; ++i)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) red[wave - half][n][i][v][lane] = acc[n][i][v];
+            }
+            __syncthreads();
+            if (wave < half) {
+#pragma unroll
+                for (int n = 0; n < NE; ++n)
+#pragma unroll
+                    for (int i = 0; i < TT; ++i)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) acc[n][i][v] += red[wave][n][i][v][lane];
+            }
+            __syncthreads();
+        }
+        if (wave == 0) {
+#pragma unroll
+            for (int n = 0; n < NE; ++n) {
+                if (e0 + 16 * n >= E_pad) break;
+#pragma unroll
+                for (int i = 0; i < TT; ++i)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        zs[(16 * i + r) * zp + e0 + 16 * n + 4 * v + quad] = static_cast<float>(acc[n][i][v]);
+            }
+        }
     }
     __syncthreads();
-    const int lane = lane_id();
-    for (int t = wave; t < ntok; t += kRouterWaves) {
-        float z[4];
+    // four tokens per wave
+    const int t = 4 * wave + quad;
+    if (4 * wave >= NT) return;  // whole waves
+    const int64_t tok = tok0 + t;
+    auto finish = [&](auto q_c) {
+        constexpr int Q = decltype(q_c)::value;
+        float z[Q];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int e = lane + q * kWave;
-            z[q] = e < E ? smem[t * zp + e] + (bias != nullptr ? bias[e] : 0.0f) : -INFINITY;
+        for (int q = 0; q < Q; ++q) {
+            const int e = r + 16 * q;
+            z[q] = e < E ? zs[t * zp + e] + (bias != nullptr ? bias[e] : 0.0f) : -INFINITY;
         }
-        softmax_topk_token<4>(z, tok0 + t, E, k, renorm, logits, probs, topk_idx, topk_w);
-    }
+        softmax_topk_rows<Q>(z, tok < T, tok, E, k, renorm, logits, probs, topk_idx, topk_w);
+    };
+    if (E <= 16) finish(std::integral_constant<int, 1>{});
+    else if (E <= 64) finish(std::integral_constant<int, 4>{});
+    else if (E <= 128) finish(std::integral_constant<int, 8>{});
+    else finish(std::integral_constant<int, 16>{});
 }
 
 // bf16 path: partial logits into part[KS][T][E_pad], then the top-k kernel.
@@ -517,10 +588,16 @@ hipError_t launch_route(const void* x, int x_dtype, int64_t T, int d, const floa
         return launch_router_bf16(static_cast<const uint16_t*>(x), T, d, wsplit, bias, E, k, renorm, part, logits,
                                   probs, topk_idx, topk_w, stream);
     }
-    const dim3 grid(static_cast<unsigned>(ceil_div(T, kRouterTokens)));
-    const size_t lds = sizeof(float) * kRouterTokens * (E_pad + 1);
-    hipLaunchKernelGGL(router_f32_kernel, grid, dim3(kRouterThreads), lds, stream, static_cast<const float*>(x), T,
-                       d, w_gate, bias, E, E_pad, k, renorm, logits, probs, topk_idx, topk_w);
+    // 32 tokens per workgroup once that still gives every CU one: the router
+    // weights then pass through L2 half as often
+    const int tt = T >= 32 * 256 ? 2 : 1;
+    const dim3 grid(static_cast<unsigned>(ceil_div(T, 16 * tt)));
+    if (tt == 1)
+        hipLaunchKernelGGL(router_f32_kernel<1>, grid, dim3(kRouterThreads), 0, stream, static_cast<const float*>(x),
+                           T, d, w_gate, bias, E, E_pad, k, renorm, logits, probs, topk_idx, topk_w);
+    else
+        hipLaunchKernelGGL(router_f32_kernel<2>, grid, dim3(kRouterThreads), 0, stream, static_cast<const float*>(x),
+                           T, d, w_gate, bias, E, E_pad, k, renorm, logits, probs, topk_idx, topk_w);
     return hipGetLastError();
 }
 
