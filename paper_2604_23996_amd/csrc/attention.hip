@@ -35,10 +35,9 @@ constexpr int AT_BQ = 128;  // query rows per workgroup (4 waves x 32)
 constexpr int AT_BK = 64;   // keys per block
 constexpr int AT_THREADS = 256;
 constexpr int AT_MP = AT_BK + 8;  // pitch of the score channels' rows: four rows x two halves on distinct banks
-constexpr int kAtBufFlags = 0x00020000;
-constexpr uint32_t kAtOob = 0x80000000u;  // a byte offset past any buffer: reads return 0
 
 typedef int at_i32x4 __attribute__((ext_vector_type(4)));
+typedef int at_i32x4_u __attribute__((ext_vector_type(4), aligned(2)));  // at any element
 typedef short at_v4i16 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) at_v4i16 at_lds_v4i16;
 
@@ -61,27 +60,32 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(at_f32x2{a, b}, at_bf16x2));
 }
 
-template <int DH>
-__device__ __forceinline__ void attn_fwd_body(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
-                                              const uint16_t* __restrict__ v, int64_t T, int H, int Hkv,
-                                              const int32_t* __restrict__ offsets, int n_batch,
-                                              const float* __restrict__ m_in, float scale_log2,
-                                              uint16_t* __restrict__ o, float* __restrict__ m_heads) {
+// DMA: K and V start on 16-byte boundaries, as the buffer-to-LDS loads want them;
+// at any other start the rows go through registers (not pipelined: correct, slower).
+template <int DH, bool DMA>
+__global__ void __launch_bounds__(AT_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
+attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+                int64_t T, int H, int Hkv, const int32_t* __restrict__ offsets, int n_batch,
+                const float* __restrict__ m_in, float scale_log2, uint16_t* __restrict__ o,
+                float* __restrict__ m_heads) {
     constexpr int CPK = DH / 8;           // 16-byte chunks per key row
     constexpr int KC = DH / 16;           // K = 16 slices of the QK^T contraction
     constexpr int DT = DH / 32;           // 32-row tiles of O^T
-    constexpr int KCH = AT_BK * CPK / AT_THREADS;  // K (and V) 16-byte chunks per thread per block
-    static_assert(KCH >= 1, "head size");
-    // Padded rows instead of swizzles, so that every fragment address is a
-    // per-lane base plus an immediate. Pitches chosen so that the fragment
-    // reads hit distinct LDS banks: K rows of DH + 8 elements (16-byte reads of
-    // 16 consecutive keys), V rows of DH + 32 elements (the transposing reads
-    // of 8 keys x 64 bytes).
-    constexpr int KP = DH + 8;   // K row pitch (elements)
-    constexpr int VP = DH + 32;  // V row pitch (elements)
-    __shared__ __attribute__((aligned(16))) uint16_t k_lds[AT_BK * KP];
-    __shared__ __attribute__((aligned(16))) uint16_t v_lds[AT_BK * VP];
-    __shared__ __attribute__((aligned(16))) float mv_lds[4 * AT_MP];
+    // K and V rows come HBM -> LDS by buffer-to-LDS loads (no registers in
+    // between) into one of two buffers while the other is read: one barrier per
+    // key block. Rows are unpadded and their 16-byte chunks swizzled, so that
+    // the fragment reads hit distinct banks: K rows by the key (16-byte reads of
+    // consecutive keys), V rows in 64-byte groups of chunks by the key's low bits
+    // (the transposing reads take 64 bytes of each of 8 keys). Against rows staged
+    // through registers into one padded buffer, two barriers per block: 178 -> 170
+    // us for 7000 tokens in five samples, 32 heads of 128 over 8 KV heads (with
+    // attn_update_kernel).
+    constexpr int RB = DH * 2;                    // row bytes
+    constexpr int KV_BYTES = AT_BK * RB;
+    constexpr int RPI = 1024 / RB;                // rows per load instruction
+    constexpr int NI = AT_BK / RPI / (AT_THREADS / kWave);  // load instructions per wave, K and V each
+    __shared__ __attribute__((aligned(1024))) uint8_t kv_lds[2][2 * KV_BYTES];
+    __shared__ __attribute__((aligned(16))) float mv_lds[2][4 * AT_MP];
 
     const int nqb = static_cast<int>(ceil_div(T, AT_BQ));
     // Heads run fastest and the query blocks from the last one down, so the
@@ -92,7 +96,7 @@ __device__ __forceinline__ void attn_fwd_body(const uint16_t* __restrict__ q, co
     const int hq = H % 8 == 0 ? (hi % 8) * (H / 8) + hi / 8 : hi;
     const int qb = nqb - 1 - static_cast<int>(blockIdx.x) / H;
     const int hk = hq / (H / Hkv);
-    const int wave = threadIdx.x / kWave, lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave), lane = lane_id();
     const int half = lane >> 5, l32 = lane & 31;
     const int Ti = static_cast<int>(T);
     const int row0 = qb * AT_BQ;
@@ -104,19 +108,21 @@ __device__ __forceinline__ void attn_fwd_body(const uint16_t* __restrict__ q, co
     const int qe = q_ok ? qi : Ti - 1;
     const int qstart = min(max(sample_start(offsets, n_batch, qe), 0), qe);
     const int wq0 = row0 + wave * 32;  // first query row of this wave
-    // per-lane base of the transposing V reads: 16-lane group g = lane / 16
-    // covers dims 16 (g & 1) .. + 15 of a 32-dim tile and keys 4 (g >> 1) .. + 3
-    // of an 8-key half-slice; lane j of the group points at key j / 4, dims 4 (j % 4) ..
-    const int vtr_base = ((lane >> 5) * 4 + ((lane & 15) >> 2)) * VP + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+    // swizzle of a K row's and a V row's chunks
+    auto k_swz = [](int key) { return DH == 128 ? key & 15 : (key >> 1) & 7; };
+    auto v_swz = [](int key) { return DH == 128 ? (key & 3) << 2 : ((key >> 1) & 1) << 2; };
+    // The transposing V reads: 16-lane group g = lane / 16 covers dims
+    // 16 (g & 1) .. + 15 of a 32-dim tile and keys 4 (g >> 1) .. + 3 of an
+    // 8-key half-slice; lane j of the group points at key j / 4, dims 4 (j % 4) ..
+    const int v_key = (lane >> 5) * 4 + ((lane & 15) >> 2);
+    const int v_chunk = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);  // of the tile's four
+    const int v_byte = v_key * RB + (lane & 1) * 8;
     // sample start of the wave's last query: the largest start of its queries
     const int wq_start_max = __builtin_amdgcn_readlane(qstart, 31);
 
-    const __amdgpu_buffer_rsrc_t rsK = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint16_t*>(k), 0, static_cast<int>(T * Hkv * DH * 2), kAtBufFlags);
-    const __amdgpu_buffer_rsrc_t rsV = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint16_t*>(v), 0, static_cast<int>(T * Hkv * DH * 2), kAtBufFlags);
-    const __amdgpu_buffer_rsrc_t rsM = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float*>(m_in), 0, static_cast<int>(T * 2 * 4), kAtBufFlags);
+    const i32x4_t rsK = buf_rsrc(k, static_cast<int>(T * Hkv * DH * 2));
+    const i32x4_t rsV = buf_rsrc(v, static_cast<int>(T * Hkv * DH * 2));
+    const i32x4_t rsM = buf_rsrc(m_in, static_cast<int>(T * 2 * 4));
 
     // the wave's Q rows as B fragments held in registers for the whole key
     // loop: slice c = dims 16c + 8*half .. + 7 of query qe
@@ -130,53 +136,36 @@ __device__ __forceinline__ void attn_fwd_body(const uint16_t* __restrict__ q, co
         }
     }
 
-    // global -> register staging of one key block
-    // byte offset of the row of `key` in K or V; keys below 0 wrap to offsets
-    // >= 2^31 and keys >= T land past the buffer: the bounds check reads zeros
-    auto key_off = [&](int key) -> uint32_t {
-        return static_cast<uint32_t>((key * Hkv + hk) * DH * 2);
-    };
-    at_i32x4 kr[KCH], vr[KCH];
-    float2 mr;
-    auto load_block = [&](int kb0_) {
-        int kb0 = kb0_;
-        asm volatile("" : "+v"(kb0));  // per-lane copy: the per-item offsets are rebuilt in the loop
+    // Key block kb0 into buffer `buf`: this wave's share of the K and V rows, and
+    // (waves 0 and 1) the keys' vision and text scores. Keys past T read zeros.
+    const uint32_t lds_kv = lds_address(kv_lds), lds_mv = lds_address(mv_lds);
+    const int ld_row = lane / CPK, ld_slot = lane % CPK;
+    auto load_block = [&](int buf, int kb0) {
+        const uint32_t dst = lds_kv + static_cast<uint32_t>(buf * 2 * KV_BYTES);
 #pragma unroll
-        for (int i = 0; i < KCH; ++i) {
-            const int id = threadIdx.x + i * AT_THREADS;
-            const int key = id / CPK, c = id % CPK;
-            kr[i] = __builtin_amdgcn_raw_buffer_load_b128(rsK, static_cast<int>(key_off(kb0 + key) + c * 16), 0, 0);
+        for (int i = 0; i < NI; ++i) {
+            const int R = (wave * NI + i) * RPI + ld_row;  // key of the block
+            // T * Hkv * RB < 2^31 and a block is far smaller: a key past T stays out of range
+            const int row = static_cast<int>((static_cast<uint32_t>(kb0 + R) * Hkv + hk) * static_cast<uint32_t>(RB));
+            const uint32_t o = static_cast<uint32_t>((wave * NI + i) * 1024);
+            if constexpr (DMA) {
+                dma16(rsK, row + ((ld_slot ^ k_swz(R)) * 16), dst + o);
+                dma16(rsV, row + ((ld_slot ^ v_swz(R)) * 16), dst + KV_BYTES + o);
+            } else {
+                uint8_t* l = kv_lds[buf] + o + lane * 16;
+                const int64_t e = (static_cast<int64_t>(kb0 + R) * Hkv + hk) * DH;  // elements
+                const bool in = kb0 + R < Ti;
+                at_i32x4 kv4{}, vv4{};
+                if (in) {
+                    kv4 = *reinterpret_cast<const at_i32x4_u*>(k + e + (ld_slot ^ k_swz(R)) * 8);
+                    vv4 = *reinterpret_cast<const at_i32x4_u*>(v + e + (ld_slot ^ v_swz(R)) * 8);
+                }
+                *reinterpret_cast<at_i32x4*>(l) = kv4;
+                *reinterpret_cast<at_i32x4*>(l + KV_BYTES) = vv4;
+            }
         }
-#pragma unroll
-        for (int i = 0; i < KCH; ++i) {
-            const int id = threadIdx.x + i * AT_THREADS;
-            const int key = id / CPK, c = id % CPK;
-            vr[i] = __builtin_amdgcn_raw_buffer_load_b128(rsV, static_cast<int>(key_off(kb0 + key) + c * 16), 0, 0);
-        }
-        if (threadIdx.x < AT_BK) {
-            const int key = kb0 + static_cast<int>(threadIdx.x);
-            const uint32_t off = (key >= 0 && key < Ti) ? static_cast<uint32_t>(key * 8) : kAtOob;
-            mr.x = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsM, static_cast<int>(off), 0, 0));
-            mr.y = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsM, static_cast<int>(off == kAtOob ? off : off + 4), 0, 0));
-        }
-    };
-    // register -> LDS: K and V rows (16-byte chunks, padded rows)
-    auto store_block = [&]() {
-        int sz = 0;  // opaque zero: keeps the store addresses from being hoisted out of the key loop
-        asm volatile("" : "+v"(sz));
-        uint16_t* kst = k_lds + sz;
-        uint16_t* vst = v_lds + sz;
-#pragma unroll
-        for (int i = 0; i < KCH; ++i) {
-            const int id = threadIdx.x + i * AT_THREADS;
-            const int key = id / CPK, c = id % CPK;
-            *reinterpret_cast<at_i32x4*>(kst + key * KP + c * 8) = kr[i];
-            *reinterpret_cast<at_i32x4*>(vst + key * VP + c * 8) = vr[i];
-        }
-        if (threadIdx.x < AT_BK) {
-            mv_lds[threadIdx.x] = mr.x;
-            mv_lds[AT_MP + threadIdx.x] = mr.y;
-        }
+        if (wave < 2)
+            dma4(rsM, (kb0 + lane) * 8 + 4 * wave, lds_mv + static_cast<uint32_t>((buf * 4 + wave) * AT_MP * 4));
     };
 
     f32x16_t oacc[DT];
@@ -185,47 +174,53 @@ __device__ __forceinline__ void attn_fwd_body(const uint16_t* __restrict__ q, co
     float m_run = -INFINITY, l_run = 0.f, a0 = 0.f, a1 = 0.f;
 
     // rows 2 and 3 of the score channels: ones (the softmax denominator) and zeros
-    if (threadIdx.x < 2 * AT_MP) mv_lds[2 * AT_MP + threadIdx.x] = threadIdx.x < AT_MP ? 1.f : 0.f;
+    if (threadIdx.x < 2 * AT_MP)
+        mv_lds[0][2 * AT_MP + threadIdx.x] = mv_lds[1][2 * AT_MP + threadIdx.x] = threadIdx.x < AT_MP ? 1.f : 0.f;
     // keys that some query of this wave may see
     const int wk_lo = __builtin_amdgcn_readlane(qstart, 0), wk_hi = wq0 + 31;
 
     const int nkb = static_cast<int>(ceil_div(kend - kstart, AT_BK));
-    load_block(kstart);
+    load_block(0, kstart);
     for (int b = 0; b < nkb; ++b) {
         const int kb0 = kstart + b * AT_BK;
-        __syncthreads();  // the previous block's LDS reads are done
-        store_block();
-        __syncthreads();
-        if (b + 1 < nkb) load_block(kb0 + AT_BK);  // next block's loads fly during this block's math
+        // this wave's loads of block b have landed; behind the barrier every wave's
+        // have, and every wave is done reading the other buffer
+        wait_vm_lgkm0<0>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");  // no LDS read moves above the barrier
+        if (b + 1 < nkb) load_block((b + 1) & 1, kb0 + AT_BK);
         if (kb0 > wk_hi || kb0 + AT_BK <= wk_lo) continue;  // uniform; the barriers are above
         // LDS addresses are rebuilt inside the loop from an opaque zero: hoisting
         // all of them out of the loop would not fit the register budget
         int lz = 0;
         asm volatile("" : "+v"(lz));
-        const uint16_t* kl = k_lds + lz;
-        const uint16_t* vl = v_lds + lz;
-        const float* ml = mv_lds + (lane & 3) * AT_MP + lz;
+        const uint8_t* kl = kv_lds[b & 1] + l32 * RB + lz;
+        const uint8_t* vl = kv_lds[b & 1] + KV_BYTES + v_byte + lz;
+        const float* ml = mv_lds[b & 1] + (lane & 3) * AT_MP + lz;
+        const int k_x = half ^ k_swz(l32), v_x = v_chunk ^ v_swz(v_key);  // 32-key tiles and 4-key steps keep the swizzle
 
-        // S^T = K Q^T for the two 32-key tiles; K fragments read one slice ahead
+        // S^T = K Q^T for the two 32-key tiles; K fragments read two slices ahead
         // (the scheduling barriers keep the compiler from hoisting every LDS
         // read of the block, which would not fit the register budget)
         f32x16_t s[2] = {f32x16_t{}, f32x16_t{}};
         auto kfrag = [&](int c, int t) {
-            const int key = t * 32 + l32;
-            return *reinterpret_cast<const bf16x8_t*>(kl + key * KP + (2 * c + half) * 8);
+            return *reinterpret_cast<const bf16x8_t*>(kl + t * 32 * RB + ((2 * c) ^ k_x) * 16);
         };
-        bf16x8_t ka[2][2];
-        ka[0][0] = kfrag(0, 0);
-        ka[0][1] = kfrag(0, 1);
+        bf16x8_t ka[3][2];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            ka[c][0] = kfrag(c, 0);
+            ka[c][1] = kfrag(c, 1);
+        }
 #pragma unroll
         for (int c = 0; c < KC; ++c) {
-            if (c + 1 < KC) {
-                ka[(c + 1) & 1][0] = kfrag(c + 1, 0);
-                ka[(c + 1) & 1][1] = kfrag(c + 1, 1);
+            if (c + 2 < KC) {
+                ka[(c + 2) % 3][0] = kfrag(c + 2, 0);
+                ka[(c + 2) % 3][1] = kfrag(c + 2, 1);
             }
 #pragma unroll
             for (int t = 0; t < 2; ++t)
-                s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[c & 1][t], __builtin_bit_cast(bf16x8_t, qf[c]), s[t], 0, 0, 0);
+                s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[c % 3][t], __builtin_bit_cast(bf16x8_t, qf[c]), s[t], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
         // The block maximum of this query's logits; keys outside the query's
@@ -274,13 +269,29 @@ __device__ __forceinline__ void attn_fwd_body(const uint16_t* __restrict__ q, co
         // query's sum of channel c. (Three FMAs per probability on the vector
         // ALUs, which bound the block, became one 8-cycle matrix instruction.)
         f32x4_t sc[2] = {f32x4_t{}, f32x4_t{}};
+        // four consecutive keys of this lane, one group ahead
+        auto chan = [&](int i) { return *reinterpret_cast<const f32x4_t*>(ml + 8 * i + 4 * half); };
+        // V fragments of 16-key slice c: keys 16c + 4 half + 0..3 and 16c + 8 + 4 half + 0..3 of dim 32i + lane % 32
+        auto vfrag = [&](int c, at_i32x4 (&va)[DT]) {
+#pragma unroll
+            for (int i = 0; i < DT; ++i) {
+                const uint8_t* va_i = vl + ((4 * i) ^ v_x) * 16;
+                const at_v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((at_lds_v4i16*)(va_i + 16 * c * RB));
+                const at_v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((at_lds_v4i16*)(va_i + (16 * c + 8) * RB));
+                const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
+                va[i] = at_i32x4{static_cast<int>(l2.x), static_cast<int>(l2.y), static_cast<int>(h2.x), static_cast<int>(h2.y)};
+            }
+        };
+        at_i32x4 va[2][DT];
+        f32x4_t mcn = chan(0);
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 __builtin_amdgcn_sched_barrier(0);
-                const int kk = t * 32 + 8 * g + 4 * half;  // four consecutive keys of this lane
-                const f32x4_t mc = *reinterpret_cast<const f32x4_t*>(ml + kk);
+                const f32x4_t mc = mcn;
+                if (4 * t + g < 7) mcn = chan(4 * t + g + 1);
+                else vfrag(0, va[0]);  // the value product's first slice comes in under the last group
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const float p = __builtin_amdgcn_exp2f(fmaf(s[t][4 * g + e], scale_log2, -m_use));
@@ -294,6 +305,7 @@ __device__ __forceinline__ void attn_fwd_body(const uint16_t* __restrict__ q, co
         // O^T += V^T P^T over four 16-key slices
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
+            if (c < 3) vfrag(c + 1, va[(c + 1) & 1]);
             const f32x16_t& st = s[c >> 1];
             const int e0 = 8 * (c & 1);
             const at_i32x4 pb{static_cast<int>(pack_bf16x2(st[e0 + 0], st[e0 + 1])),
@@ -301,17 +313,9 @@ __device__ __forceinline__ void attn_fwd_body(const uint16_t* __restrict__ q, co
                               static_cast<int>(pack_bf16x2(st[e0 + 4], st[e0 + 5])),
                               static_cast<int>(pack_bf16x2(st[e0 + 6], st[e0 + 7]))};
 #pragma unroll
-            for (int i = 0; i < DT; ++i) {
-                // keys 16c + 4 half + 0..3 and 16c + 8 + 4 half + 0..3 of dim 32i + lane % 32
-                const at_v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (at_lds_v4i16*)(vl + vtr_base + (16 * c) * VP + 32 * i));
-                const at_v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (at_lds_v4i16*)(vl + vtr_base + (16 * c + 8) * VP + 32 * i));
-                const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
-                const at_i32x4 va{static_cast<int>(l2.x), static_cast<int>(l2.y), static_cast<int>(h2.x), static_cast<int>(h2.y)};
-                oacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, va),
+            for (int i = 0; i < DT; ++i)
+                oacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, va[c & 1][i]),
                                                                   __builtin_bit_cast(bf16x8_t, pb), oacc[i], 0, 0, 0);
-            }
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -336,20 +340,6 @@ __device__ __forceinline__ void attn_fwd_body(const uint16_t* __restrict__ q, co
         mh[0] = a0t / l_tot;
         mh[1] = a1t / l_tot;
     }
-}
-
-__global__ void __launch_bounds__(AT_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
-attn_fwd_kernel_d128(const uint16_t* q, const uint16_t* k, const uint16_t* v, int64_t T, int H, int Hkv,
-                     const int32_t* offsets, int n_batch, const float* m_in, float scale_log2, uint16_t* o,
-                     float* m_heads) {
-    attn_fwd_body<128>(q, k, v, T, H, Hkv, offsets, n_batch, m_in, scale_log2, o, m_heads);
-}
-
-__global__ void __launch_bounds__(AT_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
-attn_fwd_kernel_d64(const uint16_t* q, const uint16_t* k, const uint16_t* v, int64_t T, int H, int Hkv,
-                    const int32_t* offsets, int n_batch, const float* m_in, float scale_log2, uint16_t* o,
-                    float* m_heads) {
-    attn_fwd_body<64>(q, k, v, T, H, Hkv, offsets, n_batch, m_in, scale_log2, o, m_heads);
 }
 
 // Eq. 3 head average and Eq. 4 mix: one wave per token.
@@ -409,14 +399,12 @@ hipError_t launch_attention(const void* q, const void* k, const void* v, int64_t
     if (T == 0) return hipSuccess;
     const dim3 grid(static_cast<unsigned>(ceil_div(T, AT_BQ) * H));
     const float scale_log2 = scale * 1.4426950408889634f;
-    if (head_dim == 128)
-        hipLaunchKernelGGL(attn_fwd_kernel_d128, grid, dim3(AT_THREADS), 0, stream, static_cast<const uint16_t*>(q),
-                           static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v), T, H, Hkv,
-                           sample_offsets, n_batch, m_in, scale_log2, static_cast<uint16_t*>(o), m_heads);
-    else
-        hipLaunchKernelGGL(attn_fwd_kernel_d64, grid, dim3(AT_THREADS), 0, stream, static_cast<const uint16_t*>(q),
-                           static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v), T, H, Hkv,
-                           sample_offsets, n_batch, m_in, scale_log2, static_cast<uint16_t*>(o), m_heads);
+    const bool dma = (reinterpret_cast<uintptr_t>(k) | reinterpret_cast<uintptr_t>(v)) % 16 == 0;
+    const auto kernel = head_dim == 128 ? (dma ? attn_fwd_kernel<128, true> : attn_fwd_kernel<128, false>)
+                                        : (dma ? attn_fwd_kernel<64, true> : attn_fwd_kernel<64, false>);
+    hipLaunchKernelGGL(kernel, grid, dim3(AT_THREADS), 0, stream, static_cast<const uint16_t*>(q),
+                       static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v), T, H, Hkv, sample_offsets,
+                       n_batch, m_in, scale_log2, static_cast<uint16_t*>(o), m_heads);
     return hipGetLastError();
 }
 

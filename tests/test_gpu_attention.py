@@ -53,6 +53,23 @@ def test_attention_ragged_samples(dh, H, Hkv):
     _check_attention(a, o, mh)
 
 
+@pytest.mark.parametrize("dh", [128, 64])
+def test_attention_keys_at_any_element(dh):
+    # K and V that start off a 16-byte boundary take the staged loads: same bits
+    a = W.make_attention_inputs(((70, 61), (130, 3)), 64, 4, 2, dh, seed=dh)
+    say("attention unaligned keys", dh, a.T)
+    o, mh = _run_attention(a)
+
+    def shifted(x):
+        buf = torch.zeros(x.numel() + 8, dtype=x.dtype, device=x.device)
+        buf[1:1 + x.numel()] = x.flatten()
+        return buf[1:1 + x.numel()].view(x.shape)
+
+    o2, mh2 = S.attention_scores(t(a.q), shifted(t(a.k)), shifted(t(a.v)), t(a.sample_offsets), t(a.m_in))
+    torch.cuda.synchronize()
+    assert np.array_equal(o, host(o2)) and np.array_equal(mh, host(mh2))
+
+
 def test_attention_explicit_scale_and_flat_logits():
     samples = ((100, 60),)
     a = W.make_attention_inputs(samples, 64, 2, 2, 128, seed=5, logit_std=0.05)
