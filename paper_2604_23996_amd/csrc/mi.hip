@@ -16,6 +16,8 @@
 //                h_k = sum_m M_jm c[m][k], dlogit_e = s g_e (h_bin(e) - sum_k G_k h_k)
 //                with s = -grad_scale / N_batch.
 // No atomics: every result is reproducible bit for bit.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -25,6 +27,11 @@ namespace {
 
 constexpr int kMiThreads = 256;
 constexpr int kRowsPerChunk = 32;
+// One sample whose chunk partials are at most kOneSampleDoubles (32 KB): the
+// gradient kernel finalizes it in each of at most kOneSampleBlocks blocks, which
+// saves a dependent launch of ~6 us where the re-read partials cost less than 2.
+constexpr int kOneSampleDoubles = 4096;
+constexpr int kOneSampleBlocks = 256;
 
 struct MiWs {
     double* part;     // [n_batch * C][2E + 2]
@@ -137,91 +144,91 @@ mi_partial_kernel(const float* __restrict__ probs, const float* __restrict__ M, 
     }
 }
 
-// One block per sample. The chunk partials are summed by (expert, chunk
+// One block finalizes sample i. The chunk partials are summed by (expert, chunk
 // group) threads in chunk order, the groups combined in a fixed order; then
-// thread (m, k) owns one cell of the joint, and sums over cells are taken by
-// every thread in the same fixed order from LDS.
-__global__ void __launch_bounds__(kMiThreads)
-mi_finalize_kernel(int64_t T, int E, const int32_t* __restrict__ off, int n_batch, int C,
-                   const int32_t* __restrict__ e2b, int n_bins, const double* __restrict__ part,
-                   double* __restrict__ coef, double* __restrict__ mi64, int32_t* __restrict__ members,
-                   float* __restrict__ mi_per_sample) {
-    __shared__ double red[kMiThreads][2];
-    __shared__ double wred[kMiThreads][2];
-    __shared__ double A[2][256];
-    __shared__ double P[2][64];    // S-bar, then the joint P(m, k)
-    __shared__ double term[2][64];
-    __shared__ double Wm[2];
-    __shared__ int32_t mem[256];
-    __shared__ int32_t bin_s[256];
+// lane k of wave m owns cell (m, k) of the joint, and sums over cells are wave
+// reductions (loops over the cells in LDS, with a division each, took half of
+// the block's 9 us). Returns I_i (every thread); cv is the cell's gradient
+// coefficient (thread 64 m + k); mem and bin_s hold the bins'
+// member lists and the bin map for the whole block.
+struct MiFinalLds {
+    double red[kMiThreads][2];
+    double wred[kMiThreads][2];
+    double A[2][256];
+    double P[2][64];    // S-bar
+    double term[2];
+    double Wm[2];
+    int32_t mem[256];
+    int32_t bin_s[256];
+};
+__device__ __forceinline__ double mi_finalize(MiFinalLds& lds, int i, int64_t T, int E, const int32_t* __restrict__ off,
+                                              int C, const int32_t* __restrict__ e2b, int n_bins,
+                                              const double* __restrict__ part, double& cv) {
+    auto& red = lds.red;
+    auto& wred = lds.wred;
+    auto& A = lds.A;
+    auto& P = lds.P;
+    auto& term = lds.term;
+    auto& Wm = lds.Wm;
+    auto& mem = lds.mem;
+    auto& bin_s = lds.bin_s;
     const int NB = E / n_bins;
     const int tid = threadIdx.x;
-    const int i = blockIdx.x;
+    int64_t a, b;
+    sample_range(off, T, i, a, b);
+    const int my_bin = tid < E ? e2b[tid] : 0;  // E <= 256 threads
     // chunk partials: thread (cg, e) sums chunks cg, cg + RG, ... in order
     const int EP = static_cast<int>(ceil_div(E, kWave) * kWave);
     const int RG = kMiThreads / EP;
     const int cg = tid / EP, e = tid % EP;
     const double* pi = part + static_cast<int64_t>(i) * C * (2 * E + 2);
     double s0 = 0.0, s1 = 0.0, w0 = 0.0, w1 = 0.0;
-    auto add = [&](const double* pc) {
-        if (e < E) {
-            s0 += pc[e];
-            s1 += pc[E + e];
-        }
-        if (e == 0) {
-            w0 += pc[2 * E];
-            w1 += pc[2 * E + 1];
-        }
-    };
     if (cg < RG) {
-        // chunks in order; the loads of 16 chunks go out before their sums
-        constexpr int U = 16;
-        int c = cg;
-        for (; c + (U - 1) * RG < C; c += U * RG) {
-            double v[U][2];
+        // chunks in order; the loads of 8 chunks go out before their sums (chunks
+        // past the last add 0: a branch would pull their loads into it)
+        constexpr int U = 8;
+        const int er = e < E ? e : 0;
+        for (int c = cg; c < C; c += U * RG) {
+            double v[U][2], q[U][2];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const double* pc = pi + static_cast<int64_t>(c + u * RG) * (2 * E + 2);
-                v[u][0] = e < E ? pc[e] : 0.0;
-                v[u][1] = e < E ? pc[E + e] : 0.0;
+                const double* pc = pi + static_cast<int64_t>(c + u * RG < C ? c + u * RG : c) * (2 * E + 2);
+                v[u][0] = pc[er];
+                v[u][1] = pc[E + er];
             }
             if (e == 0) {
-                double q[U][2];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const double* pc = pi + static_cast<int64_t>(c + u * RG) * (2 * E + 2);
+                    const double* pc = pi + static_cast<int64_t>(c + u * RG < C ? c + u * RG : c) * (2 * E + 2);
                     q[u][0] = pc[2 * E];
                     q[u][1] = pc[2 * E + 1];
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    w0 += q[u][0];
-                    w1 += q[u][1];
+                    w0 += c + u * RG < C ? q[u][0] : 0.0;
+                    w1 += c + u * RG < C ? q[u][1] : 0.0;
                 }
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                if (e < E) {
-                    s0 += v[u][0];
-                    s1 += v[u][1];
-                }
+                s0 += c + u * RG < C ? v[u][0] : 0.0;
+                s1 += c + u * RG < C ? v[u][1] : 0.0;
             }
         }
-        for (; c < C; c += RG) add(pi + static_cast<int64_t>(c) * (2 * E + 2));
     }
     // bin member lists in ascending expert order: expert e takes slot
     // (its bin, the number of lower experts in that bin); slots no expert
     // takes stay -1 (violated precondition: a bin with fewer than N_B experts)
-    for (int q = tid; q < E; q += blockDim.x) {
-        bin_s[q] = e2b[q];
-        mem[q] = -1;
+    if (tid < E) {
+        bin_s[tid] = my_bin;
+        mem[tid] = -1;
     }
     __syncthreads();
-    for (int q = tid; q < E; q += blockDim.x) {
-        const int k = bin_s[q];
+    if (tid < E) {
         int rank = 0;
-        for (int e = 0; e < q; ++e) rank += bin_s[e] == k ? 1 : 0;
-        if (k >= 0 && k < n_bins && rank < NB) mem[k * NB + rank] = q;
+#pragma unroll 8
+        for (int o = 0; o < E; ++o) rank += o < tid && bin_s[o] == my_bin ? 1 : 0;
+        if (my_bin >= 0 && my_bin < n_bins && rank < NB) mem[my_bin * NB + rank] = tid;
     }
     red[tid][0] = s0;
     red[tid][1] = s1;
@@ -249,47 +256,62 @@ mi_finalize_kernel(int64_t T, int E, const int32_t* __restrict__ off, int n_batc
         }
     }
     __syncthreads();
-    if (i == 0)
-        for (int q = tid; q < E; q += blockDim.x) members[q] = mem[q];
-    int64_t a, b;
-    sample_range(off, T, i, a, b);
-    const bool cell = tid < 2 * n_bins;
-    const int cm = cell ? tid / n_bins : 0, ck = cell ? tid % n_bins : 0;
+    // cell (m, k): lane k of wave m (at most 64 bins); sums over a modality's cells
+    // are wave reductions, the other modality's values come through LDS
+    const int cm = tid / kWave, ck = tid % kWave;
+    const bool cell = cm < 2 && ck < n_bins;
     // Eq. 12: S-bar[m][k] = sum_{e in B_k} A[m][e] / (N_B W_m)
-    if (cell) {
-        double s = 0.0;
+    double sb = 0.0;
+    if (cell && b > a && Wm[cm] > 0.0) {
+#pragma unroll 4
         for (int n = 0; n < NB; ++n) {
             const int ee = mem[ck * NB + n];
-            if (ee >= 0) s += A[cm][ee];
+            sb += ee >= 0 ? A[cm][ee] : 0.0;
         }
-        P[cm][ck] = (b > a && Wm[cm] > 0.0) ? s / (static_cast<double>(NB) * Wm[cm]) : 0.0;
+        sb /= static_cast<double>(NB) * Wm[cm];
+    }
+    const double row = wave_sum_u(sb);
+    if (cm < 2) {
+        P[cm][ck] = sb;
+        if (ck == 0) term[cm] = row;
     }
     __syncthreads();
     // Eq. 13: normalise; marginals
-    double Z = 0.0;
-    for (int m = 0; m < 2; ++m)
-        for (int k = 0; k < n_bins; ++k) Z += P[m][k];
+    const double Z = term[0] + term[1];
     double pmk = 0.0, pm = 0.0, pk = 0.0;
     if (cell && Z > 0.0) {
-        for (int k = 0; k < n_bins; ++k) pm += P[cm][k] / Z;
-        pk = P[0][ck] / Z + P[1][ck] / Z;
-        pmk = P[cm][ck] / Z;
+        pm = row / Z;
+        pk = (P[0][ck] + P[1][ck]) / Z;
+        pmk = sb / Z;
     }
     // Eq. 14
     const double lr = (cell && pmk > 0.0) ? log(pmk / (pm * pk)) : 0.0;
-    if (cell) term[cm][ck] = pmk > 0.0 ? pmk * lr : 0.0;
+    const double part_I = wave_sum_u(pmk * lr);
+    __syncthreads();  // term is read above
+    if (cm < 2 && ck == 0) term[cm] = part_I;
     __syncthreads();
-    double I = 0.0;
-    for (int m = 0; m < 2; ++m)
-        for (int k = 0; k < n_bins; ++k) I += term[m][k];
-    if (cell) {
-        double cv = 0.0;
-        if (Wm[cm] > 0.0 && pmk > 0.0) cv = (lr - I) / (static_cast<double>(NB) * Wm[cm] * Z);
-        coef[(static_cast<int64_t>(i) * 2 + cm) * n_bins + ck] = cv;
-    }
+    const double I = term[0] + term[1];
+    cv = cell && Wm[cm] > 0.0 && pmk > 0.0 ? (lr - I) / (static_cast<double>(NB) * Wm[cm] * Z) : 0.0;
+    return I;
+}
+
+// One block per sample. With one sample its MI is the loss (Eq. 15).
+__global__ void __launch_bounds__(kMiThreads)
+mi_finalize_kernel(int64_t T, int E, const int32_t* __restrict__ off, int n_batch, int C,
+                   const int32_t* __restrict__ e2b, int n_bins, const double* __restrict__ part,
+                   double* __restrict__ coef, double* __restrict__ mi64, int32_t* __restrict__ members,
+                   float* __restrict__ mi_per_sample, float* __restrict__ loss) {
+    __shared__ MiFinalLds lds;
+    const int i = blockIdx.x, tid = threadIdx.x;
+    double cv;
+    const double I = mi_finalize(lds, i, T, E, off, C, e2b, n_bins, part, cv);
+    if (i == 0 && tid < E) members[tid] = lds.mem[tid];
+    if (tid < 2 * kWave && tid % kWave < n_bins)
+        coef[(static_cast<int64_t>(i) * 2 + tid / kWave) * n_bins + tid % kWave] = cv;
     if (tid == 0) {
         mi64[i] = I;
         mi_per_sample[i] = static_cast<float>(I);
+        if (n_batch == 1) loss[0] = static_cast<float>(-I);
     }
 }
 
@@ -304,13 +326,32 @@ __global__ void mi_loss_kernel(const double* __restrict__ mi64, int n_batch, flo
     if (threadIdx.x == 0) write_loss(mi64, n_batch, loss);
 }
 
+// ONE: a single sample of few chunk partials (mi_one_sample): every block
+// finalizes it for itself, and no mi_finalize runs before.
+template <bool ONE>
 __global__ void __launch_bounds__(kMiThreads)
 mi_grad_kernel(const float* __restrict__ probs, const float* __restrict__ M, int64_t T, int E,
-               const int32_t* __restrict__ off, int n_batch, const int32_t* __restrict__ e2b,
-               int n_bins, const int32_t* __restrict__ members, const double* __restrict__ coef,
+               const int32_t* __restrict__ off, int n_batch, const int32_t* e2b,
+               int n_bins, const int32_t* members, const double* __restrict__ coef,
                double scale, float* __restrict__ dlogits, const double* __restrict__ mi64,
-               float* __restrict__ loss) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) write_loss(mi64, n_batch, loss);
+               float* __restrict__ loss, int C, const double* __restrict__ part, float* __restrict__ mi_per_sample) {
+    __shared__ std::conditional_t<ONE, MiFinalLds, int> fin;
+    __shared__ double coef_s[128];
+    if constexpr (ONE) {
+        double cv;
+        const double I = mi_finalize(fin, 0, T, E, off, C, e2b, n_bins, part, cv);
+        if (threadIdx.x < 2 * kWave && threadIdx.x % kWave < n_bins)
+            coef_s[threadIdx.x / kWave * n_bins + threadIdx.x % kWave] = cv;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            mi_per_sample[0] = static_cast<float>(I);
+            loss[0] = static_cast<float>(-I);
+        }
+        members = fin.mem;
+        e2b = fin.bin_s;
+        __syncthreads();
+    } else {
+        if (blockIdx.x == 0 && threadIdx.x == 0) write_loss(mi64, n_batch, loss);
+    }
     constexpr int kWaves = kMiThreads / kWave;
     __shared__ float gl[kWaves][256];
     __shared__ double hl[kWaves][64];
@@ -346,7 +387,7 @@ mi_grad_kernel(const float* __restrict__ probs, const float* __restrict__ M, int
     auto load_coef = [&](int i, double& c0, double& c1) {
         c0 = c1 = 0.0;
         if (lane < n_bins) {
-            const double* cf = coef + static_cast<int64_t>(i) * 2 * n_bins;
+            const double* cf = ONE ? coef_s : coef + static_cast<int64_t>(i) * 2 * n_bins;
             c0 = cf[lane];
             c1 = cf[n_bins + lane];
         }
@@ -433,18 +474,25 @@ hipError_t launch_mi(const float* probs, const float* M, int64_t T, int E,
     hipLaunchKernelGGL(mi_partial_kernel, dim3(w.C, n_batch), dim3(kMiThreads), 0, stream, probs, M,
                        T, E, sample_offsets, w.C, w.part);
     if ((err = hipGetLastError()) != hipSuccess) return err;
+    const double scale = -static_cast<double>(grad_scale) / n_batch;
+    int64_t blocks = ceil_div(T, kMiThreads / kWave);
+    if (dlogits != nullptr && n_batch == 1 && w.C * (2 * E + 2) <= kOneSampleDoubles) {
+        if (blocks > kOneSampleBlocks) blocks = kOneSampleBlocks;
+        hipLaunchKernelGGL(mi_grad_kernel<true>, dim3(static_cast<unsigned>(blocks)), dim3(kMiThreads), 0,
+                           stream, probs, M, T, E, sample_offsets, n_batch, expert_to_bin, n_bins,
+                           w.members, w.coef, scale, dlogits, w.mi, loss, w.C, w.part, mi_per_sample);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(mi_finalize_kernel, dim3(n_batch), dim3(kMiThreads), 0, stream, T, E,
                        sample_offsets, n_batch, w.C, expert_to_bin, n_bins, w.part, w.coef, w.mi,
-                       w.members, mi_per_sample);
+                       w.members, mi_per_sample, loss);
     if ((err = hipGetLastError()) != hipSuccess) return err;
     if (dlogits != nullptr) {
-        int64_t blocks = ceil_div(T, kMiThreads / kWave);
         if (blocks > 2048) blocks = 2048;
-        const double scale = -static_cast<double>(grad_scale) / n_batch;
-        hipLaunchKernelGGL(mi_grad_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kMiThreads), 0,
+        hipLaunchKernelGGL(mi_grad_kernel<false>, dim3(static_cast<unsigned>(blocks)), dim3(kMiThreads), 0,
                            stream, probs, M, T, E, sample_offsets, n_batch, expert_to_bin, n_bins,
-                           w.members, w.coef, scale, dlogits, w.mi, loss);
-    } else {
+                           w.members, w.coef, scale, dlogits, w.mi, loss, w.C, w.part, mi_per_sample);
+    } else if (n_batch > 1) {
         hipLaunchKernelGGL(mi_loss_kernel, dim3(1), dim3(64), 0, stream, w.mi, n_batch, loss);
     }
     if ((err = hipGetLastError()) != hipSuccess) return err;
