@@ -149,17 +149,11 @@ bal_partial_kernel(const float* __restrict__ probs, const int32_t* __restrict__ 
     }
 }
 
-// Fixed-order sum of one double per thread over the block's first four waves
-// (the other threads pass 0); sh holds four doubles.
-__device__ __forceinline__ double block_sum_f64(double v, double* sh) {
-    const double w = wave_sum_u(v);
-    if (threadIdx.x < 256 && lane_id() == 0) sh[threadIdx.x / kWave] = w;
-    __syncthreads();
-    const double r = (sh[0] + sh[1]) + (sh[2] + sh[3]);
-    __syncthreads();
-    return r;
-}
-
+// After the counts are summed the three results are independent chains of
+// double divisions, so each has a thread group of its own (0: Eq. 16; 1: Eq.
+// 10-11; 2: Eq. 18-19) and three barriers serve them all (one after the other
+// with a barrier around each of four sums: 12.9 us, now 11.9, at 64 chunks x 64
+// experts).
 __global__ void __launch_bounds__(kFinThreads)
 bal_finalize_kernel(int64_t nchunk, int E, int n_bins, const int32_t* __restrict__ cnt_in,
                     const int32_t* __restrict__ tk_in, const double* __restrict__ mass_in, double beta,
@@ -169,15 +163,14 @@ bal_finalize_kernel(int64_t nchunk, int E, int n_bins, const int32_t* __restrict
     __shared__ int32_t tk_g[kFinGroups][64];
     __shared__ int32_t cnt_g[kFinGroups][2][256];
     __shared__ double mass_g[kFinGroups][256];
-    __shared__ int32_t tk[64];
+    __shared__ int32_t rank_g[kFinGroups][256];
     __shared__ double fs[256];
-    __shared__ double red[4];
+    __shared__ double red[4][4];  // wave sums of: loss term, vision load, text load, deviation
     const int e = threadIdx.x & 255, grp = threadIdx.x >> 8;  // E <= 256
-    const bool first = grp == 0;
     const int NB = E / n_bins;
     const int64_t len = ceil_div(nchunk, kFinGroups);
     const int64_t lo = grp * len, hi = lo + len < nchunk ? lo + len : nchunk;
-    constexpr int B = 8;  // chunk loads in flight; the sums still run in chunk order
+    constexpr int B = 16;  // chunk loads in flight; the sums still run in chunk order
     int32_t cv = 0, ct = 0, tb = 0;
     double S = 0.0;
     const int er = e < E ? e : 0, br = e < n_bins ? e : 0;
@@ -193,93 +186,108 @@ bal_finalize_kernel(int64_t nchunk, int E, int n_bins, const int32_t* __restrict
             vb[q] = tk_in[c * n_bins + br];
         }
 #pragma unroll
-        for (int q = 0; q < B; ++q)
-            if (c0 + q < hi) {
-                cv += vv[q];
-                ct += vt[q];
-                S += vm[q];
-                tb += vb[q];
-            }
+        for (int q = 0; q < B; ++q) {  // chunks past the last add 0: a branch would pull their loads into it
+            const int in = -static_cast<int>(c0 + q < hi);
+            cv += vv[q] & in;
+            ct += vt[q] & in;
+            tb += vb[q] & in;
+            S += in ? vm[q] : 0.0;
+        }
     }
+    // needed after the block's sums: in flight during them
+    const int my_bin = e2b[er];
+    const double ema_v = load_ema != nullptr ? load_ema[er] : 0.0, ema_t = load_ema != nullptr ? load_ema[E + er] : 0.0;
     cnt_g[grp][0][e] = cv;
     cnt_g[grp][1][e] = ct;
     mass_g[grp][e] = S;
     if (e < 64) tk_g[grp][e] = tb;
     __syncthreads();
+    const int wg = __builtin_amdgcn_readfirstlane(e / kWave);  // wave of its group
+    const bool head = lane_id() == 0;
     cv = ct = 0;
-    S = 0.0;
-    if (first && e < E) {
+    if (e < E) {
 #pragma unroll
         for (int g = 0; g < kFinGroups; ++g) {
             cv += cnt_g[g][0][e];
             ct += cnt_g[g][1][e];
-            S += mass_g[g][e];
         }
     }
-    if (first && e < n_bins) tk[e] = (tk_g[0][e] + tk_g[1][e]) + (tk_g[2][e] + tk_g[3][e]);
-    __syncthreads();
-    // Eq. 16 and its gradient coefficients
-    double term = 0.0;
-    if (first && e < E) {
-        const int32_t Tk = tk[e2b[e]];
-        const double n_e = static_cast<double>(cv) + static_cast<double>(ct);
-        double c = 0.0;
-        if (Tk > 0) {
-            const double t = static_cast<double>(Tk);
-            term = NB * (n_e / t) * (S / t);
-            c = NB * (n_e / t) / t;
-        }
-        coef[e] = c;
-        if (counts != nullptr) {
-            counts[e] = cv;
-            counts[E + e] = ct;
-        }
-    }
-    const double L = block_sum_f64(term, red);
-    if (threadIdx.x == 0 && bal_loss != nullptr) bal_loss[0] = static_cast<float>(L);
-    // Eq. 10: EMA of the expert loads (rows: vision, text), products rounded before the sum
-    double f = 0.5;
-    if (first && e < E) {
-        double lv = cv, lt = ct;
-        if (load_ema != nullptr) {
-            const double a = 1.0 - beta;
-            lv = __dadd_rn(__dmul_rn(beta, load_ema[e]), __dmul_rn(a, static_cast<double>(cv)));
-            lt = __dadd_rn(__dmul_rn(beta, load_ema[E + e]), __dmul_rn(a, static_cast<double>(ct)));
-            load_ema[e] = lv;
-            load_ema[E + e] = lt;
-        }
-        const double tot = __dadd_rn(lt, lv);
-        if (tot > 0.0) f = __ddiv_rn(lt, tot);  // Eq. 11
-        fs[e] = f;
-        if (fspec_out != nullptr) fspec_out[e] = f;
-    }
-    __syncthreads();
-    // stable ascending rank -> consecutive bins of N_B; each group ranks a quarter of the pairs
-    if (e2b_next != nullptr) {
-        int rank = 0;
+    if (grp == 0) {
+        // Eq. 16 and its gradient coefficients
+        double term = 0.0;
         if (e < E) {
-            const double fe = fs[e];
-            const int q0 = grp * 64, q1 = q0 + 64 < E ? q0 + 64 : E;
-            for (int q = q0; q < q1; ++q) rank += (fs[q] < fe || (fs[q] == fe && q < e)) ? 1 : 0;
+            S = 0.0;
+#pragma unroll
+            for (int g = 0; g < kFinGroups; ++g) S += mass_g[g][e];
+            const int32_t Tk = (tk_g[0][my_bin] + tk_g[1][my_bin]) + (tk_g[2][my_bin] + tk_g[3][my_bin]);
+            const double n_e = static_cast<double>(cv) + static_cast<double>(ct);
+            double c = 0.0;
+            if (Tk > 0) {
+                const double t = static_cast<double>(Tk);
+                term = NB * (n_e / t) * (S / t);
+                c = NB * (n_e / t) / t;
+            }
+            coef[e] = c;
+            if (counts != nullptr) {
+                counts[e] = cv;
+                counts[E + e] = ct;
+            }
         }
-        cnt_g[grp][0][e] = rank;
-        __syncthreads();
-        if (first && e < E)
-            e2b_next[e] = ((cnt_g[0][0][e] + cnt_g[1][0][e]) + (cnt_g[2][0][e] + cnt_g[3][0][e])) / NB;
+        const double w = wave_sum_u(term);
+        if (head) red[0][wg] = w;
+    } else if (grp == 1) {
+        // Eq. 10: EMA of the expert loads (rows: vision, text), products rounded before the sum
+        if (e < E) {
+            double lv = cv, lt = ct, f = 0.5;
+            if (load_ema != nullptr) {
+                const double a = 1.0 - beta;
+                lv = __dadd_rn(__dmul_rn(beta, ema_v), __dmul_rn(a, static_cast<double>(cv)));
+                lt = __dadd_rn(__dmul_rn(beta, ema_t), __dmul_rn(a, static_cast<double>(ct)));
+                load_ema[e] = lv;
+                load_ema[E + e] = lt;
+            }
+            const double tot = __dadd_rn(lt, lv);
+            if (tot > 0.0) f = __ddiv_rn(lt, tot);  // Eq. 11
+            fs[e] = f;
+            if (fspec_out != nullptr) fspec_out[e] = f;
+        }
+    } else if (grp == 2) {
+        // Eq. 18's totals (integers: exact in any order)
+        const double wv = wave_sum_u(static_cast<double>(cv)), wt = wave_sum_u(static_cast<double>(ct));
+        if (head) {
+            red[1][wg] = wv;
+            red[2][wg] = wt;
+        }
     }
-    // Eq. 18-19 on this batch's counts (integers: exact in any order)
-    const double tot_v = block_sum_f64(static_cast<double>(cv), red);
-    const double tot_t = block_sum_f64(static_cast<double>(ct), red);
-    double dev = 0.0;
-    if (first && e < E) {
-        const double nv = tot_v > 0.0 ? cv / tot_v : 0.0;
-        const double nt = tot_t > 0.0 ? ct / tot_t : 0.0;
-        const double den = nt + nv;
-        const double c_text = den > 0.0 ? nt / den : 0.5;
-        dev = 2.0 * fabs(c_text - 0.5);
+    __syncthreads();
+    auto total = [&](int i) { return (red[i][0] + red[i][1]) + (red[i][2] + red[i][3]); };
+    if (threadIdx.x == 0 && bal_loss != nullptr) bal_loss[0] = static_cast<float>(total(0));
+    // stable ascending rank -> consecutive bins of N_B; each group ranks a quarter of the pairs
+    if (e2b_next != nullptr && e < E) {
+        int rank = 0;
+        const double fe = fs[e];
+        const int q0 = grp * 64, q1 = q0 + 64 < E ? q0 + 64 : E;
+        for (int q = q0; q < q1; ++q) rank += (fs[q] < fe || (fs[q] == fe && q < e)) ? 1 : 0;
+        rank_g[grp][e] = rank;
     }
-    const double msi = block_sum_f64(dev, red) / E;
-    if (threadIdx.x == 0 && msi_out != nullptr) msi_out[0] = static_cast<float>(msi);
+    if (grp == 2) {
+        // Eq. 18-19 on this batch's counts
+        const double tot_v = total(1), tot_t = total(2);
+        double dev = 0.0;
+        if (e < E) {
+            const double nv = tot_v > 0.0 ? cv / tot_v : 0.0;
+            const double nt = tot_t > 0.0 ? ct / tot_t : 0.0;
+            const double den = nt + nv;
+            const double c_text = den > 0.0 ? nt / den : 0.5;
+            dev = 2.0 * fabs(c_text - 0.5);
+        }
+        const double w = wave_sum_u(dev);
+        if (head) red[3][wg] = w;
+    }
+    __syncthreads();
+    if (grp == 0 && e < E && e2b_next != nullptr)
+        e2b_next[e] = ((rank_g[0][e] + rank_g[1][e]) + (rank_g[2][e] + rank_g[3][e])) / NB;
+    if (threadIdx.x == 0 && msi_out != nullptr) msi_out[0] = static_cast<float>(total(3) / E);
 }
 
 __global__ void __launch_bounds__(kBalThreads)
