@@ -596,9 +596,9 @@ size_t bwd_ws_parts(const smoes_layer* L, BwdWs* out, void* base) {
     w.dx_r = c.take(es * R * L->d);
     w.dx_s = c.take(es * T * L->d);
     w.wrow = static_cast<float*>(c.take(sizeof(float) * R));
-    w.wh_r = c.take(es * R * L->inter);
+    w.wh_r = c.take(gen ? es * R * L->inter : 0);  // the packed path writes w H k-packed only
     w.wh_s = c.take(gen ? es * T * L->shared_inter : 0);
-    w.work4 = static_cast<int32_t*>(c.take(sizeof(int32_t) * (L->E + 2)));
+    w.work4 = static_cast<int32_t*>(c.take(sizeof(int32_t) * (gen ? 3 : 1) * (L->E + 2)));
     w.router = c.take(router_bwd_workspace_bytes(T, L->d, L->E, L->act_dtype == SMOES_BF16 ? 1 : 0));
     const int64_t kr = gen ? 0 : kpad_routed(L), ksh = gen || L->shared_inter == 0 ? 0 : kpad_shared(L);
     w.kp = static_cast<int32_t*>(c.take(gen ? 0 : sizeof(int32_t) * (L->E + 1)));
@@ -736,7 +736,10 @@ int smoes_moe_backward(const smoes_layer* L, const smoes_layer_io* io, const voi
     bp.dx_r = bw.dx_r;
     bp.dx_s = bw.dx_s;
     bp.wrow = bw.wrow;
-    bp.wh_r = bw.wh_r;
+    bp.pt_dab_r = bw.pt_dab_r;
+    bp.pt_wh_r = bw.pt_wh_r;
+    bp.pt_dab_s = bw.pt_dab_s;
+    bp.kp = bw.kp;
     bp.work4 = bw.work4;
     // Caller's stream s: combine weights, the routed experts' dgrad GEMMs
     // (pre-activation recompute unless kept, dH with the SwiGLU backward,
@@ -771,24 +774,21 @@ int smoes_moe_backward(const smoes_layer* L, const smoes_layer_io* io, const voi
         SMOES_BTRY(launch_kpack(dout, d, nullptr, nullptr, nullptr, 1, T, ksh, bw.pt_rows_s, c));
         SMOES_BTRY(launch_kpack(fb.h_s, SI, nullptr, nullptr, nullptr, 1, T, ksh, bw.pt_h_s, c));
         SMOES_BTRY(launch_wgrad_pk(1, d, SI, nullptr, nullptr, T, bw.pt_rows_s, bw.pt_h_s, G->dws2, c));
-        SMOES_BTRY(launch_kpack(bw.dab_s, 2 * SI, nullptr, nullptr, nullptr, 1, T, ksh, bw.pt_dab_s, c));
         SMOES_BTRY(launch_kpack(io->x, d, nullptr, nullptr, nullptr, 1, T, ksh, bw.pt_rows_s, c));
         SMOES_BTRY(launch_wgrad_pk(1, 2 * SI, d, nullptr, nullptr, T, bw.pt_dab_s, bw.pt_rows_s, G->dws13, c));
     }
     if (sides != nullptr) SMOES_BTRY(hipEventRecord(e_join, c));
     // routed chain
     SMOES_BTRY(launch_row_weights(perm_inv, io->topk_w, T, L->k, bw.wrow, s));
+    SMOES_BTRY(launch_kpad_offsets(offsets, L->E, bw.kp, wgrad_tiles_per_group(d, I), wgrad_tiles_per_group(2 * I, d),
+                                   bw.ranges, s));
     for (int mode = L->save_preact ? 4 : 3; mode <= 5; ++mode)
         SMOES_BTRY(launch_bwd_gemm(mode, a, fw.experts, bp, 1, s));
     // dW2 = dout^T (w H) over each expert's rows (dout gathered); dW13 = [dA dB]^T X (x
-    // gathered): both operands k-packed per expert first (rows padded to 16)
+    // gathered): both operands k-packed per expert first (rows padded to 16; [dA dB] and w H by mode 4)
     const int64_t kr = kpad_routed(L);
-    SMOES_BTRY(launch_kpad_offsets(offsets, L->E, bw.kp, wgrad_tiles_per_group(d, I), wgrad_tiles_per_group(2 * I, d),
-                                   bw.ranges, s));
     SMOES_BTRY(launch_kpack(dout, d, perm_token, offsets, bw.kp, L->E, T, kr, bw.pt_rows_r, s));
-    SMOES_BTRY(launch_kpack(bw.wh_r, I, nullptr, offsets, bw.kp, L->E, T, kr, bw.pt_wh_r, s));
     SMOES_BTRY(launch_wgrad_pk(L->E, d, I, bw.kp, bw.ranges, T, bw.pt_rows_r, bw.pt_wh_r, G->dw2, s));
-    SMOES_BTRY(launch_kpack(bw.dab_r, 2 * I, nullptr, offsets, bw.kp, L->E, T, kr, bw.pt_dab_r, s));
     SMOES_BTRY(launch_kpack(io->x, d, perm_token, offsets, bw.kp, L->E, T, kr, bw.pt_rows_r, s));
     SMOES_BTRY(launch_wgrad_pk(L->E, 2 * I, d, bw.kp, bw.ranges + 9, T, bw.pt_dab_r, bw.pt_rows_r, G->dw13, s));
     if (sides != nullptr) SMOES_BTRY(hipStreamWaitEvent(s, e_join, 0));

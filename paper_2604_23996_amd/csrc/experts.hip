@@ -150,6 +150,9 @@ __device__ __forceinline__ bool decode_tile(const int32_t* __restrict__ work, co
     return true;
 }
 
+typedef short v4i16_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) v4i16_t lds_v4i16_t;
+
 __device__ __forceinline__ float silu(float a) { return a / (1.0f + expf(-a)); }
 
 __device__ __forceinline__ uint4 as_uint4(i32x4_t v) {
@@ -187,7 +190,12 @@ struct GemmArgs {
     void* dx_r;         // [R][d] input gradient of each routed row
     void* dx_s;         // [T][d] shared experts' input gradient
     const float* wrow;  // [R] combine weight of each routed row
-    void* wh_r;         // [R][inter] w H of each routed row (mode 4 output)
+    // mode 4 outputs for the weight gradients, k-packed (wgrad.hip): the routed
+    // rows' [dA dB] and w H (kp: padded row prefix of the experts), the shared [dA dB]
+    uint16_t* pt_dab_r;
+    uint16_t* pt_wh_r;
+    uint16_t* pt_dab_s;
+    const int32_t* kp;
     // shared down GEMM with the combine in its epilogue (mode 7)
     const int32_t* inv;    // [T][k] routed row of each (token, slot)
     const float* topk_w;   // [T][k] combine weights
@@ -732,10 +740,19 @@ gemm_bf16_pk_kernel(GemmArgs p) {
         // plus w H = w silu(a) b for the dW2 product (routed rows). In four
         // passes of 32 rows: the rows' a | b slices come into LDS as whole
         // rows, each lane turns its four adjacent columns into dA | dB | w H
-        // in place, and the three slices go out as whole rows.
+        // in place; dA and dB go out as whole rows (the dX GEMM's operand), and
+        // all three (w H for routed rows only) k-packed for the weight
+        // gradients: 16 rows x 32 columns per 1 KB, a lane's eight rows of one
+        // column by two transposing LDS reads. (As passes of their own the
+        // three k-packs read the rows back: at 16384 tokens, d 2048, 64 experts
+        // top-6 of 1408 and two shared ones 118 + 198 + 57 us.)
         const uint16_t* AB = static_cast<const uint16_t*>(shared ? p.ab_s : p.ab_r);
         uint16_t* dAB = static_cast<uint16_t*>(shared ? p.dab_s : p.dab_r);
-        uint16_t* WH = shared ? nullptr : static_cast<uint16_t*>(p.wh_r);
+        const int64_t kp0 = shared ? 0 : p.kp[t.g];
+        const int64_t Ks = shared ? ceil_div(p.T, 16) : (p.kp[t.g + 1] - kp0) / 16;
+        const int64_t ks0 = (t.row0 - (shared ? 0 : p.off[t.g])) / 16;  // the tile's first 16-row slice of its group
+        uint16_t* PD = (shared ? p.pt_dab_s : p.pt_dab_r) + kp0 * (2 * n_out);  // 2 n_out is a multiple of 32
+        uint16_t* PH = shared ? nullptr : p.pt_wh_r + kp0 * (32 * ceil_div(n_out, 32));
         const int64_t ld = 2 * static_cast<int64_t>(n_out);
         constexpr int EP = 3 * TC + 8;  // LDS row: a | b | w H (pitch = 4 mod 64 dwords)
         uint16_t* el = reinterpret_cast<uint16_t*>(lds);
@@ -802,14 +819,40 @@ gemm_bf16_pk_kernel(GemmArgs p) {
                 }
             }
             __syncthreads();
-            const int nparts = WH != nullptr ? 3 : 2;
-            for (int q = threadIdx.x; q < 32 * (3 * TC / 8); q += PK_THREADS) {
-                const int r = q / (3 * TC / 8), ch = q % (3 * TC / 8);
+            for (int q = threadIdx.x; q < 32 * (2 * TC / 8); q += PK_THREADS) {
+                const int r = q / (2 * TC / 8), ch = q % (2 * TC / 8);
                 const int part = ch / (TC / 8), c = (ch % (TC / 8)) * 8;
-                if (r < rows_here && c < ncols && part < nparts) {
-                    const uint4 v = *reinterpret_cast<const uint4*>(el + r * EP + part * TC + c);
-                    if (part < 2) *reinterpret_cast<uint4*>(dAB + (rbase + r) * ld + part * n_out + col0 + c) = v;
-                    else *reinterpret_cast<uint4*>(WH + (rbase + r) * n_out + col0 + c) = v;
+                if (r < rows_here && c < ncols)
+                    *reinterpret_cast<uint4*>(dAB + (rbase + r) * ld + part * n_out + col0 + c) =
+                        *reinterpret_cast<const uint4*>(el + r * EP + part * TC + c);
+            }
+            // k-packed: lane l takes column 32 f + l % 32 of the wave's 64 and rows 8 (l / 32) .. + 7
+            // of slice tt; in each 16-lane group lane j supplies the address of row j / 4, columns
+            // 4 (j % 4) .. and receives column j of four rows. Rows past the group are zero here
+            // (zero accumulators, a, b and w), as the padding has to be.
+            const int tr0 = (8 * (lane >> 5) + ((lane & 15) >> 2)) * EP + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+#pragma unroll
+            for (int tt = 0; tt < 2; ++tt) {
+                if (16 * tt >= rows_here) break;  // uniform
+#pragma unroll
+                for (int part = 0; part < 3; ++part) {
+                    if (part == 2 && shared) break;
+#pragma unroll
+                    for (int f = 0; f < 2; ++f) {
+                        const int c = wave * 64 + 32 * f;
+                        const uint16_t* src = el + tr0 + 16 * tt * EP + part * TC + c;
+                        const v4i16_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_t*)src);
+                        const v4i16_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_t*)(src + 4 * EP));
+                        const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
+                        const int cl = c + (lane & 31);
+                        if (cl < ncols) {
+                            const int cc = (part == 1 ? n_out : 0) + col0 + cl;  // column of [dA dB] or of w H
+                            uint16_t* P = part < 2 ? PD : PH;
+                            *reinterpret_cast<uint4*>(P + ((cc >> 5) * Ks + ks0 + 2 * i + tt) * 512 +
+                                                      ((lane >> 5) * 32 + (cc & 31)) * 8) =
+                                make_uint4(l2.x, l2.y, h2.x, h2.y);
+                        }
+                    }
                 }
             }
             __syncthreads();
@@ -1519,7 +1562,8 @@ GemmArgs make_args(const ExpertArgs& a, const ExpWs& w, const int32_t* work, int
     g.ab_s = a.ab_s;
     g.dab_r = g.dab_s = g.dx_r = g.dx_s = nullptr;
     g.wrow = nullptr;
-    g.wh_r = nullptr;
+    g.pt_dab_r = g.pt_dab_s = g.pt_wh_r = nullptr;
+    g.kp = nullptr;
     g.inv = a.perm_inv;
     g.topk_w = a.topk_w;
     g.out = a.out;
@@ -1721,7 +1765,10 @@ hipError_t launch_bwd_gemm(int mode, const ExpertArgs& a, void* fwd_ws, const Bw
     g.dx_r = bp.dx_r;
     g.dx_s = bp.dx_s;
     g.wrow = bp.wrow;
-    g.wh_r = bp.wh_r;
+    g.pt_dab_r = static_cast<uint16_t*>(bp.pt_dab_r);
+    g.pt_dab_s = static_cast<uint16_t*>(bp.pt_dab_s);
+    g.pt_wh_r = static_cast<uint16_t*>(bp.pt_wh_r);
+    g.kp = bp.kp;
     const dim3 grid(static_cast<unsigned>(work_bound(a.T, a.k, a.E, PK_BM, nt_r, nt_s, has_shared, part)));
     if (grid.x == 0) return hipSuccess;
     if (mode == 3) hipLaunchKernelGGL(gemm_bf16_pk_kernel<3>, grid, dim3(PK_THREADS), 0, stream, g);

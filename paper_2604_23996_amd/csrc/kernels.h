@@ -119,11 +119,14 @@ struct BwdGemmPtrs {
     void* dx_r;         // [R][d]
     void* dx_s;         // [T][d]
     const float* wrow;  // [R]
-    void* wh_r;         // [R][inter] w H of the routed rows (written by mode 4)
+    void* pt_dab_r;     // k-packed (launch_kpack's layout), written by mode 4: [dA dB] and w H of the
+    void* pt_wh_r;      //   routed rows, [dA dB] of the shared experts
+    void* pt_dab_s;
+    const int32_t* kp;  // [E + 1] padded row prefix (launch_kpad_offsets), read by the routed mode 4
     int32_t* work4;     // [E + 2] table of mode 4
 };
 // mode 3: recomputed gate/up pre-activations; 4: dH = w dout W2 with the SwiGLU
-// backward -> [dA dB] (and w H for routed rows); 5: dX = [dA dB] W13. part: 1
+// backward -> [dA dB] (as rows and k-packed, with w H for routed rows); 5: dX = [dA dB] W13. part: 1
 // routed, 2 shared.
 hipError_t launch_bwd_gemm(int mode, const ExpertArgs& a, void* fwd_ws, const BwdGemmPtrs& bp, int part,
                            hipStream_t stream);
