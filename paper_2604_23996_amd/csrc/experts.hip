@@ -95,6 +95,7 @@ __device__ __forceinline__ bool decode_tile(const int32_t* __restrict__ work, co
     const int xcd = blockIdx.x & 7;
     const int slot = blockIdx.x >> 3;
     int g, local;
+    int64_t base, rows_g;
     if (part == 2) {
         const int ns = static_cast<int>(ceil_div(T, bm)) * nt_shared;
         const int s8 = (ns + 7) / 8;
@@ -116,21 +117,45 @@ __device__ __forceinline__ bool decode_tile(const int32_t* __restrict__ work, co
         else return false;
         if (w >= routed) {
             g = E;
+            local = w - routed;
         } else {
-            int lo = 0, hi = E - 1;  // last g with work[g] <= w
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (work[mid] <= w) lo = mid; else hi = mid - 1;
+            // the last g with work[g] <= w: lane l holds entries l, l + 64, ... of the
+            // table and the offsets, all loaded at once (a binary search waits for
+            // log2(E) dependent loads before the tile's first operand load)
+            const int lane = lane_id();
+            int wv[4], ov[4], on[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (64 * q >= E) break;  // uniform
+                const int e = lane + 64 * q < E ? lane + 64 * q : E - 1;
+                wv[q] = work[e];
+                ov[q] = off[e];
+                on[q] = off[e + 1];
             }
-            g = lo;
+            int n = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (64 * q >= E) break;
+                n += __popcll(__ballot(lane + 64 * q < E && wv[q] <= w));
+            }
+            g = n - 1;  // work[0] = 0
+            int wg = 0, o0 = 0, o1 = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (64 * q >= E) break;
+                if ((g >> 6) == q) {
+                    wg = __builtin_amdgcn_readlane(wv[q], g & 63);
+                    o0 = __builtin_amdgcn_readlane(ov[q], g & 63);
+                    o1 = __builtin_amdgcn_readlane(on[q], g & 63);
+                }
+            }
+            local = w - wg;
+            base = o0;
+            rows_g = o1 - o0;
         }
-        local = w - work[g];
     }
-    int64_t base, rows_g;
     int ntn;
     if (g < E) {
-        base = off[g];
-        rows_g = off[g + 1] - off[g];
         ntn = nt_routed;
     } else {
         base = 0;
