@@ -718,6 +718,7 @@ int smoes_moe_backward(const smoes_layer* L, const smoes_layer_io* io, const voi
                                      T, L->d, L->E, L->k, L->renorm_topk ? 1 : 0, G->dw, G->dz, s));
         SMOES_BTRY(launch_dwgate(G->dz, io->x, bf16, T, L->d, L->E, G->dw_gate, G->dbias, bw.router, s));
         SMOES_BTRY(launch_row_weights(perm_inv, io->topk_w, T, L->k, bw.wrow, s));
+        SMOES_BTRY(launch_generic_bwd_tables(a, bw.work4, s));
         for (int step = 0; step < 5; ++step) SMOES_BTRY(launch_generic_bwd(step, a, gp, s));
         SMOES_BTRY(launch_dx_gather(bw.dx_r, sh ? bw.dx_s : nullptr, 0, perm_inv, G->dz, io->w_gate, T, L->d, L->E,
                                     L->k, G->dx, nullptr, s));

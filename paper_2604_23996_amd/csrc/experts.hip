@@ -1100,16 +1100,18 @@ __global__ void pack_weights_kernel(const uint16_t* __restrict__ src, int batch,
 // 16-byte chunks per index (64 bf16 or 32 float32): each thread loads its
 // chunks of both operands into registers one step ahead, turns an operand
 // whose memory runs along the index into chunks along K, and writes them to
-// the other of two LDS buffers while the current one is multiplied: one
-// barrier per step. In a float32 layer the matrix cores bound a tile (64
+// LDS: in a float32 layer to the other of two buffers, one barrier per step; in
+// a bf16 layer to the only one, two barriers, because its tiles are short (an
+// expert's 250 rows are four steps of the weight gradients) and four blocks per
+// CU hide their start and end where two cannot. In a float32 layer the matrix cores bound a tile (64
 // cycles per 4096 flops), and 64 x 64 gives small layers enough tiles; in a
 // bf16 layer the LDS reads do (four fragments per three products at 64 x 64,
 // five per six at 64 x 128, hence NH = 2).
 // Against float32 vector-ALU tiles (64 x 64, K steps of 16): at 1000 tokens x
 // 1024, 16 experts of 512, top-4, one shared, row-major bf16, GB_AB / DH / DX /
-// DW2 / DW13 343 / 177 / 264 / 151 / 228 -> 28 / 35 / 59 / 57 / 90 us; the
+// DW2 / DW13 343 / 177 / 264 / 151 / 228 -> 26 / 34 / 50 / 53 / 77 us; the
 // forward of the 512 x 256 float32 layer with 8 experts of 512, top-2, 44 + 58
-// -> 17 + 16 us.
+// -> 17 + 15 us.
 enum { GB_AB = 0, GB_DH = 1, GB_DX = 2, GB_DW2 = 3, GB_DW13 = 4, RM_FW1 = 5, RM_FW2 = 6 };
 
 struct RmArgs {
@@ -1261,7 +1263,7 @@ struct RmOperand {
 };
 
 template <int MODE, bool BF16>
-__global__ void __launch_bounds__(kThreads, 2)
+__global__ void __launch_bounds__(kThreads, BF16 ? 4 : 2)
 gemm_rm_kernel(RmArgs p) {
     constexpr bool kRows = MODE != GB_DW2 && MODE != GB_DW13;
     constexpr bool kFwd = MODE == RM_FW1 || MODE == RM_FW2;
@@ -1274,7 +1276,8 @@ gemm_rm_kernel(RmArgs p) {
     using OpH = RmOperand<BF16, kHkc, 2 * NH, CK, 0>;
     constexpr int F_BYTES = 64 * 128, H_BYTES = BH * 128;
     constexpr int BUF = OpF::PLANES * F_BYTES + H_BYTES;
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[2][BUF];
+    constexpr int NB = BF16 ? 1 : 2;  // LDS buffers
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[NB][BUF];
 
     const int tid = threadIdx.x;
     int g, f0, h0, NF, N, K;
@@ -1370,9 +1373,7 @@ gemm_rm_kernel(RmArgs p) {
             }
         }
     };
-    OpF opf;
-    OpH oph;
-    auto load = [&](int s) {
+    auto load = [&](OpF& opf, OpH& oph, int s) {
         const int kf = s * KS + OpF::lds_chunk() * CK, kh = s * KS + OpH::lds_chunk() * CK;
         if constexpr (kRows) {
 #pragma unroll
@@ -1392,12 +1393,12 @@ gemm_rm_kernel(RmArgs p) {
             }
         }
     };
-    auto store = [&](int s) {
+    auto store = [&](OpF& opf, OpH& oph, int s) {
         if ((s + 1) * KS > K) {
             opf.cut(s * KS + OpF::lds_chunk() * CK, K);
             oph.cut(s * KS + OpH::lds_chunk() * CK, K);
         }
-        uint8_t* b = lds[s & 1];
+        uint8_t* b = lds[s % NB];
         opf.put(b, F_BYTES);
         oph.put(b + OpF::PLANES * F_BYTES, H_BYTES);
     };
@@ -1409,7 +1410,7 @@ gemm_rm_kernel(RmArgs p) {
 #pragma unroll
     for (int j = 0; j < NH; ++j) acc[j] = f32x16_t{};
     auto compute = [&](int s) {
-        const uint8_t* b = lds[s & 1];
+        const uint8_t* b = lds[s % NB];
         auto frag = [&](const uint8_t* base, int R, int c) {
             return *reinterpret_cast<const uint4*>(base + R * 128 + ((c ^ (((R >> 1) ^ (R >> 4)) & 7)) * 16));
         };
@@ -1440,22 +1441,54 @@ gemm_rm_kernel(RmArgs p) {
         }
     };
     if (nk > 0) {
+        // PD steps of operands are in registers or in flight: a float32 step is
+        // 1024 cycles of matrix work, less than the latency of its loads, so there
+        // the loads run two steps ahead of the step that is written to LDS (17.3 ->
+        // 16.5 and 15.7 -> 15.0 us for the forward above); in a bf16 layer the
+        // registers for that cost the fourth block per CU (GB_DW2 / DW13 53 / 77
+        // -> 58 / 85 us)
+        constexpr int PD = BF16 ? 1 : 2;
+        OpF opf[PD];
+        OpH oph[PD];
         load_tok(0);
-        load(0);
+        load(opf[0], oph[0], 0);
         load_tok(1);
-        store(0);
-        if (nk > 1) load(1);
-        load_tok(2);
+        if constexpr (PD == 2) {
+            if (nk > 1) load(opf[1], oph[1], 1);
+            load_tok(2);
+        }
+        store(opf[0], oph[0], 0);
+        if (nk > PD) load(opf[0], oph[0], PD);
+        load_tok(PD + 1);
         __syncthreads();
-        for (int s = 0; s < nk; ++s) {
-            // the buffer written here was last read before the barrier that ended step s - 1
-            if (s + 1 < nk) store(s + 1);
-            if (s + 2 < nk) {
-                load(s + 2);
-                load_tok(s + 3);
+        // step s; r: the registers that hold step s + 1
+        auto step = [&](int s, OpF& rf, OpH& rh) {
+            if constexpr (NB == 2) {
+                // the buffer written here was last read before the barrier that ended step s - 1
+                if (s + 1 < nk) store(rf, rh, s + 1);
+                if (s + 1 + PD < nk) {
+                    load(rf, rh, s + 1 + PD);
+                    load_tok(s + 2 + PD);
+                }
+                compute(s);
+            } else {
+                compute(s);
+                if (s + 1 < nk) {
+                    __syncthreads();  // every wave is done reading step s
+                    store(rf, rh, s + 1);
+                    if (s + 1 + PD < nk) {
+                        load(rf, rh, s + 1 + PD);
+                        load_tok(s + 2 + PD);
+                    }
+                }
             }
-            compute(s);
             __syncthreads();
+        };
+        for (int s = 0; s < nk; s += PD) {
+            step(s, opf[PD - 1], oph[PD - 1]);
+            if constexpr (PD == 2) {
+                if (s + 1 < nk) step(s + 1, opf[0], oph[0]);
+            }
         }
     }
 
@@ -1463,7 +1496,7 @@ gemm_rm_kernel(RmArgs p) {
     if constexpr (MODE == RM_FW1) {
         // gate and up sit in different waves: through LDS, then whole rows of 32 columns
         float* C = reinterpret_cast<float*>(lds);
-        static_assert(64 * 65 * 4 <= 2 * BUF, "the output tile fits the operand buffers");
+        static_assert(64 * 65 * 4 <= NB * BUF, "the output tile fits the operand buffers");
 #pragma unroll
         for (int v = 0; v < 16; ++v)
             C[(32 * wf + 8 * (v >> 2) + 4 * half + (v & 3)) * 65 + 32 * wh_ + l32] = acc[0][v];
@@ -1741,6 +1774,46 @@ bwd_work_kernel(const int32_t* __restrict__ off, int E, int64_t T, int bm, int n
     if (g == 0) work[E + 1] = sc[E - 1] + (has_shared ? static_cast<int32_t>(ceil_div(T, bm)) * nt_s : 0);
 }
 
+// The three row steps' tables of the row-major backward (same tiles of FBM
+// rows, nt column tiles of the step): table i at work + i (E + 2).
+struct RmTables {
+    int nt_r[3], nt_s[3];
+};
+__global__ void __launch_bounds__(256)
+rm_work_kernel(const int32_t* __restrict__ off, int E, int64_t T, int has_shared, RmTables t, int32_t* __restrict__ work) {
+    __shared__ int32_t sc[4];
+    const int g = threadIdx.x, lane = lane_id(), wave = g / kWave;
+    int v = g < E ? static_cast<int>(ceil_div(off[g + 1] - off[g], FBM)) : 0;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {  // inclusive scan: the wave, then the waves before
+        const int u = __shfl_up(v, o);
+        if (lane >= o) v += u;
+    }
+    if (lane == kWave - 1) sc[wave] = v;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) v += sc[w];
+    const int shared = has_shared ? static_cast<int>(ceil_div(T, FBM)) : 0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        int32_t* w = work + i * (E + 2);
+        if (g == 0) w[0] = 0;
+        if (g < E) w[g + 1] = v * t.nt_r[i];
+        if (g == E - 1) w[E + 1] = v * t.nt_r[i] + shared * t.nt_s[i];
+    }
+}
+
+hipError_t launch_generic_bwd_tables(const ExpertArgs& a, int32_t* work, hipStream_t stream) {
+    RmTables t;
+    const bool bf16 = a.act_dtype == 1;
+    for (int i = 0; i < 3; ++i) {
+        t.nt_r[i] = rm_row_tiles(GB_AB + i, a.inter, a.d, bf16);
+        t.nt_s[i] = rm_row_tiles(GB_AB + i, a.shared_inter, a.d, bf16);
+    }
+    hipLaunchKernelGGL(rm_work_kernel, dim3(1), dim3(256), 0, stream, a.expert_offsets, a.E, a.T,
+                       a.shared_inter > 0 ? 1 : 0, t, work);
+    return hipGetLastError();
+}
+
 ExpertFwdBuffers experts_fwd_buffers(const ExpertArgs& a, void* ws) {
     const ExpWs w = carve(ws, a.T, a.d, a.k, a.inter, a.shared_inter, a.act_dtype, a.E);
     ExpertFwdBuffers b;
@@ -1836,10 +1909,7 @@ hipError_t launch_generic_bwd(int step, const ExpertArgs& a, const GenericBwdPtr
     dim3 grid;
     if (step <= GB_DX) {
         const int nt_r = rm_row_tiles(step, a.inter, a.d, bf16), nt_s = rm_row_tiles(step, a.shared_inter, a.d, bf16);
-        hipLaunchKernelGGL(bwd_work_kernel, dim3(1), dim3(256), 0, stream, a.expert_offsets, a.E, a.T, FBM, nt_r, nt_s,
-                           has_shared ? 1 : 0, bp.work);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+        g.work = bp.work + step * (a.E + 2);
         grid = dim3(static_cast<unsigned>(work_bound(a.T, a.k, a.E, FBM, nt_r, nt_s, has_shared, 0)));
     } else {
         auto tiles = [&](int n_out) {

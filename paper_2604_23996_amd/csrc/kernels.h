@@ -143,7 +143,7 @@ struct GenericBwdPtrs {
     float* dx_r;        // [R][d]
     float* dx_s;        // [T][d]
     const float* wrow;  // [R] combine weight of each routed row
-    int32_t* work;      // [E + 2] work table, rebuilt by each row step
+    int32_t* work;      // [3][E + 2] work tables of the row steps (launch_generic_bwd_tables)
     void* dw13;
     void* dw2;
     void* dws13;
@@ -151,6 +151,7 @@ struct GenericBwdPtrs {
 };
 // step 0: pre-activations; 1: dH and the SwiGLU backward (dA dB, w H); 2: dX;
 // 3: dW2 and dWs2; 4: dW13 and dWs13. Routed and shared experts in one launch.
+hipError_t launch_generic_bwd_tables(const ExpertArgs& a, int32_t* work, hipStream_t stream);
 hipError_t launch_generic_bwd(int step, const ExpertArgs& a, const GenericBwdPtrs& bp, hipStream_t stream);
 // k-packed operands (fragment order, rows contiguous, each group padded to 16
 // rows) and the weight gradients from them: kp = padded row prefix of the
