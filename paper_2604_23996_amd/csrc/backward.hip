@@ -136,7 +136,7 @@ dx_gather_kernel(const void* __restrict__ dx_r, const void* __restrict__ dx_s, c
         }
     };
     // two tokens at a time, four routed rows of each in flight (with one row index
-    // and one row at a time 17 us for 1000 tokens x 1024, top-4); slots in order,
+    // and one row at a time 17 us for 1000 tokens x 1024, top-4, now 12); slots in order,
     // then the shared row. Rows past a token's are read again and not added.
 #pragma unroll
     for (int t0 = 0; t0 < kDxTok; t0 += 2) {
