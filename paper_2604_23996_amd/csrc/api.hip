@@ -565,15 +565,13 @@ struct BwdWs {
     void* wh_s;  // float32 H of the shared experts (float32 backward only)
     int32_t* work4;
     void* router;
-    // k-packed weight-gradient operands (packed bf16 path): routed rows (dout,
-    // then x, gathered), w H, [dA dB]; the same for the shared experts' tokens
+    // k-packed weight-gradient operands (packed bf16 path): w H and [dA dB] of the
+    // routed rows, H and [dA dB] of the shared experts
     int32_t* kp;
     int32_t* ranges;  // [2][9] XCD tile ranges of the two routed weight-gradient launches
     void* dxg;        // packed W_gate and dz fragments of the input gradient
-    void* pt_rows_r;
     void* pt_wh_r;
     void* pt_dab_r;
-    void* pt_rows_s;
     void* pt_h_s;
     void* pt_dab_s;
 };
@@ -604,10 +602,8 @@ size_t bwd_ws_parts(const smoes_layer* L, BwdWs* out, void* base) {
     w.kp = static_cast<int32_t*>(c.take(gen ? 0 : sizeof(int32_t) * (L->E + 1)));
     w.ranges = static_cast<int32_t*>(c.take(gen ? 0 : sizeof(int32_t) * 18));
     w.dxg = c.take(gen ? 0 : dx_mfma_workspace_bytes(T, L->d, L->E));
-    w.pt_rows_r = c.take(2 * kpack_elems(L->d, kr));
     w.pt_wh_r = c.take(2 * kpack_elems(L->inter, kr));
     w.pt_dab_r = c.take(2 * kpack_elems(2 * L->inter, kr));
-    w.pt_rows_s = c.take(2 * kpack_elems(L->d, ksh));
     w.pt_h_s = c.take(2 * kpack_elems(L->shared_inter, ksh));
     w.pt_dab_s = c.take(2 * kpack_elems(2 * L->shared_inter, ksh));
     if (out != nullptr) *out = w;
@@ -770,28 +766,26 @@ int smoes_moe_backward(const smoes_layer* L, const smoes_layer_io* io, const voi
     if (sh) {
         for (int mode = L->save_preact ? 4 : 3; mode <= 5; ++mode)
             SMOES_BTRY(launch_bwd_gemm(mode, a, fw.experts, bp, 2, c));
-        // dWs2 = dout^T H_s and dWs13 = [dA dB]_s^T X over all tokens, from k-packed copies
-        const int64_t ksh = kpad_shared(L);
-        SMOES_BTRY(launch_kpack(dout, d, nullptr, nullptr, nullptr, 1, T, ksh, bw.pt_rows_s, c));
-        SMOES_BTRY(launch_kpack(fb.h_s, SI, nullptr, nullptr, nullptr, 1, T, ksh, bw.pt_h_s, c));
-        SMOES_BTRY(launch_wgrad_pk(1, d, SI, nullptr, nullptr, T, bw.pt_rows_s, bw.pt_h_s, G->dws2, c));
-        SMOES_BTRY(launch_kpack(io->x, d, nullptr, nullptr, nullptr, 1, T, ksh, bw.pt_rows_s, c));
-        SMOES_BTRY(launch_wgrad_pk(1, 2 * SI, d, nullptr, nullptr, T, bw.pt_dab_s, bw.pt_rows_s, G->dws13, c));
+        // dWs2 = dout^T H_s and dWs13 = [dA dB]_s^T X over all tokens ([dA dB]_s k-packed by mode 4)
+        SMOES_BTRY(launch_kpack(fb.h_s, SI, T, bw.pt_h_s, c));
+        SMOES_BTRY(launch_wgrad_pk(1, d, SI, false, dout, nullptr, nullptr, nullptr, nullptr, T, T, bw.pt_h_s,
+                                   G->dws2, c));
+        SMOES_BTRY(launch_wgrad_pk(1, d, 2 * SI, true, io->x, nullptr, nullptr, nullptr, nullptr, T, T, bw.pt_dab_s,
+                                   G->dws13, c));
     }
     if (sides != nullptr) SMOES_BTRY(hipEventRecord(e_join, c));
     // routed chain
     SMOES_BTRY(launch_row_weights(perm_inv, io->topk_w, T, L->k, bw.wrow, s));
-    SMOES_BTRY(launch_kpad_offsets(offsets, L->E, bw.kp, wgrad_tiles_per_group(d, I), wgrad_tiles_per_group(2 * I, d),
+    SMOES_BTRY(launch_kpad_offsets(offsets, L->E, bw.kp, wgrad_tiles_per_group(d, I), wgrad_tiles_per_group(d, 2 * I),
                                    bw.ranges, s));
     for (int mode = L->save_preact ? 4 : 3; mode <= 5; ++mode)
         SMOES_BTRY(launch_bwd_gemm(mode, a, fw.experts, bp, 1, s));
     // dW2 = dout^T (w H) over each expert's rows (dout gathered); dW13 = [dA dB]^T X (x
-    // gathered): both operands k-packed per expert first (rows padded to 16; [dA dB] and w H by mode 4)
-    const int64_t kr = kpad_routed(L);
-    SMOES_BTRY(launch_kpack(dout, d, perm_token, offsets, bw.kp, L->E, T, kr, bw.pt_rows_r, s));
-    SMOES_BTRY(launch_wgrad_pk(L->E, d, I, bw.kp, bw.ranges, T, bw.pt_rows_r, bw.pt_wh_r, G->dw2, s));
-    SMOES_BTRY(launch_kpack(io->x, d, perm_token, offsets, bw.kp, L->E, T, kr, bw.pt_rows_r, s));
-    SMOES_BTRY(launch_wgrad_pk(L->E, 2 * I, d, bw.kp, bw.ranges + 9, T, bw.pt_dab_r, bw.pt_rows_r, G->dw13, s));
+    // gathered); [dA dB] and w H were k-packed by mode 4 (each expert's rows padded to 16)
+    SMOES_BTRY(launch_wgrad_pk(L->E, d, I, false, dout, perm_token, offsets, bw.kp, bw.ranges, T, T * L->k, bw.pt_wh_r,
+                               G->dw2, s));
+    SMOES_BTRY(launch_wgrad_pk(L->E, d, 2 * I, true, io->x, perm_token, offsets, bw.kp, bw.ranges + 9, T, T * L->k,
+                               bw.pt_dab_r, G->dw13, s));
     if (sides != nullptr) SMOES_BTRY(hipStreamWaitEvent(s, e_join, 0));
     SMOES_BTRY(launch_dx_gather(bw.dx_r, sh ? bw.dx_s : nullptr, 1, perm_inv, G->dz, io->w_gate, T, L->d, L->E, L->k,
                                 G->dx, bw.dxg, s));

@@ -1,12 +1,15 @@
 // Expert weight gradients of the layer backward: for each group g (a routed
 // expert over its expert-contiguous rows, or the merged shared expert over
 // all tokens)
-//   dW_g[m][n] = sum_r A[ra(r)][m] * B[rb(r)][n]
-// where at most one operand's rows go through a row map (the permutation's
-// token of a routed row): dW2 = dout^T (w H) with dout gathered, dW13 =
-// [dA dB]^T X with x gathered. Both operands are first written once more in
-// the matrix cores' fragment order with the contraction (the group's rows)
-// contiguous, then multiplied with the forward's packed tiling.
+//   dW_g[m][n] = sum_r A[ra(r)][m] * B[r][n]
+// where the rows of A go through a row map (the permutation's token of a
+// routed row) or are the tokens: dW2 = dout^T (w H) with A = dout, dW13 =
+// [dA dB]^T X with A = x (and the output transposed). B is k-packed: in the
+// matrix cores' fragment order with the contraction (the group's rows)
+// contiguous, as the dH GEMM writes w H and [dA dB]; the shared experts' H is
+// packed here.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -16,17 +19,14 @@ namespace {
 
 // ============================================================ k-packed weight gradients
 //
-// The same products from operands stored once more, per group, in the matrix
-// cores' fragment order with the contraction (the group's rows) contiguous:
-// for a row-major S with C columns and a group of rows [r0, r1) (rows taken
-// through a row map when given),
-//   P[cg][ks][l][e] = S[row(r0 + 16 ks + 8 (l / 32) + e)][32 cg + l % 32],
-// zero past the group's rows and past C; the groups follow each other, each
+// k-packed, for a row-major S with C columns and a group of rows [r0, r1):
+//   P[cg][ks][l][e] = S[r0 + 16 ks + 8 (l / 32) + e][32 cg + l % 32],
+// zero past the group's rows; the groups follow each other, each
 // padded to a multiple of 16 rows (kp: the padded row prefix). A fragment is
 // one 1 KB block: lane l's 16 bytes are an MFMA operand as they are.
-// wgrad_pk_kernel then runs the forward's packed tiling: 128 (m) x 256 (n)
-// tiles, the m operand brought to LDS by buffer-to-LDS loads through a
-// three-stage ring of K = 64 slices and read with plain 16-byte LDS reads, the
+// wgrad_pk_kernel runs the forward's packed tiling: 128 (m) x 256 (n)
+// tiles, the row-major m operand brought to LDS by buffer-to-LDS loads through
+// a three-stage ring of K = 64 slices and read with transposing LDS reads, the
 // n operand loaded straight into registers one slice ahead.
 
 constexpr int KP_COLS = 256;  // source columns per k-pack block (8 column groups)
@@ -77,49 +77,25 @@ kpad_offsets_kernel(const int32_t* __restrict__ off, int E, int32_t* __restrict_
     }
 }
 
-// One block per (16-row slice of the padded row space, 256 source columns):
-// the slice's rows come into LDS as rows, and each lane writes one fragment
-// lane (8 consecutive rows of one column) as 16 bytes.
+// One block per (16-row slice, 256 source columns) of one group of T rows: the
+// slice's rows come into LDS as rows, and each lane writes one fragment lane (8
+// consecutive rows of one column) as 16 bytes.
 __global__ void __launch_bounds__(256)
-kpack_kernel(const uint16_t* __restrict__ S, int C, const int32_t* __restrict__ map, const int32_t* __restrict__ off,
-             const int32_t* __restrict__ kp, int n_groups, int64_t T, uint16_t* __restrict__ P) {
+kpack_kernel(const uint16_t* __restrict__ S, int C, int64_t T, uint16_t* __restrict__ P) {
     __shared__ __attribute__((aligned(16))) uint16_t tile[16][KP_COLS + 8];
-    const int64_t prow = static_cast<int64_t>(blockIdx.x) * 16;  // first padded row of the slice
-    int64_t kp0, kp1, r0, r1;
-    if (kp == nullptr) {  // one group of T rows
-        kp0 = 0;
-        kp1 = ceil_div(T, 16) * 16;
-        r0 = 0;
-        r1 = T;
-        if (prow >= kp1) return;
-    } else {
-        if (prow >= kp[n_groups]) return;  // past the padded total (the grid is sized for a bound)
-        int lo = 0, hi = n_groups - 1;     // last g with kp[g] <= prow
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (kp[mid] <= prow) lo = mid; else hi = mid - 1;
-        }
-        kp0 = kp[lo];
-        kp1 = kp[lo + 1];
-        r0 = off[lo];
-        r1 = off[lo + 1];
-    }
-    const int64_t ks = (prow - kp0) / 16, Ks = (kp1 - kp0) / 16;
+    const int64_t ks = blockIdx.x, Ks = ceil_div(T, 16);
     const int CG = static_cast<int>(ceil_div(C, 32));
     const int c0 = blockIdx.y * KP_COLS;
     for (int q = threadIdx.x; q < 16 * (KP_COLS / 8); q += blockDim.x) {
         const int rr = q / (KP_COLS / 8), ch = q % (KP_COLS / 8);
-        const int64_t r = r0 + 16 * ks + rr;
+        const int64_t r = 16 * ks + rr;
         const int c = c0 + ch * 8;
         uint4 v = make_uint4(0, 0, 0, 0);
-        if (r < r1 && c < C) {  // C % 8 == 0: a chunk is all in or all out
-            const int64_t src = map != nullptr ? static_cast<int64_t>(map[r]) : r;
-            v = *reinterpret_cast<const uint4*>(S + src * C + c);
-        }
+        if (r < T && c < C)  // C % 8 == 0: a chunk is all in or all out
+            v = *reinterpret_cast<const uint4*>(S + r * C + c);
         *reinterpret_cast<uint4*>(&tile[rr][ch * 8]) = v;
     }
     __syncthreads();
-    uint16_t* Pg = P + 32 * static_cast<int64_t>(CG) * kp0;
     for (int q = threadIdx.x; q < (KP_COLS / 32) * 64; q += blockDim.x) {
         const int f = q / 64, l = q % 64;
         const int cg = c0 / 32 + f;
@@ -129,19 +105,35 @@ kpack_kernel(const uint16_t* __restrict__ S, int C, const int32_t* __restrict__ 
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             w[e] = static_cast<uint32_t>(tile[rb + 2 * e][col]) | (static_cast<uint32_t>(tile[rb + 2 * e + 1][col]) << 16);
-        *reinterpret_cast<uint4*>(Pg + (static_cast<int64_t>(cg) * Ks + ks) * 512 + l * 8) =
+        *reinterpret_cast<uint4*>(P + (static_cast<int64_t>(cg) * Ks + ks) * 512 + l * 8) =
             make_uint4(w[0], w[1], w[2], w[3]);
     }
+}
+
+typedef short v4i16_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) v4i16_t lds_v4i16_t;
+
+// f(0) .. f(3) with the index as a compile-time constant
+template <class F>
+__device__ __forceinline__ void unroll4(F f) {
+    f(std::integral_constant<int, 0>{});
+    f(std::integral_constant<int, 1>{});
+    f(std::integral_constant<int, 2>{});
+    f(std::integral_constant<int, 3>{});
 }
 
 constexpr int WP_BM = 128, WP_TN = 256, WP_BK = 64, WP_ST = 3, WP_THREADS = 256;
 // m tiles per super-row of the tile order (16: 1504 -> 1473 us per routed launch at 16384 x 4096,
 // 160 experts, against 8; 4: 1492 us)
 constexpr int kWpGroupM = 16;
-constexpr int WP_A_BYTES = WP_BM * WP_BK * 2;  // 16 fragments of 1 KB per stage
-constexpr int WP_OP = WP_TN + 8;               // epilogue row pitch (elements)
+constexpr int WP_A_BYTES = WP_BM * WP_BK * 2;  // 64 rows x 128 columns per stage
 constexpr int WP_EPI = 2 * WP_A_BYTES;         // epilogue staging: past ring slots 0 and 1
-constexpr int WP_LDS = WP_EPI + (WP_BM / 2) * WP_OP * 2;
+// half an output tile: 64 m rows of 256 n, or 128 n rows of 128 m (pitches of + 8 elements)
+constexpr int wp_epi_bytes(bool nrows) {
+    return nrows ? (WP_TN / 2) * (WP_BM + 8) * 2 : (WP_BM / 2) * (WP_TN + 8) * 2;
+}
+constexpr int WP_LDS = WP_EPI + wp_epi_bytes(true);
+static_assert(wp_epi_bytes(true) >= wp_epi_bytes(false), "either half tile fits");
 static_assert(WP_LDS >= WP_ST * WP_A_BYTES, "the ring fits");
 
 struct WpArgs {
@@ -149,9 +141,12 @@ struct WpArgs {
     const int32_t* kp;   // [n_groups + 1] padded row prefix, or NULL: one group of T rows
     const int32_t* ranges;  // [9] first tile of each XCD's range (work-balanced), or NULL: equal counts
     int64_t T;
-    const uint16_t* PA;  // k-packed m operand (M source columns)
+    const uint16_t* A;   // m operand, row-major: [T][M]
+    const int32_t* map;  // row of A for each row of the groups, or NULL: the row itself
+    const int32_t* off;  // [n_groups + 1] first row of each group (with kp)
+    int64_t n_rows;      // rows of all groups (entries of map)
     const uint16_t* PB;  // k-packed n operand (N source columns)
-    uint16_t* out;       // [n_groups][M][N] bf16
+    uint16_t* out;       // bf16 [n_groups][M][N], or [n_groups][N][M] (NROWS)
 };
 
 // Persistent: block (x = blockIdx % 8, seat) runs on XCD x and takes the
@@ -161,6 +156,18 @@ struct WpArgs {
 // is written (staged through LDS past ring slots 0 and 1, half a tile at a
 // time, with buffer stores that every lane issues whatever the bounds), so
 // the next tile's first data arrives while the stores drain.
+//
+// The m operand is dout or x as it is: a stage's 64 rows (MAP: gathered, their
+// indices loaded a stage ahead of the DMA that needs them) of the tile's 128
+// columns go to LDS row by row, and a fragment is two transposing reads of four
+// rows of 16 columns per 16 lanes. DMA q of wave w brings rows 16 w + 4 a + q
+// (a = 0..3) as 256-byte LDS rows 16 w + 4 q + a, their 16-byte chunks XORed
+// with 4 q, so that the four rows of a transposing read lie in distinct banks.
+// k-packed like the n operand, each of the gathered matrices took a pass of its
+// own: 2 x 132 + 2 x 29 us for 16384 tokens x 2048, 64 experts top-6.
+// NROWS: the output's rows are the n operand's columns (dW13, whose gathered
+// operand is its columns): the matrix products swap their operands.
+template <bool MAP, bool NROWS>
 __global__ void __launch_bounds__(WP_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 wgrad_pk_kernel(WpArgs p) {
     __shared__ __attribute__((aligned(1024))) uint8_t lds[WP_LDS];
@@ -181,17 +188,19 @@ wgrad_pk_kernel(WpArgs p) {
     hi = uniform_int(hi);
     int b = lo + seat;
     if (b >= hi) return;
-    const int MG = static_cast<int>(ceil_div(p.M, 32)), NG = static_cast<int>(ceil_div(p.N, 32));
+    const int NG = static_cast<int>(ceil_div(p.N, 32));
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = lane_id();
-    const int half = lane >> 5, l32 = lane & 31;
+    const int half = lane >> 5;
 
-    // the tile whose operands are being requested: its group, corner and
-    // 16-row slice count, the operand descriptors, and this lane's byte
-    // offsets of slice 0 of its m fragment and its two n fragments (out of
-    // range past the matrix edge)
+    const int lrow = 16 * wave + 4 * (lane >> 4) + (lane & 3);  // row of a stage whose index this lane holds
+    const i32x4_t rsA = buf_rsrc(p.A, static_cast<int>(p.T * p.M * 2));
+    const __amdgpu_buffer_rsrc_t rsI = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<int32_t*>(p.map), 0, MAP ? static_cast<int>(p.n_rows * 4) : 0, kBufferFlags);
+
+    // the tile whose operands are being requested: its group, corner, first
+    // row, row and 16-row slice counts, and the n operand's descriptor
     struct Tile {
-        int g, m0, n0, Ks, va, vb0, vb1;
-        i32x4_t rsA;
+        int g, m0, n0, r0, rows, Ks;
         __amdgpu_buffer_rsrc_t rsB;
     };
     auto decode = [&](int bb) {
@@ -207,67 +216,97 @@ wgrad_pk_kernel(WpArgs p) {
         const int64_t kp0 = p.kp != nullptr ? p.kp[t.g] : 0;
         const int64_t kp1 = p.kp != nullptr ? p.kp[t.g + 1] : ceil_div(p.T, 16) * 16;
         t.Ks = uniform_int(static_cast<int>((kp1 - kp0) / 16));  // 16-row slices of the group
-        const uint16_t* PAg = p.PA + 32 * static_cast<int64_t>(MG) * kp0;
+        t.r0 = p.kp != nullptr ? uniform_int(p.off[t.g]) : 0;
+        t.rows = p.kp != nullptr ? uniform_int(p.off[t.g + 1]) - t.r0 : static_cast<int>(p.T);
         const uint16_t* PBg = p.PB + 32 * static_cast<int64_t>(NG) * kp0;
-        t.rsA = buf_rsrc(PAg, MG * t.Ks * 1024);
         t.rsB = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(uniform_ptr(PBg)), 0,
                                                   uniform_int(NG * t.Ks * 1024), kBufferFlags);
-        const int mg = t.m0 / 32 + wave, ng = t.n0 / 32 + 2 * wave;
-        t.va = mg < MG ? (mg * t.Ks * 64 + lane) * 16 : kOutOfRange;
-        t.vb0 = ng < NG ? (ng * t.Ks * 64 + lane) * 16 : kOutOfRange;
-        t.vb1 = ng + 1 < NG ? ((ng + 1) * t.Ks * 64 + lane) * 16 : kOutOfRange;
         return t;
     };
     const uint32_t lds_base = lds_address(lds);
-    // A DMA q of stage s: fragment (m group m0 / 32 + wave, slice 4 s + q) into LDS block wave * 4 + q of the slot
-    auto issue_aq = [&](const Tile& t, int slot, int s, int q) {
-        const int ks = 4 * s + q;
-        const int vo = (t.va + ks * 1024) | (ks < t.Ks ? 0 : kOutOfRange);
-        dma16(t.rsA, vo, lds_base + slot * WP_A_BYTES + (wave * 4 + q) * 1024);
+    // index of this lane's row of stage s (any value past the group's rows: the DMA masks them)
+    auto load_idx = [&](const Tile& t, int s) {
+        return MAP ? __builtin_amdgcn_raw_buffer_load_b32(rsI, (t.r0 + 64 * s + lrow) * 4, 0, 0) : 0;
+    };
+    // byte offset in A of this lane's row of stage s, out of range past the group's rows
+    auto row_off = [&](const Tile& t, int s, int idx) {
+        const int R = 64 * s + lrow;
+        return R < t.rows ? (MAP ? idx : t.r0 + R) * (p.M * 2) : kOutOfRange;
+    };
+    // A DMA q of a stage with row offsets ro into its ring slot: every lane of a row takes the
+    // offset of row 4 (lane / 16) + q of the wave's 16 (a quad broadcast)
+    auto issue_aq = [&](const Tile& t, int slot, int ro, auto q_c) {
+        constexpr int q = decltype(q_c)::value;
+        const int col = t.m0 * 2 + (((lane & 15) * 16) ^ (q * 64));  // M % 8 == 0: a chunk is all in or all out
+        const int vo = static_cast<int>(static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(ro, q * 0x55, 0xf, 0xf, true)) +
+                                        static_cast<uint32_t>(col)) |
+                       (col < p.M * 2 ? 0 : kOutOfRange);
+        dma16(rsA, vo, lds_base + slot * WP_A_BYTES + (wave * 4 + q) * 1024);
     };
     // the two n fragments (n groups n0 / 32 + 2 wave + gg) of slice 4 s + j
     auto issue_bj = [&](const Tile& t, i32x4_t (&bq)[4][2], int s, int j) {
-        const int ks = 4 * s + j;
-        const int past = ks < t.Ks ? 0 : kOutOfRange;
-        bq[j][0] = __builtin_amdgcn_raw_buffer_load_b128(t.rsB, (t.vb0 + ks * 1024) | past, 0, 0);
-        bq[j][1] = __builtin_amdgcn_raw_buffer_load_b128(t.rsB, (t.vb1 + ks * 1024) | past, 0, 0);
-    };
-    i32x4_t b0[4][2], b1[4][2];
-    // stages 0 and 1 of the decoded tile: 16 loads per wave, the 4 DMAs of stage 0 first
-    auto prologue = [&](const Tile& t) {
+        const int ks = 4 * s + j, ng = t.n0 / 32 + 2 * wave;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) issue_aq(t, 0, 0, q);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            issue_bj(t, b0, 0, j);
-            issue_aq(t, 1, 1, j);
+        for (int gg = 0; gg < 2; ++gg) {  // out of range past the group's rows and the matrix edge
+            const int so = ks < t.Ks && ng + gg < NG ? ((ng + gg) * t.Ks + ks) * 1024 : kOutOfRange;
+            bq[j][gg] = __builtin_amdgcn_raw_buffer_load_b128(
+                t.rsB, static_cast<int>(static_cast<uint32_t>(so) + static_cast<uint32_t>(lane * 16)), 0, 0);
         }
     };
+    i32x4_t b0[4][2], b1[4][2];
+    // stages 0 and 1 of the decoded tile (row indices in i0 and i1): 16 loads per wave, the 4
+    // DMAs of stage 0 first
+    auto prologue = [&](const Tile& t, int i0, int i1) {
+        const int ro0 = row_off(t, 0, i0), ro1 = row_off(t, 1, i1);
+        unroll4([&](auto q) { issue_aq(t, 0, ro0, q); });
+        unroll4([&](auto j) {
+            issue_bj(t, b0, 0, j);
+            issue_aq(t, 1, ro1, j);
+        });
+    };
     f32x16_t acc[4][2];
+    // this lane's address for the transposing reads of m group 0, slice 0: row 4 q + 2 half (q =
+    // lane % 16 / 4, logical row 8 half + q) and the one after it, columns 16 (lane / 16 % 2) +
+    // 4 (lane % 4) ..; m group i is 64 i bytes away under the swizzle
+    const int tq = (lane & 15) >> 2;
+    const int tr0 = (4 * tq + 2 * half) * 256 + tq * 64 + ((lane >> 4) & 1) * 32 + ((lane & 3) >> 1) * 16 + (lane & 1) * 8;
     // stage s from ring slot `slot`: substep j issues the n fragments of stage
     // s + 1 (2 loads) and the DMA q = j of stage s + 2, reads the m fragments
-    // of substep j + 1 and runs 8 MFMAs
-    auto stage_run = [&](const Tile& t, int slot, int s, const i32x4_t (&bc)[4][2], i32x4_t (&bn)[4][2]) {
+    // of substep j + 1 and runs 8 MFMAs. ic: row indices of stage s + 2; in: those of
+    // stage s + 3, loaded first.
+    auto stage_run = [&](const Tile& t, int slot, int s, const i32x4_t (&bc)[4][2], i32x4_t (&bn)[4][2], int ic, int& in) {
         const uint8_t* base = lds + slot * WP_A_BYTES;
         const int nslot = slot == 0 ? 2 : slot - 1;  // (slot + 2) % 3
         bf16x8_t af[2][4];
         auto rd = [&](int j, bf16x8_t (&a)[4]) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = *reinterpret_cast<const bf16x8_t*>(base + (i * 4 + j) * 1024 + lane * 16);
+            for (int i = 0; i < 4; ++i) {
+                const uint8_t* a0 = base + (tr0 ^ (i * 64)) + j * 4096;
+                const v4i16_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_t*)a0);
+                const v4i16_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_t*)(a0 + 256));
+                const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
+                a[i] = __builtin_bit_cast(bf16x8_t, make_uint4(l2.x, l2.y, h2.x, h2.y));
+            }
         };
         rd(0, af[0]);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        const int ro = row_off(t, s + 2, ic);
+        in = load_idx(t, s + 3);
+        unroll4([&](auto j_c) {
+            constexpr int j = decltype(j_c)::value;
             __builtin_amdgcn_sched_barrier(0);
             issue_bj(t, bn, s + 1, j);
-            issue_aq(t, nslot, s + 2, j);
-            if (j < 3) rd(j + 1, af[(j + 1) & 1]);
+            issue_aq(t, nslot, ro, j_c);
+            if constexpr (j < 3) rd(j + 1, af[(j + 1) & 1]);
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int gg = 0; gg < 2; ++gg)  // rows of the MFMA tile: n, columns: m
-                    acc[i][gg] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        __builtin_bit_cast(bf16x8_t, bc[j][gg]), af[j & 1][i], acc[i][gg], 0, 0, 0);
+                for (int gg = 0; gg < 2; ++gg) {
+                    const bf16x8_t n = __builtin_bit_cast(bf16x8_t, bc[j][gg]);
+                    if constexpr (NROWS)  // rows of the MFMA tile: m, columns: n
+                        acc[i][gg] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[j & 1][i], n, acc[i][gg], 0, 0, 0);
+                    else  // rows of the MFMA tile: n, columns: m
+                        acc[i][gg] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(n, af[j & 1][i], acc[i][gg], 0, 0, 0);
+                }
 #pragma unroll
             for (int q = 0; q < 3; ++q) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -276,10 +315,10 @@ wgrad_pk_kernel(WpArgs p) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
             }
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        }
+        });
         __builtin_amdgcn_sched_barrier(0);
     };
     // Vector memory operations retire in order. Before stage s reads its
@@ -287,16 +326,26 @@ wgrad_pk_kernel(WpArgs p) {
     // fly: for s >= 2 the 12 of stage s - 1's run (n fragments of stage s,
     // DMA of stage s + 1); for s = 0 and 1 of every tile but a block's first
     // also the 16 output stores of the previous tile, issued after this
-    // tile's first two stages were requested. The barrier makes every
+    // tile's first two stages were requested. Row index loads are not counted:
+    // they are the oldest of their run and due in the next one. The barrier makes every
     // wave's DMA visible and frees the slot the DMA of stage s + 2
     // overwrites. Past the group's rows every load is out of range and
     // returns zeros, so every stage issues the same count and the waits stay
     // exact.
     constexpr int kStoresPerTile = (WP_BM * WP_TN / 8) / WP_THREADS;  // 16-byte stores per lane
     Tile cur = decode(b);
-    prologue(cur);
+    int ie = load_idx(cur, 2), io = 0;  // row indices of the even and odd stage that the DMAs reach next
+    {
+        const int i0 = load_idx(cur, 0), i1 = load_idx(cur, 1);
+        prologue(cur, i0, i1);
+    }
     bool after_stores = false;
     for (;;) {
+        // the next tile and the row indices of its first two stages, loaded under this one's products
+        const int nb = b + seats;
+        Tile nxt = cur;
+        if (nb < hi) nxt = decode(nb);
+        const int n0i = load_idx(nxt, 0), n1i = load_idx(nxt, 1);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -308,74 +357,87 @@ wgrad_pk_kernel(WpArgs p) {
                 if (after_stores) wait_vm_lgkm0<12 + kStoresPerTile>();
                 else wait_vm_lgkm0<12>();
                 __builtin_amdgcn_s_barrier();
-                stage_run(cur, 0, 0, b0, b1);
+                stage_run(cur, 0, 0, b0, b1, ie, io);
             }
             if (nk > 1) {
                 if (after_stores) wait_vm_lgkm0<12 + kStoresPerTile>();
                 else wait_vm_lgkm0<12>();
                 __builtin_amdgcn_s_barrier();
-                stage_run(cur, 1, 1, b1, b0);
+                stage_run(cur, 1, 1, b1, b0, io, ie);
             }
             s = 2;
             slot = 2;
             for (; s + 2 <= nk; s += 2) {
                 wait_vm_lgkm0<12>();
                 __builtin_amdgcn_s_barrier();
-                stage_run(cur, slot, s, b0, b1);
+                stage_run(cur, slot, s, b0, b1, ie, io);
                 slot = slot == 2 ? 0 : slot + 1;
                 wait_vm_lgkm0<12>();
                 __builtin_amdgcn_s_barrier();
-                stage_run(cur, slot, s + 1, b1, b0);
+                stage_run(cur, slot, s + 1, b1, b0, io, ie);
                 slot = slot == 2 ? 0 : slot + 1;
             }
             if (s < nk) {
                 wait_vm_lgkm0<12>();
                 __builtin_amdgcn_s_barrier();
-                stage_run(cur, slot, s, b0, b1);
+                stage_run(cur, slot, s, b0, b1, ie, io);
             }
         }
         wait_vm_lgkm0<0>();  // drain: the next tile's DMA reuses the ring
         __builtin_amdgcn_s_barrier();
         // output of this tile, then the next tile's first two stages
         const int og = cur.g, om0 = cur.m0, on0 = cur.n0;
-        const int nb = b + seats;
         if (nb < hi) {
-            cur = decode(nb);
-            prologue(cur);
+            cur = nxt;
+            ie = load_idx(cur, 2);
+            prologue(cur, n0i, n1i);
         }
         const __amdgpu_buffer_rsrc_t rsO = __builtin_amdgcn_make_buffer_rsrc(
             uniform_ptr(p.out + static_cast<int64_t>(og) * p.M * p.N), 0, uniform_int(p.M * p.N * 2), kBufferFlags);
         uint16_t* ot = reinterpret_cast<uint16_t*>(lds + WP_EPI);
+        // opaque: the addresses below are rebuilt per tile instead of held in registers across the K loop
+        int tid = static_cast<int>(threadIdx.x);
+        asm volatile("" : "+v"(tid));
+        const int e_half = (tid >> 5) & 1, e_l32 = tid & 31;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            // element v of lane l of acc[i][gg]: n = 8 (v / 4) + 4 half + v % 4 of n group
-            // 2 wave + gg of the tile, m = l32 of m group i; four adjacent n go to LDS as
-            // 8 bytes, then whole rows of the half tile to memory
+            // Element v of lane l of acc[i][gg] is n = 8 (v / 4) + 4 half + v % 4 of n group 2 wave
+            // + gg of the tile and m = l32 of m group i (NROWS: m and n the other way round). Four
+            // adjacent columns of an output row go to LDS as 8 bytes, then whole rows of the half
+            // tile (m groups 2 h, 2 h + 1; NROWS: n group h of each wave) to memory.
+            constexpr int OC = NROWS ? WP_BM : WP_TN, OP = OC + 8;  // columns and row pitch
+            auto put = [&](const f32x16_t& a, int vq, int row, int col) {
+                *reinterpret_cast<uint2*>(ot + row * OP + col + 8 * vq + 4 * e_half) =
+                    make_uint2(static_cast<uint32_t>(f32_to_bf16(a[4 * vq])) |
+                                   (static_cast<uint32_t>(f32_to_bf16(a[4 * vq + 1])) << 16),
+                               static_cast<uint32_t>(f32_to_bf16(a[4 * vq + 2])) |
+                                   (static_cast<uint32_t>(f32_to_bf16(a[4 * vq + 3])) << 16));
+            };
 #pragma unroll
-            for (int i = 2 * h; i < 2 * h + 2; ++i)
+            for (int vq = 0; vq < 4; ++vq) {
+                if constexpr (NROWS) {
 #pragma unroll
-                for (int vq = 0; vq < 4; ++vq)
+                    for (int i = 0; i < 4; ++i) put(acc[i][h], vq, wave * 32 + e_l32, i * 32);
+                } else {
 #pragma unroll
-                    for (int gg = 0; gg < 2; ++gg) {
-                        const f32x16_t& a = acc[i][gg];
-                        *reinterpret_cast<uint2*>(ot + ((i - 2 * h) * 32 + l32) * WP_OP + wave * 64 + gg * 32 + 8 * vq +
-                                                  4 * half) =
-                            make_uint2(static_cast<uint32_t>(f32_to_bf16(a[4 * vq])) |
-                                           (static_cast<uint32_t>(f32_to_bf16(a[4 * vq + 1])) << 16),
-                                       static_cast<uint32_t>(f32_to_bf16(a[4 * vq + 2])) |
-                                           (static_cast<uint32_t>(f32_to_bf16(a[4 * vq + 3])) << 16));
-                    }
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int gg = 0; gg < 2; ++gg) put(acc[2 * h + i][gg], vq, i * 32 + e_l32, wave * 64 + gg * 32);
+                }
+            }
             __syncthreads();
-            constexpr int CH = WP_TN / 8;
+            constexpr int CH = OC / 8;
+            const int n_r = NROWS ? p.N : p.M, n_c = NROWS ? p.M : p.N;
 #pragma unroll
             for (int u = 0; u < kStoresPerTile / 2; ++u) {
-                const int q = u * WP_THREADS + static_cast<int>(threadIdx.x);
+                const int q = u * WP_THREADS + tid;
                 const int r = q / CH, c = (q % CH) * 8;
-                const int row = om0 + 64 * h + r, col = on0 + c;
-                // N % 8 == 0: a chunk is all in or all out; out of range the store is dropped
-                const int vo = (row < p.M && col < p.N) ? (row * p.N + col) * 2 : kOutOfRange;
-                __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const i32x4_t*>(ot + r * WP_OP + c), rsO,
-                                                       vo, 0, kBufferNonTemporal);
+                const int row = NROWS ? on0 + (r / 32) * 64 + 32 * h + r % 32 : om0 + 64 * h + r;
+                const int col = (NROWS ? om0 : on0) + c;
+                // n_c % 8 == 0: a chunk is all in or all out; out of range the store is dropped
+                const int vo = (row < n_r && col < n_c) ? (row * n_c + col) * 2 : kOutOfRange;
+                __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const i32x4_t*>(ot + r * OP + c), rsO, vo, 0,
+                                                       kBufferNonTemporal);
             }
             __syncthreads();  // the half tile's LDS reads are done before the next writes
         }
@@ -398,18 +460,17 @@ hipError_t launch_kpad_offsets(const int32_t* off, int E, int32_t* kp, int per0,
     return hipGetLastError();
 }
 
-hipError_t launch_kpack(const void* S, int C, const int32_t* map, const int32_t* off, const int32_t* kp,
-                        int n_groups, int64_t T, int64_t max_padded_rows, void* P, hipStream_t stream) {
-    const int64_t slices = ceil_div(max_padded_rows, 16);
-    if (slices == 0 || C == 0) return hipSuccess;
-    const dim3 grid(static_cast<unsigned>(slices), static_cast<unsigned>(ceil_div(C, KP_COLS)));
-    hipLaunchKernelGGL(kpack_kernel, grid, dim3(256), 0, stream, static_cast<const uint16_t*>(S), C, map, off, kp,
-                       n_groups, T, static_cast<uint16_t*>(P));
+hipError_t launch_kpack(const void* S, int C, int64_t T, void* P, hipStream_t stream) {
+    if (T == 0 || C == 0) return hipSuccess;
+    const dim3 grid(static_cast<unsigned>(ceil_div(T, 16)), static_cast<unsigned>(ceil_div(C, KP_COLS)));
+    hipLaunchKernelGGL(kpack_kernel, grid, dim3(256), 0, stream, static_cast<const uint16_t*>(S), C, T,
+                       static_cast<uint16_t*>(P));
     return hipGetLastError();
 }
 
-hipError_t launch_wgrad_pk(int n_groups, int M, int N, const int32_t* kp, const int32_t* ranges, int64_t T,
-                           const void* PA, const void* PB, void* out, hipStream_t stream) {
+hipError_t launch_wgrad_pk(int n_groups, int M, int N, bool n_rows_out, const void* A, const int32_t* map,
+                           const int32_t* off, const int32_t* kp, const int32_t* ranges, int64_t T, int64_t n_rows,
+                           const void* PB, void* out, hipStream_t stream) {
     if (n_groups == 0 || M == 0 || N == 0) return hipSuccess;
     WpArgs p;
     p.n_groups = n_groups;
@@ -418,13 +479,18 @@ hipError_t launch_wgrad_pk(int n_groups, int M, int N, const int32_t* kp, const 
     p.kp = kp;
     p.ranges = ranges;
     p.T = T;
-    p.PA = static_cast<const uint16_t*>(PA);
+    p.A = static_cast<const uint16_t*>(A);
+    p.map = map;
+    p.off = off;
+    p.n_rows = n_rows;
     p.PB = static_cast<const uint16_t*>(PB);
     p.out = static_cast<uint16_t*>(out);
     // two resident workgroups per CU, 32 CUs per XCD; fewer when there are fewer tiles
     const int64_t nblk = static_cast<int64_t>(n_groups) * ceil_div(M, WP_BM) * ceil_div(N, WP_TN);
     const int64_t per_xcd = ceil_div(nblk, 8) < 64 ? ceil_div(nblk, 8) : 64;
-    hipLaunchKernelGGL(wgrad_pk_kernel, dim3(static_cast<unsigned>(8 * per_xcd)), dim3(WP_THREADS), 0, stream, p);
+    const auto kernel = map != nullptr ? (n_rows_out ? wgrad_pk_kernel<true, true> : wgrad_pk_kernel<true, false>)
+                                       : (n_rows_out ? wgrad_pk_kernel<false, true> : wgrad_pk_kernel<false, false>);
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(8 * per_xcd)), dim3(WP_THREADS), 0, stream, p);
     return hipGetLastError();
 }
 
