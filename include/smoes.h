@@ -496,11 +496,11 @@ typedef struct smoes_layer_grads {
 /*
  * Bytes of the backward's workspace for desc (0 for an invalid desc): the
  * recomputed pre-activations and their gradients, each routed row's input
- * gradient, and w H and for bf16 layers with packed weights also [dA dB] and
- * the shared experts' H k-packed (each expert's rows padded to 16; w H only so).
+ * gradient and w H; for bf16 layers with packed weights their gradients, w H
+ * and the shared experts' H are k-packed (each expert's rows padded to 16).
  * At T = 16384, d = 4096, 160 experts of inter 1536, top-6 and two shared
- * experts the k-packed operands take 1.2 GB and the whole workspace 3.1 GB
- * (3.9 GB when the forward did not keep the pre-activations). Host arithmetic only.
+ * experts the k-packed operands take 1.2 GB and the whole workspace 2.3 GB
+ * (3.1 GB when the forward did not keep the pre-activations). Host arithmetic only.
  */
 size_t smoes_backward_workspace_bytes(const smoes_layer* desc);
 

@@ -589,12 +589,12 @@ size_t bwd_ws_parts(const smoes_layer* L, BwdWs* out, void* base) {
     // the pre-activations are recomputed here unless the forward kept them
     w.ab_r = c.take(L->save_preact ? 0 : es * R * 2 * L->inter);
     w.ab_s = c.take(L->save_preact ? 0 : es * T * 2 * L->shared_inter);
-    w.dab_r = c.take(es * R * 2 * L->inter);
-    w.dab_s = c.take(es * T * 2 * L->shared_inter);
+    w.dab_r = c.take(gen ? es * R * 2 * L->inter : 0);  // the packed path writes [dA dB] and w H k-packed only
+    w.dab_s = c.take(gen ? es * T * 2 * L->shared_inter : 0);
     w.dx_r = c.take(es * R * L->d);
     w.dx_s = c.take(es * T * L->d);
     w.wrow = static_cast<float*>(c.take(sizeof(float) * R));
-    w.wh_r = c.take(gen ? es * R * L->inter : 0);  // the packed path writes w H k-packed only
+    w.wh_r = c.take(gen ? es * R * L->inter : 0);
     w.wh_s = c.take(gen ? es * T * L->shared_inter : 0);
     w.work4 = static_cast<int32_t*>(c.take(sizeof(int32_t) * (gen ? 3 : 1) * (L->E + 2)));
     w.router = c.take(router_bwd_workspace_bytes(T, L->d, L->E, L->act_dtype == SMOES_BF16 ? 1 : 0));
@@ -728,8 +728,6 @@ int smoes_moe_backward(const smoes_layer* L, const smoes_layer_io* io, const voi
     bp.ws13t = ws13t;
     bp.ab_r = L->save_preact ? fw.ab_r : bw.ab_r;
     bp.ab_s = L->save_preact ? fw.ab_s : bw.ab_s;
-    bp.dab_r = bw.dab_r;
-    bp.dab_s = bw.dab_s;
     bp.dx_r = bw.dx_r;
     bp.dx_s = bw.dx_s;
     bp.wrow = bw.wrow;

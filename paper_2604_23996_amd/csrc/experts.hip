@@ -210,13 +210,11 @@ struct GemmArgs {
     const void* ws13t;  // packed Ws13^T (N = d, K = 2 shared_inter)
     void* ab_r;         // [R][2 inter] pre-activations (gate | up), routed rows
     void* ab_s;         // [T][2 shared_inter]
-    void* dab_r;        // [R][2 inter] their gradients
-    void* dab_s;        // [T][2 shared_inter]
     void* dx_r;         // [R][d] input gradient of each routed row
     void* dx_s;         // [T][d] shared experts' input gradient
     const float* wrow;  // [R] combine weight of each routed row
-    // mode 4 outputs for the weight gradients, k-packed (wgrad.hip): the routed
-    // rows' [dA dB] and w H (kp: padded row prefix of the experts), the shared [dA dB]
+    // mode 4 outputs, k-packed (wgrad.hip): the routed rows' [dA dB] and w H (kp:
+    // padded row prefix of the experts), the shared [dA dB]; mode 5 reads [dA dB]
     uint16_t* pt_dab_r;
     uint16_t* pt_wh_r;
     uint16_t* pt_dab_s;
@@ -582,8 +580,10 @@ gemm_bf16_pk_kernel(GemmArgs p) {
         } else if constexpr (MODE == 5) {  // dX = [dA dB] W13: contraction over 2 inter
             K = 2 * (shared ? p.shared_inter : p.inter);
             n_out = p.d;
-            Abase = shared ? static_cast<const uint16_t*>(p.dab_s) : static_cast<const uint16_t*>(p.dab_r);
-            a_rows = shared ? p.T : p.T * p.k;
+            // the group's k-packed rows (K columns: a multiple of 32)
+            const int64_t kp0 = shared ? 0 : p.kp[t.g];
+            a_rows = shared ? ceil_div(p.T, 16) * 16 : p.kp[t.g + 1] - kp0;
+            Abase = (shared ? p.pt_dab_s : p.pt_dab_r) + kp0 * K;
             Wr = static_cast<const uint16_t*>(p.w13t);
             Ws = static_cast<const uint16_t*>(p.ws13t);
         } else {
@@ -611,10 +611,19 @@ gemm_bf16_pk_kernel(GemmArgs p) {
     // lane moves the 16-byte chunk (lane % 8) ^ swizzle(row) of its row into slot lane % 8.
     // aoff: element offset of the row start; rows past the tile get 2^30, whose
     // byte offset (>= 2^31) is out of range: zero fill without memory traffic.
+    // Mode 5: instruction q of wave w brings the k-packed block of 16-row slice 2 w + q / 2 and
+    // 32-column group q % 2 of the stage, 1 KB; the two row halves' 16-byte chunks are XORed with
+    // 0 and 4, so that a transposing read (below) spreads over the banks.
+    const int a_ks = MODE == 5 ? uniform_int(static_cast<int>(a_rows / 16)) : 0;  // 16-row slices of the group
+    const int a_ks0 = MODE == 5 ? uniform_int(static_cast<int>(t.row0 - (shared ? 0 : p.off[t.g])) / 16) : 0;
     uint32_t aoff[IA];
     int achk[IA];
 #pragma unroll
     for (int q = 0; q < IA; ++q) {
+        if constexpr (MODE == 5) {
+            aoff[q] = achk[q] = 0;
+            continue;
+        }
         const int R = (wave * IA + q) * 8 + lane / 8;
         const int rr = R < t.rows ? R : 0;
         int src;
@@ -624,12 +633,24 @@ gemm_bf16_pk_kernel(GemmArgs p) {
         achk[q] = ((lane % 8) ^ ((R / 2) % 8)) * 8;
     }
     // One A DMA instruction (rows (wave * IA + q) * 8 ..) of stage s into ring slot `slot`.
+    // (Mode 5 issues it as inline assembly: before a transposing read the compiler would wait for
+    // every load in flight that it knows to write LDS: 966 -> 1542 us for the routed dX.)
+    const i32x4_t rs5 = buf_rsrc(Abase, static_cast<int>(a_rows * K * 2));
+    const uint32_t lds_base = lds_address(lds);
     auto issue_aq = [&](int slot, int s, int q) {
-        const int k = s * BK + achk[q];
-        const int vo = static_cast<int>(((aoff[q] + static_cast<uint32_t>(k)) * 2u) |
-                                        (k < K ? 0u : static_cast<uint32_t>(kOutOfRange)));
-        auto* dst = (__attribute__((address_space(3))) void*)(lds + slot * A_BYTES + (wave * IA + q) * 1024);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, dst, 16, vo, 0, 0, 0);
+        if constexpr (MODE == 5) {
+            const int cg = 2 * s + (q & 1), ks = a_ks0 + 2 * wave + (q >> 1);
+            const int so = cg < kc_n && ks < a_ks ? (cg * a_ks + ks) * 1024 : kOutOfRange;
+            const int vo = static_cast<int>(static_cast<uint32_t>(so) +
+                                            static_cast<uint32_t>((lane ^ ((lane & 32) >> 3)) * 16));
+            dma16(rs5, vo, lds_base + static_cast<uint32_t>(slot * A_BYTES + (wave * IA + q) * 1024));
+        } else {
+            const int k = s * BK + achk[q];
+            const int vo = static_cast<int>(((aoff[q] + static_cast<uint32_t>(k)) * 2u) |
+                                            (k < K ? 0u : static_cast<uint32_t>(kOutOfRange)));
+            auto* dst = (__attribute__((address_space(3))) void*)(lds + slot * A_BYTES + (wave * IA + q) * 1024);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, dst, 16, vo, 0, 0, 0);
+        }
     };
     // Weight fragments of stage s: b[j][h] is 16-row group h of K slice 32 (2 s + j).
     // Quarter q of a stage loads groups 2 (q % 2) and 2 (q % 2) + 1 of slice q / 2.
@@ -650,6 +671,9 @@ gemm_bf16_pk_kernel(GemmArgs p) {
 #pragma unroll
         for (int h = 0; h < 4; ++h) acc[i][h] = f32x4_t{};
     const int quad = lane >> 4, l16 = lane & 15;
+    // mode 5's transposing reads: lane j of a 16-lane group supplies the address of column 8 quad +
+    // j / 4 (+ 4 in the second read: the chunk's bit 2), rows 4 (j % 4) .. and receives row j
+    const int tr0 = ((((l16 & 3) >> 1) * 32 + 8 * quad + (l16 >> 2)) ^ (((l16 & 3) >> 1) * 4)) * 16 + (l16 & 1) * 8;
 
     // Stage s from ring slot `slot` with weight registers bc, while the loads of
     // the next stages go out between the MFMAs. A stage (K = 64) runs in four
@@ -667,13 +691,23 @@ gemm_bf16_pk_kernel(GemmArgs p) {
         const uint8_t* base = lds + slot * A_BYTES;
         const int nslot = slot == 0 ? 2 : slot - 1;  // (slot + 2) % 3
         bf16x8_t af[2][4];
+        int tr = tr0;
+        if constexpr (MODE == 5) asm volatile("" : "+v"(tr));  // rebuilt per stage: its sums would not fit the registers
         // token fragment of tile 2 u + q % 2, K slice q / 2: row 16 i + l % 16, k 32 j + 8 (l / 16) ..
         auto rd = [&](int q, bf16x8_t (&a)[4]) {
             const int c = (q >> 1) * 4 + quad;
 #pragma unroll
             for (int u = 0; u < MT; ++u) {
-                const int R = (2 * u + (q & 1)) * 16 + l16;
-                a[u] = *reinterpret_cast<const bf16x8_t*>(base + R * (BK * 2) + ((c ^ ((R / 2) % 8)) * 16));
+                if constexpr (MODE == 5) {
+                    const uint8_t* a0 = base + ((2 * u + (q & 1)) * 2 + (q >> 1)) * 1024;
+                    const v4i16_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_t*)(a0 + tr));
+                    const v4i16_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_t*)(a0 + (tr ^ 64)));
+                    const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
+                    a[u] = __builtin_bit_cast(bf16x8_t, make_uint4(l2.x, l2.y, h2.x, h2.y));
+                } else {
+                    const int R = (2 * u + (q & 1)) * 16 + l16;
+                    a[u] = *reinterpret_cast<const bf16x8_t*>(base + R * (BK * 2) + ((c ^ ((R / 2) % 8)) * 16));
+                }
             }
         };
         rd(0, af[0]);
@@ -700,7 +734,7 @@ gemm_bf16_pk_kernel(GemmArgs p) {
 #pragma unroll
             for (int v = 0; v < MT; ++v) {
                 if (3 + v < NM) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, MODE == 5 ? 2 : 1, 0);
             }
             if (NM > 3 + MT) __builtin_amdgcn_sched_group_barrier(0x008, NM - 3 - MT, 0);
         }
@@ -765,14 +799,14 @@ gemm_bf16_pk_kernel(GemmArgs p) {
         // plus w H = w silu(a) b for the dW2 product (routed rows). In four
         // passes of 32 rows: the rows' a | b slices come into LDS as whole
         // rows, each lane turns its four adjacent columns into dA | dB | w H
-        // in place; dA and dB go out as whole rows (the dX GEMM's operand), and
-        // all three (w H for routed rows only) k-packed for the weight
-        // gradients: 16 rows x 32 columns per 1 KB, a lane's eight rows of one
-        // column by two transposing LDS reads. (As passes of their own the
-        // three k-packs read the rows back: at 16384 tokens, d 2048, 64 experts
-        // top-6 of 1408 and two shared ones 118 + 198 + 57 us.)
+        // in place, and the three go out (w H for routed rows only) k-packed for
+        // the weight gradients and the dX GEMM: 16 rows x 32 columns per 1 KB, a
+        // lane's eight rows of one column by two transposing LDS reads. (As
+        // passes of their own three k-packs read the rows back: at 16384 tokens,
+        // d 2048, 64 experts top-6 of 1408 and two shared ones 118 + 198 + 57 us;
+        // [dA dB] stored as rows too, for the dX GEMM, 919 + 296 us for the routed
+        // and the shared launch, without 812 + 260.)
         const uint16_t* AB = static_cast<const uint16_t*>(shared ? p.ab_s : p.ab_r);
-        uint16_t* dAB = static_cast<uint16_t*>(shared ? p.dab_s : p.dab_r);
         const int64_t kp0 = shared ? 0 : p.kp[t.g];
         const int64_t Ks = shared ? ceil_div(p.T, 16) : (p.kp[t.g + 1] - kp0) / 16;
         const int64_t ks0 = (t.row0 - (shared ? 0 : p.off[t.g])) / 16;  // the tile's first 16-row slice of its group
@@ -844,13 +878,6 @@ gemm_bf16_pk_kernel(GemmArgs p) {
                 }
             }
             __syncthreads();
-            for (int q = threadIdx.x; q < 32 * (2 * TC / 8); q += PK_THREADS) {
-                const int r = q / (2 * TC / 8), ch = q % (2 * TC / 8);
-                const int part = ch / (TC / 8), c = (ch % (TC / 8)) * 8;
-                if (r < rows_here && c < ncols)
-                    *reinterpret_cast<uint4*>(dAB + (rbase + r) * ld + part * n_out + col0 + c) =
-                        *reinterpret_cast<const uint4*>(el + r * EP + part * TC + c);
-            }
             // k-packed: lane l takes column 32 f + l % 32 of the wave's 64 and rows 8 (l / 32) .. + 7
             // of slice tt; in each 16-lane group lane j supplies the address of row j / 4, columns
             // 4 (j % 4) .. and receives column j of four rows. Rows past the group are zero here
@@ -1618,7 +1645,7 @@ GemmArgs make_args(const ExpertArgs& a, const ExpWs& w, const int32_t* work, int
     g.w2t = g.ws2t = g.w13t = g.ws13t = nullptr;
     g.ab_r = a.ab_r;
     g.ab_s = a.ab_s;
-    g.dab_r = g.dab_s = g.dx_r = g.dx_s = nullptr;
+    g.dx_r = g.dx_s = nullptr;
     g.wrow = nullptr;
     g.pt_dab_r = g.pt_dab_s = g.pt_wh_r = nullptr;
     g.kp = nullptr;
@@ -1858,8 +1885,6 @@ hipError_t launch_bwd_gemm(int mode, const ExpertArgs& a, void* fwd_ws, const Bw
     g.ws13t = bp.ws13t;
     g.ab_r = bp.ab_r;
     g.ab_s = bp.ab_s;
-    g.dab_r = bp.dab_r;
-    g.dab_s = bp.dab_s;
     g.dx_r = bp.dx_r;
     g.dx_s = bp.dx_s;
     g.wrow = bp.wrow;

@@ -114,8 +114,6 @@ struct BwdGemmPtrs {
     const void* ws13t;
     void* ab_r;         // [R][2 inter]
     void* ab_s;         // [T][2 shared_inter]
-    void* dab_r;
-    void* dab_s;
     void* dx_r;         // [R][d]
     void* dx_s;         // [T][d]
     const float* wrow;  // [R]
@@ -126,7 +124,7 @@ struct BwdGemmPtrs {
     int32_t* work4;     // [E + 2] table of mode 4
 };
 // mode 3: recomputed gate/up pre-activations; 4: dH = w dout W2 with the SwiGLU
-// backward -> [dA dB] (as rows and k-packed, with w H for routed rows); 5: dX = [dA dB] W13. part: 1
+// backward -> [dA dB] (k-packed, with w H for routed rows); 5: dX = [dA dB] W13. part: 1
 // routed, 2 shared.
 hipError_t launch_bwd_gemm(int mode, const ExpertArgs& a, void* fwd_ws, const BwdGemmPtrs& bp, int part,
                            hipStream_t stream);
