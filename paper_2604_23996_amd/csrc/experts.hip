@@ -1056,49 +1056,97 @@ gemm_bf16_pk_kernel(GemmArgs p) {
     }
 }
 
-// Pack `batch` row-major matrices into the fragment order above. interleave:
-// the source has 2 * n rows (gate rows then up rows) and 16-row group 4q + 2v
-// + h takes rows 32q + 16v.. of half h; otherwise the source has n rows.
-// transpose: the source is stored [k][n] (the packed matrix is its
-// transpose). One thread per 16-byte fragment; k % 8 == 0.
-__global__ void pack_weights_kernel(const uint16_t* __restrict__ src, int batch, int n, int k, int interleave,
-                                    int transpose, uint16_t* __restrict__ dst) {
-    const int ng = static_cast<int>((interleave ? 4 : 2) * ceil_div(n, 32));  // 16-row groups
+// Pack `batch` row-major matrices into the fragment order above; k % 8 == 0.
+// interleave: the source has 2 * n rows (gate rows then up rows) and 16-row
+// group 4q + 2v + h takes rows 32q + 16v.. of half h; otherwise the source has
+// n rows. One block per 16-row group and kPackCols columns: whole row pieces of 1
+// KB come in, and the fragments go out of LDS, 1 KB each. (One thread per
+// fragment, 64 bytes of each of 16 rows per wave load: 278 us for 64 gate / up
+// matrices of 2816 x 2048, now 246, 6 TB/s.)
+constexpr int kPackCols = 512;
+constexpr int64_t kPackBlocks = 1 << 22;  // a launch holds fewer than 2^32 threads
+__global__ void __launch_bounds__(256)
+pack_rows_kernel(const uint16_t* __restrict__ src, unsigned items, int n, int k, int interleave,
+                 uint16_t* __restrict__ dst) {
+    __shared__ __attribute__((aligned(16))) uint16_t tile[16][kPackCols + 8];  // row pitch = 4 mod 64 dwords
+    const int ng = (interleave ? 4 : 2) * ((n + 31) / 32);  // 16-row groups
     const int kc_n = (k + 31) / 32;
-    const int64_t per = static_cast<int64_t>(ng) * kc_n * 64;  // fragments per matrix
-    const int64_t total = per * batch;
-    const int64_t src_rows = interleave ? 2 * static_cast<int64_t>(n) : n;
-    for (int64_t f = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; f < total;
-         f += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-        const int64_t b = f / per;
-        const int64_t r = f % per;
-        const int l = static_cast<int>(r % 64);
-        const int c = static_cast<int>((r / 64) % kc_n);
-        const int g = static_cast<int>(r / (64 * kc_n));
-        int row;
-        bool ok;
-        if (interleave) {
-            const int q = g / 4, v = (g / 2) % 2, h = g % 2;
-            const int rr = q * 32 + v * 16 + l % 16;
-            ok = rr < n;
-            row = h * n + rr;
-        } else {
-            row = g * 16 + l % 16;
-            ok = row < n;
-        }
-        const int kk = c * 32 + 8 * (l / 16);
-        ok = ok && kk < k;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (ok && transpose) {
-            uint16_t e8[8];
+    const int nc = (k + kPackCols - 1) / kPackCols;
+    for (unsigned item = blockIdx.x; item < items; item += gridDim.x) {  // one each below kPackBlocks
+        const unsigned bg = item / nc;  // (matrix, group)
+        const int c0 = static_cast<int>(item % nc) * kPackCols;
+        const int64_t b = bg / ng;
+        const int g = static_cast<int>(bg % ng);
+        const int wave = threadIdx.x / kWave, lane = lane_id();
+        const int64_t src_rows = interleave ? 2 * static_cast<int64_t>(n) : n;
+        const int r0 = interleave ? (g / 4) * 32 + ((g / 2) % 2) * 16 : g * 16;  // of the half
+        const int base = interleave ? (g % 2) * n : 0;
+        const int col = c0 + lane * 8;
+        uint4 v[4];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) e8[e] = src[(b * k + kk + e) * static_cast<int64_t>(n) + row];
-            v = make_uint4(e8[0] | (static_cast<uint32_t>(e8[1]) << 16), e8[2] | (static_cast<uint32_t>(e8[3]) << 16),
-                           e8[4] | (static_cast<uint32_t>(e8[5]) << 16), e8[6] | (static_cast<uint32_t>(e8[7]) << 16));
-        } else if (ok) {
-            v = *reinterpret_cast<const uint4*>(src + (b * src_rows + row) * k + kk);
+        for (int i = 0; i < 4; ++i) {
+            const int r = r0 + wave * 4 + i;
+            v[i] = r < n && col < k ? *reinterpret_cast<const uint4*>(src + (b * src_rows + base + r) * k + col)
+                                    : make_uint4(0, 0, 0, 0);
         }
-        *reinterpret_cast<uint4*>(dst + f * 8) = v;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *reinterpret_cast<uint4*>(&tile[wave * 4 + i][lane * 8]) = v[i];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kPackCols / 32 / 4; ++i) {
+            const int c = wave * (kPackCols / 32 / 4) + i;  // 32-column slice of the block
+            if (c0 / 32 + c >= kc_n) break;
+            *reinterpret_cast<uint4*>(dst + ((static_cast<int64_t>(bg) * kc_n + c0 / 32 + c) * 64 + lane) * 8) =
+                *reinterpret_cast<const uint4*>(&tile[lane % 16][32 * c + 8 * (lane / 16)]);
+        }
+        __syncthreads();  // the tile is read before the next item is written
+    }
+}
+
+// The same for matrices stored [k][n] (the packed matrix is the transpose), not
+// interleaved; n % 8 == 0. One block per 32-row slice and kPackCols source
+// columns: 1 KB row pieces come in, a fragment is two transposing LDS reads of
+// four rows of 16 columns per 16 lanes. (One thread per fragment, eight 2-byte
+// loads down a column: 502 us for the 64 matrices of 2816 x 2048 above, now
+// 246.)
+__global__ void __launch_bounds__(256)
+pack_cols_kernel(const uint16_t* __restrict__ src, unsigned items, int n, int k, uint16_t* __restrict__ dst) {
+    typedef uint32_t v4_t __attribute__((ext_vector_type(4), aligned(2)));  // the source may start at any element
+    constexpr int P = kPackCols + 16;  // row pitch = 8 mod 64 dwords
+    __shared__ __attribute__((aligned(16))) uint16_t tile[32 * P];
+    const int ng = 2 * ((n + 31) / 32);  // 16-column groups
+    const int kc_n = (k + 31) / 32;
+    const int nc = (n + kPackCols - 1) / kPackCols;
+    const int wave = threadIdx.x / kWave, lane = lane_id();
+    for (unsigned item = blockIdx.x; item < items; item += gridDim.x) {  // one each below kPackBlocks
+        const int c = static_cast<int>(item % kc_n);  // slice
+        const int64_t b = item / kc_n / nc;
+        const int n0 = static_cast<int>(item / kc_n % nc) * kPackCols;
+        const int col = n0 + lane * 8;
+        v4_t v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int kk = c * 32 + wave * 8 + i;
+            v[i] = kk < k && col < n ? *reinterpret_cast<const v4_t*>(src + (b * k + kk) * n + col) : v4_t{};
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            *reinterpret_cast<uint4*>(tile + (wave * 8 + i) * P + lane * 8) = make_uint4(v[i].x, v[i].y, v[i].z, v[i].w);
+        __syncthreads();
+        // lane j of a 16-lane group supplies the address of row j / 4, columns 4 (j % 4) .. and
+        // receives column j of four rows: rows 8 (lane / 16) .. + 3, then + 4 .. + 7
+        const uint16_t* t0 = tile + (8 * (lane >> 4) + ((lane & 15) >> 2)) * P + 4 * (lane & 3);
+#pragma unroll
+        for (int i = 0; i < kPackCols / 16 / 4; ++i) {
+            const int f = wave * (kPackCols / 16 / 4) + i, g = n0 / 16 + f;
+            if (g >= ng) break;  // uniform
+            const v4i16_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_t*)(t0 + 16 * f));
+            const v4i16_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_t*)(t0 + 16 * f + 4 * P));
+            const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
+            *reinterpret_cast<uint4*>(dst + (((b * ng + g) * kc_n + c) * 64 + lane) * 8) =
+                make_uint4(l2.x, l2.y, h2.x, h2.y);
+        }
+        __syncthreads();  // the tile is read before the next item is written
     }
 }
 
@@ -1970,9 +2018,15 @@ hipError_t launch_pack_weights(const void* src, int batch, int n, int k, int int
                                hipStream_t stream) {
     const int64_t frags = packed_weight_elems(batch, n, k, interleave) / 8;
     if (frags == 0) return hipSuccess;
-    const unsigned blocks = static_cast<unsigned>(ceil_div(frags, 256) < 65536 ? ceil_div(frags, 256) : 65536);
-    hipLaunchKernelGGL(pack_weights_kernel, dim3(blocks), dim3(256), 0, stream, static_cast<const uint16_t*>(src),
-                       batch, n, k, interleave, transpose, static_cast<uint16_t*>(dst));
+    const int64_t items = transpose ? static_cast<int64_t>(batch) * ((k + 31) / 32) * ceil_div(n, kPackCols)
+                                    : batch * (interleave ? 4 : 2) * ceil_div(n, 32) * ceil_div(k, kPackCols);
+    const unsigned blocks = static_cast<unsigned>(items < kPackBlocks ? items : kPackBlocks);
+    if (transpose)
+        hipLaunchKernelGGL(pack_cols_kernel, dim3(blocks), dim3(256), 0, stream, static_cast<const uint16_t*>(src),
+                           static_cast<unsigned>(items), n, k, static_cast<uint16_t*>(dst));
+    else
+        hipLaunchKernelGGL(pack_rows_kernel, dim3(blocks), dim3(256), 0, stream, static_cast<const uint16_t*>(src),
+                           static_cast<unsigned>(items), n, k, interleave, static_cast<uint16_t*>(dst));
     return hipGetLastError();
 }
 
