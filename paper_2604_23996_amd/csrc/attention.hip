@@ -43,7 +43,7 @@ typedef __attribute__((address_space(3))) at_v4i16 at_lds_v4i16;
 
 // Start of the sample that holds token q: offsets[s] for the largest s < n_batch
 // with offsets[s] <= q.
-__device__ __forceinline__ int sample_start(const int32_t* __restrict__ offsets, int n_batch, int q) {
+__device__ __forceinline__ int sample_start(const int32_t* offsets, int n_batch, int q) {
     int lo = 0, hi = n_batch - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -62,8 +62,11 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
 
 // DMA: K and V start on 16-byte boundaries, as the buffer-to-LDS loads want them;
 // at any other start the rows go through registers (not pipelined: correct, slower).
+// Heads of 64 fit three waves per SIMD (with the order below 96 -> 77 us for 7000
+// tokens in five samples, 32 heads over 8).
 template <int DH, bool DMA>
-__global__ void __launch_bounds__(AT_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
+__global__ void __launch_bounds__(AT_THREADS)
+__attribute__((amdgpu_waves_per_eu(DH == 128 ? 2 : 3, DH == 128 ? 2 : 3)))
 attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                 int64_t T, int H, int Hkv, const int32_t* __restrict__ offsets, int n_batch,
                 const float* __restrict__ m_in, float scale_log2, uint16_t* __restrict__ o,
@@ -86,27 +89,56 @@ attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, 
     constexpr int NI = AT_BK / RPI / (AT_THREADS / kWave);  // load instructions per wave, K and V each
     __shared__ __attribute__((aligned(1024))) uint8_t kv_lds[2][2 * KV_BYTES];
     __shared__ __attribute__((aligned(16))) float mv_lds[2][4 * AT_MP];
+    __shared__ int off_s[AT_THREADS], key_s[AT_THREADS], order_s[AT_THREADS];
 
     const int nqb = static_cast<int>(ceil_div(T, AT_BQ));
-    // Heads run fastest and the query blocks from the last one down, so the
-    // blocks that start last are the shortest causal ranges of the first sample
-    // and the launch ends evenly. Block b runs on XCD b % 8: a multiple of eight
+    // Heads run fastest; block b runs on XCD b % 8: a multiple of eight
     // heads is dealt so that an XCD gets adjacent heads, which share KV heads.
     const int hi = static_cast<int>(blockIdx.x) % H;
     const int hq = H % 8 == 0 ? (hi % 8) * (H / 8) + hi / 8 : hi;
-    const int qb = nqb - 1 - static_cast<int>(blockIdx.x) / H;
     const int hk = hq / (H / Hkv);
+    // Query blocks run from the last one down: the longest causal ranges of a
+    // sample first, and its blocks together, which share its K and V rows in L2.
+    // Where several samples make a few rounds of blocks (two per CU at a time),
+    // they run longest first over all samples instead, so that the launch ends
+    // evenly: every block ranks them for itself from the sample offsets in LDS,
+    // one thread per query block. Attention and update in us, from the last down
+    // / ranked: 512 blocks of 2 samples 75 / 61, 1760 of 5 130 / 123, 1024 of 4
+    // 199 / 181; but 128 blocks of 2 15.7 / 16.2 and 4096 of 16, without grouped
+    // heads, 232 / 263.
+    const bool ranked = n_batch > 1 && n_batch <= AT_THREADS && nqb <= AT_THREADS && gridDim.x > 256 && gridDim.x <= 2048;
+    int qb = static_cast<int>(blockIdx.x) / H;
+    if (ranked) {
+        const int t = threadIdx.x;
+        off_s[t] = t < n_batch ? offsets[t] : 0;
+        __syncthreads();
+        const int first = t * AT_BQ, last = first + AT_BQ < static_cast<int>(T) ? first + AT_BQ : static_cast<int>(T);
+        const int ks = min(max(sample_start(off_s, n_batch, first), 0), first);
+        const int key = (last - ks) / AT_BK * AT_THREADS + t;  // distinct; below 2^17
+        if (t < nqb) key_s[t] = key;
+        __syncthreads();
+        int rank = 0;
+        for (int j = 0; j < nqb; ++j) rank += key_s[j] > key ? 1 : 0;
+        if (t < nqb) order_s[rank] = t;
+        __syncthreads();
+        qb = __builtin_amdgcn_readfirstlane(order_s[qb]);
+    } else {
+        qb = nqb - 1 - qb;
+    }
+    auto start_of = [&](int row) {
+        return ranked ? sample_start(off_s, n_batch, row) : sample_start(offsets, n_batch, row);
+    };
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave), lane = lane_id();
     const int half = lane >> 5, l32 = lane & 31;
     const int Ti = static_cast<int>(T);
     const int row0 = qb * AT_BQ;
     // first key any row of the block may see (clamped so that malformed offsets cannot run the loop away)
-    const int kstart = min(max(sample_start(offsets, n_batch, row0), 0), row0);
+    const int kstart = min(max(start_of(row0), 0), row0);
     const int kend = min(row0 + AT_BQ, Ti);
     const int qi = row0 + wave * 32 + l32;
     const bool q_ok = qi < Ti;
     const int qe = q_ok ? qi : Ti - 1;
-    const int qstart = min(max(sample_start(offsets, n_batch, qe), 0), qe);
+    const int qstart = min(max(start_of(qe), 0), qe);
     const int wq0 = row0 + wave * 32;  // first query row of this wave
     // swizzle of a K row's and a V row's chunks
     auto k_swz = [](int key) { return DH == 128 ? key & 15 : (key >> 1) & 7; };

@@ -70,6 +70,16 @@ def test_attention_keys_at_any_element(dh):
     assert np.array_equal(o, host(o2)) and np.array_equal(mh, host(mh2))
 
 
+@pytest.mark.parametrize("dh,H", [(128, 11), (64, 23), (64, 24)])
+def test_attention_blocks_longest_first(dh, H):
+    # 24 query blocks of unequal samples (one empty, one of a token): 264 blocks run in order
+    # of their ranges over all samples, 552 and 576 as well; ties keep every query block once
+    a = W.make_attention_inputs(((300, 213), (0, 0), (1, 0), (900, 636), (512, 480)), 64, H, H, dh, seed=dh + H)
+    say("attention longest first", dh, H, a.T)
+    o, mh = _run_attention(a)
+    _check_attention(a, o, mh)
+
+
 def test_attention_explicit_scale_and_flat_logits():
     samples = ((100, 60),)
     a = W.make_attention_inputs(samples, 64, 2, 2, 128, seed=5, logit_std=0.05)
