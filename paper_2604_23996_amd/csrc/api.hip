@@ -583,7 +583,7 @@ size_t bwd_ws_parts(const smoes_layer* L, BwdWs* out, void* base) {
     Carver c(base);
     const int64_t T = L->T, R = L->T * L->k;
     const bool gen = generic_bwd(L);
-    // intermediates: bf16 on the packed matrix-core path, float32 on the FMA path
+    // intermediates: bf16 on the packed matrix-core path, float32 on the row-major path
     const size_t es = gen ? sizeof(float) : sizeof(uint16_t);
     BwdWs w;
     // the pre-activations are recomputed here unless the forward kept them
@@ -692,7 +692,7 @@ int smoes_moe_backward(const smoes_layer* L, const smoes_layer_io* io, const voi
     } while (0)
     const int bf16 = L->act_dtype == SMOES_BF16 ? 1 : 0;
     if (gen) {
-        // float32 FMA path, every step on s: router backward and dW_gate, then
+        // row-major path, every step on s: router backward and dW_gate, then
         // the experts (routed and shared in each launch), then the input gradient
         GenericBwdPtrs gp;
         gp.dout = dout;

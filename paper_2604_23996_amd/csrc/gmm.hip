@@ -35,7 +35,11 @@ constexpr int kGPrepThreads = 256;  // columns per gmm_prep block
 constexpr int kGMergeCols = 64;     // columns per gmm_merge block
 constexpr int kGMergeGroups = 8;    // chunk groups per column
 constexpr int kGMaxParts = 256;     // SMOES_D_MAX / kGMergeCols: parts of a log-variance sum
+// tokens per gmm_loglik wave: 4, or 1 where those would not give every CU a
+// block: a wave's chain of columns is then shorter (score of 2 tokens x 2048, K = 3:
+// 31.1 -> 20.8 us, with the weights and log-variances loaded after the columns)
 constexpr int kGTokPerWave = 4;
+constexpr int64_t kGTokFill = 256 * 4 * kGTokPerWave;
 constexpr int kGThreads = 256;
 // columns per lane of gmm_partial: 4, or 2 where the sums of 3 or 4 components would not leave four waves a SIMD
 constexpr int gmm_part_cols(int K) { return K <= 2 ? 4 : 2; }
@@ -106,14 +110,13 @@ gmm_prep_kernel(int d, int K, const float* __restrict__ gn, const float* __restr
 }
 
 // mode 0: scores M[T][2]; mode 1: responsibilities resp[T][K] of each token's own modality.
-template <bool BF16, int K>
+template <bool BF16, int K, int NT>
 __global__ void __launch_bounds__(kGThreads)
 gmm_loglik_kernel(const void* __restrict__ x, int64_t T, int d, const uint8_t* __restrict__ mid,
                   const float* __restrict__ coef, const double* __restrict__ cst, int n_part,
                   const float* __restrict__ gn, double inv_tau, int mode, float* __restrict__ M,
                   float* __restrict__ resp) {
     constexpr int MC = 2 * K;
-    constexpr int NT = kGTokPerWave;
     __shared__ double q_s[kGThreads / kWave][NT][MC];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int lane = lane_id();
@@ -122,33 +125,21 @@ gmm_loglik_kernel(const void* __restrict__ x, int64_t T, int d, const uint8_t* _
     int64_t rows[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) rows[t] = tok0 + t < T ? tok0 + t : T - 1;
-    // lane j < MC: -2 log pi_mc, pi_mc = N_mc / sum_c N_mc (uniform when the modality has no count)
-    double lp = 0.0;
-    if (lane < MC) {
-        double tot = 0.0;
-#pragma unroll
-        for (int c = 0; c < K; ++c) tot += static_cast<double>(gn[lane / K * K + c]);
-        lp = -2.0 * (tot > 0.0 ? log(static_cast<double>(gn[lane]) / tot) : -log(static_cast<double>(K)));
-    }
-    // a lane's partial sums start from its parts of sum log sigma^2 - 2 log pi
     double acc[NT][MC];
 #pragma unroll
-    for (int j = 0; j < MC; ++j) {
-        double slv = lane == j ? lp : 0.0;
-        for (int b = lane; b < n_part; b += kWave) slv += cst[j * kGMaxParts + b];
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int t = 0; t < NT; ++t) acc[t][j] = slv;
-    }
+        for (int j = 0; j < MC; ++j) acc[t][j] = 0.0;
     // the rows' next S stripes of 512 columns (8 per lane) are loaded before any is used
     constexpr int S = BF16 ? 4 : 2;
     constexpr int Q = BF16 ? 1 : 2;
     for (int g = lane * 8; g < d; g += S * kWave * 8) {
-        uint4 raw[kGTokPerWave][S][Q];
+        uint4 raw[NT][S][Q];
 #pragma unroll
         for (int s = 0; s < S; ++s) {
             const int c0 = g + s * kWave * 8 < d ? g + s * kWave * 8 : 0;
 #pragma unroll
-            for (int t = 0; t < kGTokPerWave; ++t) {
+            for (int t = 0; t < NT; ++t) {
                 const int64_t e = rows[t] * d + c0;
                 const uint4* q = BF16 ? reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(x) + e)
                                       : reinterpret_cast<const uint4*>(static_cast<const float*>(x) + e);
@@ -160,9 +151,9 @@ gmm_loglik_kernel(const void* __restrict__ x, int64_t T, int d, const uint8_t* _
       for (int s = 0; s < S; ++s) {
         const int c0 = g + s * kWave * 8;
         if (c0 >= d) break;
-        float v[kGTokPerWave][8];
+        float v[NT][8];
 #pragma unroll
-        for (int t = 0; t < kGTokPerWave; ++t) {
+        for (int t = 0; t < NT; ++t) {
             const uint32_t* w = reinterpret_cast<const uint32_t*>(&raw[t][s][0]);
 #pragma unroll
             for (int i = 0; i < 8; ++i)
@@ -178,7 +169,7 @@ gmm_loglik_kernel(const void* __restrict__ x, int64_t T, int d, const uint8_t* _
             *reinterpret_cast<float4*>(&iv[0]) = pi[0];
             *reinterpret_cast<float4*>(&iv[4]) = pi[1];
 #pragma unroll
-            for (int t = 0; t < kGTokPerWave; ++t) {
+            for (int t = 0; t < NT; ++t) {
                 float part = 0.0f;
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
@@ -189,6 +180,23 @@ gmm_loglik_kernel(const void* __restrict__ x, int64_t T, int d, const uint8_t* _
             }
         }
       }
+    }
+    // lane j < MC: -2 log pi_mc, pi_mc = N_mc / sum_c N_mc (uniform when the modality has no count)
+    double lp = 0.0;
+    if (lane < MC) {
+        double tot = 0.0;
+#pragma unroll
+        for (int c = 0; c < K; ++c) tot += static_cast<double>(gn[lane / K * K + c]);
+        lp = -2.0 * (tot > 0.0 ? log(static_cast<double>(gn[lane]) / tot) : -log(static_cast<double>(K)));
+    }
+    // a lane's partial sums take its parts of sum log sigma^2 - 2 log pi, after the columns: before
+    // them a short call would wait for these loads first
+#pragma unroll
+    for (int j = 0; j < MC; ++j) {
+        double slv = lane == j ? lp : 0.0;
+        for (int b = lane; b < n_part; b += kWave) slv += cst[j * kGMaxParts + b];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t][j] += slv;
     }
     // lane partials -> per (token, component) sums by a fixed butterfly; then one
     // lane per token of the block turns them into its result (the float64
@@ -482,15 +490,16 @@ hipError_t gmm_run(const void* x, int64_t T, int d, const uint8_t* mid, float* g
     hipError_t err;
     int n_part = static_cast<int>(ceil_div(d, kGPrepThreads));
     const dim3 pgrid(static_cast<unsigned>(n_part), 2 * K);
-    const int64_t tok_per_block = static_cast<int64_t>(kGThreads / kWave) * kGTokPerWave;
-    const dim3 lgrid(static_cast<unsigned>(ceil_div(T, tok_per_block)));
+    const int nt = T >= kGTokFill ? kGTokPerWave : 1;
+    const auto loglik = nt == 1 ? gmm_loglik_kernel<BF16, K, 1> : gmm_loglik_kernel<BF16, K, kGTokPerWave>;
+    const dim3 lgrid(static_cast<unsigned>(ceil_div(T, kGThreads / kWave * nt)));
     const double t = tau > 0.0f ? static_cast<double>(tau) : 0.5 * d;
     float* resp = resp_out != nullptr ? resp_out : w.resp;
     if (update || resp_out != nullptr) {
         hipLaunchKernelGGL(gmm_prep_kernel, pgrid, dim3(kGPrepThreads), 0, stream, d, K, gn, gsmu, gssig,
                            var_floor, w.coef, w.cst);
         if ((err = hipGetLastError()) != hipSuccess) return err;
-        hipLaunchKernelGGL((gmm_loglik_kernel<BF16, K>), lgrid, dim3(kGThreads), 0, stream, x, T, d, mid, w.coef,
+        hipLaunchKernelGGL(loglik, lgrid, dim3(kGThreads), 0, stream, x, T, d, mid, w.coef,
                            w.cst, n_part, gn, 1.0 / t, 1, M, resp);
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }
@@ -510,7 +519,7 @@ hipError_t gmm_run(const void* x, int64_t T, int d, const uint8_t* mid, float* g
                            w.coef, w.cst);
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }
-    hipLaunchKernelGGL((gmm_loglik_kernel<BF16, K>), lgrid, dim3(kGThreads), 0, stream, x, T, d, mid, w.coef, w.cst,
+    hipLaunchKernelGGL(loglik, lgrid, dim3(kGThreads), 0, stream, x, T, d, mid, w.coef, w.cst,
                        n_part, gn, 1.0 / t, 0, M, resp);
     return hipGetLastError();
 }

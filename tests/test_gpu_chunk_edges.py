@@ -95,6 +95,20 @@ def test_gmm_chunks(T, d, dtype, K):
     assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("K", [1, 4])
+@pytest.mark.parametrize("dtype", [W.BF16, W.F32])
+def test_gmm_score_tokens_per_wave(dtype, K):
+    # from 4096 tokens on a wave takes four tokens, below one: a token's score has the same bits
+    T, d = 4097, 72
+    say("gmm tokens per wave", dtype, K)
+    x, mid, rng = _tokens(T, d, dtype, 3 + K)
+    n, smu, ssig = (t(a) for a in W.random_gmm_state(rng, d, K, spread=0.05))
+    M, resp = S.gmm_modality_score(t(x), n, smu, ssig, t(mid), want_resp=True)
+    for cut in (1, 4095, 4096):
+        a, r = S.gmm_modality_score(t(x[:cut]), n, smu, ssig, t(mid[:cut]), want_resp=True)
+        assert torch.equal(a, M[:cut]) and torch.equal(r, resp[:cut]), cut
+
+
 @pytest.mark.parametrize("T", [32640, 32641, 32700])
 def test_combine_in_the_shared_down_gemm_from_512_tiles(T):
     # d = 264: two column tiles, so 32641 tokens are the first with 512 tiles; the
