@@ -125,11 +125,38 @@ gmm_loglik_kernel(const void* __restrict__ x, int64_t T, int d, const uint8_t* _
     int64_t rows[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) rows[t] = tok0 + t < T ? tok0 + t : T - 1;
+    // A lane's partial sums take its parts of sum log sigma^2 - 2 log pi: after the columns in a
+    // short call, which would wait for these loads first; before them in a long one, whose other
+    // waves hide that.
+    // lane j < MC: -2 log pi_mc, pi_mc = N_mc / sum_c N_mc (uniform when the modality has no count)
+    auto log_pi = [&] {
+        double lp = 0.0;
+        if (lane < MC) {
+            double tot = 0.0;
+#pragma unroll
+            for (int c = 0; c < K; ++c) tot += static_cast<double>(gn[lane / K * K + c]);
+            lp = -2.0 * (tot > 0.0 ? log(static_cast<double>(gn[lane]) / tot) : -log(static_cast<double>(K)));
+        }
+        return lp;
+    };
+    auto constant = [&](int j, double lp) {
+        double slv = lane == j ? lp : 0.0;
+        for (int b = lane; b < n_part; b += kWave) slv += cst[j * kGMaxParts + b];
+        return slv;
+    };
     double acc[NT][MC];
+    if constexpr (NT > 1) {
+        const double lp = log_pi();
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+        for (int j = 0; j < MC; ++j) {
+            const double slv = constant(j, lp);
 #pragma unroll
-        for (int j = 0; j < MC; ++j) acc[t][j] = 0.0;
+            for (int t = 0; t < NT; ++t) acc[t][j] = slv;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < MC; ++j) acc[0][j] = 0.0;
+    }
     // the rows' next S stripes of 512 columns (8 per lane) are loaded before any is used
     constexpr int S = BF16 ? 4 : 2;
     constexpr int Q = BF16 ? 1 : 2;
@@ -181,22 +208,10 @@ gmm_loglik_kernel(const void* __restrict__ x, int64_t T, int d, const uint8_t* _
         }
       }
     }
-    // lane j < MC: -2 log pi_mc, pi_mc = N_mc / sum_c N_mc (uniform when the modality has no count)
-    double lp = 0.0;
-    if (lane < MC) {
-        double tot = 0.0;
+    if constexpr (NT == 1) {
+        const double lp = log_pi();
 #pragma unroll
-        for (int c = 0; c < K; ++c) tot += static_cast<double>(gn[lane / K * K + c]);
-        lp = -2.0 * (tot > 0.0 ? log(static_cast<double>(gn[lane]) / tot) : -log(static_cast<double>(K)));
-    }
-    // a lane's partial sums take its parts of sum log sigma^2 - 2 log pi, after the columns: before
-    // them a short call would wait for these loads first
-#pragma unroll
-    for (int j = 0; j < MC; ++j) {
-        double slv = lane == j ? lp : 0.0;
-        for (int b = lane; b < n_part; b += kWave) slv += cst[j * kGMaxParts + b];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) acc[t][j] += slv;
+        for (int j = 0; j < MC; ++j) acc[0][j] += constant(j, lp);
     }
     // lane partials -> per (token, component) sums by a fixed butterfly; then one
     // lane per token of the block turns them into its result (the float64
