@@ -48,21 +48,17 @@ __host__ __device__ constexpr int router_ring(int ne) {
 }
 
 // KS ranges of the hidden dimension of `steps` 32-wide k-steps each (the last
-// may be shorter): as many workgroups as the chip holds (two per CU where two
-// rings fit its LDS: up to 64 experts), each range at least 8 k-steps. At 8000
-// x 2048, 64 experts 63 x 8 workgroups route in 24.8 us, 63 x 5 (one per CU,
-// 59 CUs with two) in 25.4; with one ring per CU twice the ranges only add
-// planes of partial sums (16384 x 4096, 160 experts: layer 4756 against 4739 us).
+// may be shorter): about one workgroup per CU, each range at least 8 k-steps.
+// The count is part of the logits' bits (the partial sums round to float32 per
+// range), so a change of it turns the choice of near-tied experts.
 struct RouterPlan {
     int ks, steps;
 };
-RouterPlan router_plan(int64_t T, int d, int E) {
+RouterPlan router_plan(int64_t T, int d) {
     RouterPlan p;
     const int64_t tiles = ceil_div(T, kLogitTokens);
     const int nsteps = static_cast<int>(ceil_div(d, 32));
-    const int ne = router_ne(E);
-    const int64_t fill = 2 * router_ring(ne) * router_slot_bytes(ne) <= 160 * 1024 ? 512 : 256;
-    int ks = static_cast<int>(ceil_div(fill, tiles > 0 ? tiles : 1));
+    int ks = static_cast<int>(ceil_div(256, tiles > 0 ? tiles : 1));
     const int ks_max = nsteps / 8 > 1 ? nsteps / 8 : 1;
     ks = ks < 1 ? 1 : (ks > ks_max ? ks_max : ks);
     p.steps = static_cast<int>(ceil_div(nsteps, ks));
@@ -505,7 +501,7 @@ hipError_t launch_router_bf16(const uint16_t* x, int64_t T, int d, const uint16_
                               int E, int k, int renorm, float* part, float* logits, float* probs,
                               int32_t* topk_idx, float* topk_w, hipStream_t stream) {
     const int E_pad = router_epad(E);
-    const RouterPlan p = router_plan(T, d, E);
+    const RouterPlan p = router_plan(T, d);
     const dim3 grid(static_cast<unsigned>(ceil_div(T, kLogitTokens)), static_cast<unsigned>(p.ks));
     const dim3 block(kLogitWaves * 64);
     switch (router_ne(E)) {
@@ -553,7 +549,7 @@ hipError_t launch_router_bf16(const uint16_t* x, int64_t T, int d, const uint16_
 size_t router_workspace_bytes(int64_t T, int d, int E, int x_dtype) {
     if (x_dtype != 1) return 0;
     const int E_pad = router_epad(E);
-    const RouterPlan p = router_plan(T, d, E);
+    const RouterPlan p = router_plan(T, d);
     return align_up(sizeof(uint16_t) * 3 * static_cast<size_t>(E_pad) * ceil_div(d, 32) * 32, 256) +
            align_up(sizeof(float) * static_cast<size_t>(p.ks) * T * E_pad, 256);
 }
