@@ -1341,6 +1341,16 @@ struct RmOperand {
     }
 };
 
+// eight bf16 with the infinities and NaN replaced by zero
+__device__ __forceinline__ uint4 rm_finite(uint4 h) {
+    auto keep = [](uint32_t w) {
+        const uint32_t hi = (w & 0x7f800000u) == 0x7f800000u ? 0u : 0xffff0000u;
+        const uint32_t lo = (w & 0x7f80u) == 0x7f80u ? 0u : 0xffffu;
+        return w & (hi | lo);
+    };
+    return make_uint4(keep(h.x), keep(h.y), keep(h.z), keep(h.w));
+}
+
 template <int MODE, bool BF16>
 __global__ void __launch_bounds__(kThreads, BF16 ? 4 : 2)
 gemm_rm_kernel(RmArgs p) {
@@ -1488,11 +1498,27 @@ gemm_rm_kernel(RmArgs p) {
     f32x16_t acc[NH];
 #pragma unroll
     for (int j = 0; j < NH; ++j) acc[j] = f32x16_t{};
-    auto compute = [&](int s) {
+    // again_c: H's infinities (and NaN) meet only the first of F's three terms
+    auto compute = [&](int s, auto again_c) {
         const uint8_t* b = lds[s % NB];
         auto frag = [&](const uint8_t* base, int R, int c) {
             return *reinterpret_cast<const uint4*>(base + R * 128 + ((c ^ (((R >> 1) ^ (R >> 4)) & 7)) * 16));
         };
+        if constexpr (decltype(again_c)::value) {
+#pragma unroll 1
+            for (int e = 0; e < 4 * 3; ++e) {
+                const int q = 2 - e % 3, c = 2 * (e / 3) + half;
+                const bf16x8_t fv = __builtin_bit_cast(bf16x8_t, frag(b + q * F_BYTES, 32 * wf + l32, c));
+#pragma unroll
+                for (int j = 0; j < NH; ++j) {
+                    const uint4 h = frag(b + 3 * F_BYTES, 32 * (NH * wh_ + j) + l32, c);
+                    const bf16x8_t hv = __builtin_bit_cast(bf16x8_t, q > 0 ? rm_finite(h) : h);
+                    acc[j] = MODE == GB_DW2 ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(hv, fv, acc[j], 0, 0, 0)
+                                            : __builtin_amdgcn_mfma_f32_32x32x16_bf16(fv, hv, acc[j], 0, 0, 0);
+                }
+            }
+            return;
+        }
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
             const int c = 2 * ks + half;
@@ -1519,7 +1545,7 @@ gemm_rm_kernel(RmArgs p) {
             }
         }
     };
-    if (nk > 0) {
+    auto kloop = [&](auto again_c) {
         // PD steps of operands are in registers or in flight: a float32 step is
         // 1024 cycles of matrix work, less than the latency of its loads, so there
         // the loads run two steps ahead of the step that is written to LDS (17.3 ->
@@ -1549,9 +1575,9 @@ gemm_rm_kernel(RmArgs p) {
                     load(rf, rh, s + 1 + PD);
                     load_tok(s + 2 + PD);
                 }
-                compute(s);
+                compute(s, again_c);
             } else {
-                compute(s);
+                compute(s, again_c);
                 if (s + 1 < nk) {
                     __syncthreads();  // every wave is done reading step s
                     store(rf, rh, s + 1);
@@ -1568,6 +1594,28 @@ gemm_rm_kernel(RmArgs p) {
             if constexpr (PD == 2) {
                 if (s + 1 < nk) step(s + 1, opf[0], oph[0]);
             }
+        }
+    };
+    if (nk > 0) kloop(std::false_type{});
+    if constexpr (OpF::PLANES == 3) {
+        // A term of F that is exactly zero (the lower ones of any value that is itself a bf16,
+        // and of one in fifty others) times an infinity of H is NaN, where the float32 product is
+        // that infinity. Such a tile is multiplied once more; every other one only looks at its sums.
+        bool nan = false;
+#pragma unroll
+        for (int j = 0; j < NH; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) nan |= acc[j][v] != acc[j][v];
+        uint32_t* vote = reinterpret_cast<uint32_t*>(lds);  // every wave is done with the last step
+        if (lane == 0) vote[wave] = 0;
+        if (nan) vote[wave] = 1;
+        __syncthreads();
+        nan = (vote[0] | vote[1] | vote[2] | vote[3]) != 0;
+        __syncthreads();
+        if (nan) {
+#pragma unroll
+            for (int j = 0; j < NH; ++j) acc[j] = f32x16_t{};
+            kloop(std::true_type{});
         }
     }
 

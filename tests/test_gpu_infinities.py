@@ -1,0 +1,62 @@
+"""Infinities where a kernel's split of an operand could turn them into
+something else: the row-major backward of bf16 layers (float32 operands in three
+bf16 terms) against the float32 layer of the same values."""
+from __future__ import annotations
+
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2604_23996_amd import smoes as S
+from paper_2604_23996_amd import workloads as W
+from tests.gpu_util import DEV, host, run_gpu_layer, say, t
+from tests.test_gpu_backward import _inputs
+
+pytestmark = pytest.mark.gpu
+
+CASE = dict(d=72, E=4, k=2, inter=256, n_shared=1, n_bins=2, samples=((100, 61),))
+INF = 0x7F80  # bf16 bits
+
+
+def _kinds(a):
+    """0 where finite, +-1 at infinities, 2 at NaN."""
+    a = host(a)
+    return np.where(np.isnan(a), 2, np.where(np.isinf(a), np.sign(a), 0)).astype(np.int8)
+
+
+def _rowmajor_grads(inp, dout, moved):
+    """Backward of the row-major layer; `moved` replaces tensors after the forward."""
+    spec, dev_in, outs, ws = run_gpu_layer(inp, keep_workspace=True, packed=False)
+    return S.moe_backward(spec, {**dev_in, **{n: t(v) for n, v in moved.items()}}, outs, ws, None, t(dout), None)
+
+
+@pytest.mark.parametrize("where", ["dout", "w13", "ws13"])
+@pytest.mark.parametrize("sign", [0, 0x8000])
+def test_rowmajor_infinities_as_in_float32(where, sign):
+    # a float32 value whose lower terms are zero times an infinity stays that infinity
+    cfg, inp, dout, _ = _inputs(CASE, 731)
+    say("row-major infinity", where, sign)
+    moved = {}
+    if where == "dout":
+        dout = dout.copy()
+        dout[7, 3] = INF | sign
+    else:  # an up projection: its pre-activations become infinite, the gate's do not
+        w = getattr(inp, where).copy()
+        if where == "w13":
+            w[:, cfg.inter + 5, 11] = INF | sign
+        else:
+            w[cfg.inter + 5, 11] = INF | sign
+        moved[where] = w
+    bf = _rowmajor_grads(inp, dout, moved)
+    wide = lambda v: W.bf16_bits_to_f32(v) if v is not None and v.dtype == np.uint16 else v
+    inp32 = dataclasses.replace(inp, cfg=dataclasses.replace(cfg, dtype=W.F32),
+                                **{n: wide(getattr(inp, n)) for n in ("x", "w13", "w2", "ws13", "ws2")})
+    f32 = _rowmajor_grads(inp32, wide(dout), {n: wide(v) for n, v in moved.items()})
+    seen = 0
+    for n in ("dx", "dw13", "dw2", "dws13", "dws2"):
+        a, b = _kinds(bf[n]), _kinds(f32[n])
+        seen += int((np.abs(b) == 1).sum())
+        assert np.array_equal(a, b), (n, int((a != b).sum()))
+    assert seen > 0
