@@ -855,7 +855,8 @@ gemm_bf16_pk_kernel(GemmArgs p) {
 #pragma unroll
             for (int tt = 0; tt < 2; ++tt) {
                 const int lr = 16 * tt + l16;  // row of the pass
-                const float w = shared ? 1.0f : (lr < rows_here ? p.wrow[rbase + lr] : 0.0f);
+                const bool in = lr < rows_here;
+                const float w = shared ? 1.0f : (in ? p.wrow[rbase + lr] : 0.0f);
                 uint16_t* er = el + lr * EP;
 #pragma unroll
                 for (int h = 0; h < 4; ++h) {
@@ -869,7 +870,7 @@ gemm_bf16_pk_kernel(GemmArgs p) {
                     float da[4], db[4], wh[4];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        const float dh = w * acc[2 * i + tt][h][e];
+                        const float dh = in ? w * acc[2 * i + tt][h][e] : 0.0f;
                         const float sg = 1.0f / (1.0f + __expf(-a[e]));
                         const float sa = a[e] * sg;  // silu(a)
                         da[e] = dh * bb[e] * (sg + sa * (1.0f - sg));
@@ -884,8 +885,9 @@ gemm_bf16_pk_kernel(GemmArgs p) {
             __syncthreads();
             // k-packed: lane l takes column 32 f + l % 32 of the wave's 64 and rows 8 (l / 32) .. + 7
             // of slice tt; in each 16-lane group lane j supplies the address of row j / 4, columns
-            // 4 (j % 4) .. and receives column j of four rows. Rows past the group are zero here
-            // (zero accumulators, a, b and w), as the padding has to be.
+            // 4 (j % 4) .. and receives column j of four rows. Rows past the group are zero here (a
+            // and b, and dh by choice: beside an infinite weight their accumulators are NaN), as
+            // the padding has to be.
             const int tr0 = (8 * (lane >> 5) + ((lane & 15) >> 2)) * EP + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
 #pragma unroll
             for (int tt = 0; tt < 2; ++tt) {

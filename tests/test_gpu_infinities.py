@@ -1,6 +1,7 @@
-"""Infinities where a kernel's split of an operand could turn them into
-something else: the row-major backward of bf16 layers (float32 operands in three
-bf16 terms) against the float32 layer of the same values."""
+"""Infinities where a kernel's padding or its split of an operand could turn
+them into something else: the row-major backward of bf16 layers (float32
+operands in three bf16 terms) against the float32 layer of the same values, and
+the k-packed padding of the packed backward."""
 from __future__ import annotations
 
 import dataclasses
@@ -60,3 +61,32 @@ def test_rowmajor_infinities_as_in_float32(where, sign):
         seen += int((np.abs(b) == 1).sum())
         assert np.array_equal(a, b), (n, int((a != b).sum()))
     assert seen > 0
+
+
+@pytest.mark.parametrize("streams", [False, True])
+def test_packed_padding_rows_stay_zero_beside_an_infinite_weight(streams):
+    # one token: 15 of the 16 rows of a k-packed slice are padding. With W2[3][5]
+    # infinite dH, dA and dB of column 5 are; their weight gradients are that
+    # infinity times x, and every other row's stay finite
+    cfg, inp, dout, _ = _inputs(dict(d=72, E=1, k=1, inter=48, n_shared=1, n_bins=1, samples=((1, 0),)), 741)
+    dout = dout.copy()
+    dout[0, 3] = 0x3F80  # 1.0
+    say("packed padding", streams)
+    w2, ws2 = inp.w2.copy(), inp.ws2.copy()
+    w2[0, 3, 5] = INF
+    ws2[3, 5] = INF
+    spec, dev_in, outs, ws = run_gpu_layer(inp, keep_workspace=True)
+    packed_t = S.pack_transposed_weights(spec, {"w13": t(inp.w13), "w2": t(w2), "ws13": t(inp.ws13), "ws2": t(ws2)})
+    st = S.Streams() if streams else None
+    g = S.moe_backward(spec, dev_in, outs, ws, packed_t, t(dout), None, streams=st)
+    torch.cuda.synchronize()
+    if st is not None:
+        st.close()
+    for n, inter in (("dw13", cfg.inter), ("dws13", cfg.shared_inter)):
+        k = _kinds(g[n]).reshape(2 * inter, cfg.d)
+        x = W.bf16_bits_to_f32(inp.x)[0]
+        assert np.all(x != 0)
+        for row in (5, inter + 5):
+            assert np.array_equal(np.abs(k[row]), np.ones(cfg.d)), (n, row)
+            assert len(set((k[row] * np.sign(x)).tolist())) == 1  # the sign of dA or dB times that of x
+        assert not np.delete(k, (5, inter + 5), axis=0).any(), n
