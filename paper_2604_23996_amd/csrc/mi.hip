@@ -286,7 +286,7 @@ __device__ __forceinline__ double mi_finalize(MiFinalLds& lds, int i, int64_t T,
     }
     // Eq. 14
     const double lr = (cell && pmk > 0.0) ? log(pmk / (pm * pk)) : 0.0;
-    const double part_I = wave_sum_u(pmk * lr);
+    const double part_I = wave_sum_u(pmk > 0.0 ? pmk * lr : 0.0);  // pmk is NaN where S-bar is infinite
     __syncthreads();  // term is read above
     if (cm < 2 && ck == 0) term[cm] = part_I;
     __syncthreads();

@@ -1,7 +1,8 @@
-"""Infinities where a kernel's padding or its split of an operand could turn
-them into something else: the row-major backward of bf16 layers (float32
-operands in three bf16 terms) against the float32 layer of the same values, and
-the k-packed padding of the packed backward."""
+"""Infinities where a kernel's padding, its split of an operand or its order of
+work could turn them into something else: the row-major backward of bf16 layers
+(float32 operands in three bf16 terms) against the float32 layer of the same
+values, the k-packed padding of the packed backward, and the MI of a sample with
+an infinite probability."""
 from __future__ import annotations
 
 import dataclasses
@@ -90,3 +91,22 @@ def test_packed_padding_rows_stay_zero_beside_an_infinite_weight(streams):
             assert np.array_equal(np.abs(k[row]), np.ones(cfg.d)), (n, row)
             assert len(set((k[row] * np.sign(x)).tolist())) == 1  # the sign of dA or dB times that of x
         assert not np.delete(k, (5, inter + 5), axis=0).any(), n
+
+
+@pytest.mark.parametrize("samples", [1, 3])
+def test_mi_with_an_infinite_probability(samples):
+    # the sample's joint has no finite normaliser: no cell counts, I = 0, as for an
+    # empty joint; the other samples are untouched
+    rng = np.random.default_rng(9)
+    T, E, B = 90, 16, 4
+    probs = W.random_probs(rng, T, E, 0.5)
+    M, e2b = W.random_soft_scores(rng, T), W.random_bin_map(rng, E, B)
+    off = np.linspace(0, T, samples + 1).astype(np.int32)
+    clean = host(S.mi_loss(t(probs), t(M), t(off), t(e2b), B)[0])
+    probs[2, 5] = np.inf
+    say("MI infinite probability", samples)
+    for grad in (True, False):
+        mi, loss, _ = S.mi_loss(t(probs), t(M), t(off), t(e2b), B, want_grad=grad)
+        torch.cuda.synchronize()
+        assert host(mi)[0] == 0.0 and np.array_equal(host(mi)[1:], clean[1:])
+        assert abs(host(loss)[0] + host(mi).mean()) <= 1e-6
