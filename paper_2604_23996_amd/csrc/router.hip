@@ -291,7 +291,10 @@ __device__ __forceinline__ void softmax_topk_rows(const float (&z)[Q], bool live
             }
         }
     }
+    // a NaN logit is never chosen, and must not stand before the lane's other experts
     uint32_t taken = 0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) taken |= z[q] != z[q] ? 1u << q : 0u;
     int my_i = 0;
     float my_w = 0.0f;
     for (int rr = 0; rr < k; ++rr) {

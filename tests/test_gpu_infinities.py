@@ -1,8 +1,8 @@
-"""Infinities where a kernel's padding, its split of an operand or its order of
-work could turn them into something else: the row-major backward of bf16 layers
-(float32 operands in three bf16 terms) against the float32 layer of the same
-values, the k-packed padding of the packed backward, and the MI of a sample with
-an infinite probability."""
+"""Infinities and NaN where a kernel's padding, its split of an operand or its
+order of work could turn them into something else: the row-major backward of
+bf16 layers (float32 operands in three bf16 terms) against the float32 layer of
+the same values, the k-packed padding of the packed backward, the MI of a
+sample with an infinite probability, and float32 routing past NaN logits."""
 from __future__ import annotations
 
 import dataclasses
@@ -110,3 +110,17 @@ def test_mi_with_an_infinite_probability(samples):
         torch.cuda.synchronize()
         assert host(mi)[0] == 0.0 and np.array_equal(host(mi)[1:], clean[1:])
         assert abs(host(loss)[0] + host(mi).mean()) <= 1e-6
+
+
+@pytest.mark.parametrize("E,k", [(32, 16), (64, 6), (100, 16), (256, 16)])
+def test_route_f32_past_nan_logits(E, k):
+    # experts 0 .. 15 have NaN logits: the choice falls on the best of the others
+    rng = np.random.default_rng(E)
+    T, d = 33, 40
+    x = rng.standard_normal((T, d)).astype(np.float32)
+    w = rng.standard_normal((E, d)).astype(np.float32)
+    best = 16 + np.argsort(-(x.astype(np.float64) @ w[16:].T.astype(np.float64)), axis=1)[:, :k]
+    w[:16] = np.nan
+    say("route f32 NaN", E, k)
+    idx = host(S.route(t(x), t(w), k)["topk_idx"])
+    assert np.array_equal(idx, best)
