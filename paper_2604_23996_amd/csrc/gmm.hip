@@ -118,6 +118,7 @@ gmm_loglik_kernel(const void* __restrict__ x, int64_t T, int d, const uint8_t* _
                   float* __restrict__ resp) {
     constexpr int MC = 2 * K;
     __shared__ double q_s[kGThreads / kWave][NT][MC];
+    __shared__ double c_s[MC];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int lane = lane_id();
     const int64_t blk0 = static_cast<int64_t>(blockIdx.x) * (kGThreads / kWave) * NT;
@@ -125,9 +126,10 @@ gmm_loglik_kernel(const void* __restrict__ x, int64_t T, int d, const uint8_t* _
     int64_t rows[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) rows[t] = tok0 + t < T ? tok0 + t : T - 1;
-    // A lane's partial sums take its parts of sum log sigma^2 - 2 log pi: after the columns in a
-    // short call, which would wait for these loads first; before them in a long one, whose other
-    // waves hide that.
+    // sum log sigma^2 - 2 log pi of each component, by the first wave; added to a token's sum over
+    // the columns at the end, in the same order whatever the call's length. Loaded after the
+    // columns in a short call, which would wait for these loads first, and before them in a long
+    // one, whose other waves hide that.
     // lane j < MC: -2 log pi_mc, pi_mc = N_mc / sum_c N_mc (uniform when the modality has no count)
     auto log_pi = [&] {
         double lp = 0.0;
@@ -144,19 +146,21 @@ gmm_loglik_kernel(const void* __restrict__ x, int64_t T, int d, const uint8_t* _
         for (int b = lane; b < n_part; b += kWave) slv += cst[j * kGMaxParts + b];
         return slv;
     };
-    double acc[NT][MC];
-    if constexpr (NT > 1) {
+    auto constants = [&] {
+        if (wave != 0) return;
         const double lp = log_pi();
 #pragma unroll
         for (int j = 0; j < MC; ++j) {
-            const double slv = constant(j, lp);
-#pragma unroll
-            for (int t = 0; t < NT; ++t) acc[t][j] = slv;
+            const double v = wave_sum_u(constant(j, lp));
+            if (lane == 0) c_s[j] = v;
         }
-    } else {
+    };
+    if constexpr (NT > 1) constants();
+    double acc[NT][MC];
 #pragma unroll
-        for (int j = 0; j < MC; ++j) acc[0][j] = 0.0;
-    }
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int j = 0; j < MC; ++j) acc[t][j] = 0.0;
     // the rows' next S stripes of 512 columns (8 per lane) are loaded before any is used
     constexpr int S = BF16 ? 4 : 2;
     constexpr int Q = BF16 ? 1 : 2;
@@ -208,11 +212,7 @@ gmm_loglik_kernel(const void* __restrict__ x, int64_t T, int d, const uint8_t* _
         }
       }
     }
-    if constexpr (NT == 1) {
-        const double lp = log_pi();
-#pragma unroll
-        for (int j = 0; j < MC; ++j) acc[0][j] += constant(j, lp);
-    }
+    if constexpr (NT == 1) constants();
     // lane partials -> per (token, component) sums by a fixed butterfly; then one
     // lane per token of the block turns them into its result (the float64
     // logarithms and exponentials cost a wave the same for one token as for 64)
@@ -228,7 +228,7 @@ gmm_loglik_kernel(const void* __restrict__ x, int64_t T, int d, const uint8_t* _
     if (threadIdx.x >= (kGThreads / kWave) * NT || j >= T) return;
     double ll[MC];
 #pragma unroll
-    for (int c = 0; c < MC; ++c) ll[c] = -0.5 * q_s[threadIdx.x / NT][threadIdx.x % NT][c];
+    for (int c = 0; c < MC; ++c) ll[c] = -0.5 * (q_s[threadIdx.x / NT][threadIdx.x % NT][c] + c_s[c]);
     if (mode == 0) {
         double lse[2];
 #pragma unroll
