@@ -218,8 +218,7 @@ attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, 
         // this wave's loads of block b have landed; behind the barrier every wave's
         // have, and every wave is done reading the other buffer
         wait_vm_lgkm0<0>();
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");  // no LDS read moves above the barrier
+        dma_barrier();
         if (b + 1 < nkb) load_block((b + 1) & 1, kb0 + AT_BK);
         if (kb0 > wk_hi || kb0 + AT_BK <= wk_lo) continue;  // uniform; the barriers are above
         // LDS addresses are rebuilt inside the loop from an opaque zero: hoisting

@@ -396,7 +396,7 @@ dg_mfma_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ Pz, 
     // the barrier frees the slot that slice n + 2 then overwrites.
     for (int n = 0; n < nks; ++n) {
         wait_vm_lgkm0<ND>();
-        __builtin_amdgcn_s_barrier();
+        dma_barrier();
         issue(n + 2, slot == 0 ? 2 : slot - 1);
         const uint8_t* base = lds + slot * SLOT;
         // x: token 8 (lane / 32) + r of the slice, columns c0 + 2 (lane % 32) and + 1

@@ -198,6 +198,15 @@ __device__ __forceinline__ void dma4(i32x4_t rsrc, int voff, uint32_t lds) {
                  : "memory");
 }
 
+// The workgroup barrier of the kernels that use these loads: the compiler knows
+// neither that they write LDS nor that the barrier orders them, so no memory
+// access may move across it in either direction.
+__device__ __forceinline__ void dma_barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
 // Values that are the same in every lane but that the compiler cannot prove
 // uniform (they derive from loads): pin them to SGPRs so buffer descriptors
 // built from them stay scalar.

@@ -756,6 +756,10 @@ gemm_bf16_pk_kernel(GemmArgs p) {
     // Past the end of K the loads go out of range and return zeros, so every
     // stage issues the same count and the waits stay exact.
     const int nk = static_cast<int>(ceil_div(K, BK));
+    auto barrier = [] {
+        if constexpr (MODE == 5) dma_barrier();  // its loads are inline assembly
+        else __builtin_amdgcn_s_barrier();
+    };
     auto kloop = [&](auto mt_c) {
         i32x4_t b1[2][4];
 #pragma unroll
@@ -766,17 +770,17 @@ gemm_bf16_pk_kernel(GemmArgs p) {
         int s = 0, slot = 0;
         for (; s + 2 <= nk; s += 2) {
             wait_vm_lgkm0<12>();
-            __builtin_amdgcn_s_barrier();
+            barrier();
             stage_run(mt_c, slot, s, b0, b1);
             slot = slot == 2 ? 0 : slot + 1;
             wait_vm_lgkm0<12>();
-            __builtin_amdgcn_s_barrier();
+            barrier();
             stage_run(mt_c, slot, s + 1, b1, b0);
             slot = slot == 2 ? 0 : slot + 1;
         }
         if (s < nk) {
             wait_vm_lgkm0<12>();
-            __builtin_amdgcn_s_barrier();
+            barrier();
             stage_run(mt_c, slot, s, b0, b1);
         }
     };
@@ -786,7 +790,7 @@ gemm_bf16_pk_kernel(GemmArgs p) {
     else if (trows > 32) kloop(std::integral_constant<int, 2>{});
     else kloop(std::integral_constant<int, 1>{});
     wait_vm_lgkm0<0>();  // drain: the epilogue reuses the ring
-    __builtin_amdgcn_s_barrier();
+    barrier();
 
     // Epilogue through LDS: [BM][TC + 8] bf16 tile, then 16-byte row chunks.
     // The accumulators hold transposed 16x16 tiles: element e of lane l of

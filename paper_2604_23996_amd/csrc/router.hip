@@ -213,8 +213,7 @@ router_logits_kernel(const uint16_t* __restrict__ x, int64_t T, int d, const uin
     auto step = [&](int t, const bf16x8_t (&cur)[NF], bf16x8_t (&nxt)[NF]) {
         const int rest = nk - 2 - t;
         wait_later(rest < ST - 2 ? rest : ST - 2);
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");  // no LDS read moves above the barrier
+        dma_barrier();
         if (t + ST < nk) issue(t + ST);
         __builtin_amdgcn_sched_barrier(0);
         read_frags(t + 1, nxt);
@@ -230,8 +229,7 @@ router_logits_kernel(const uint16_t* __restrict__ x, int64_t T, int d, const uin
     const int pro = nk < ST ? nk : ST;
     for (int t = 0; t < pro; ++t) issue(t);
     wait_later(pro - 1);
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
+    dma_barrier();
     bf16x8_t fa[NF], fb[NF];
     read_frags(0, fa);
     int t = 0;

@@ -356,35 +356,35 @@ wgrad_pk_kernel(WpArgs p) {
             if (nk > 0) {
                 if (after_stores) wait_vm_lgkm0<12 + kStoresPerTile>();
                 else wait_vm_lgkm0<12>();
-                __builtin_amdgcn_s_barrier();
+                dma_barrier();
                 stage_run(cur, 0, 0, b0, b1, ie, io);
             }
             if (nk > 1) {
                 if (after_stores) wait_vm_lgkm0<12 + kStoresPerTile>();
                 else wait_vm_lgkm0<12>();
-                __builtin_amdgcn_s_barrier();
+                dma_barrier();
                 stage_run(cur, 1, 1, b1, b0, io, ie);
             }
             s = 2;
             slot = 2;
             for (; s + 2 <= nk; s += 2) {
                 wait_vm_lgkm0<12>();
-                __builtin_amdgcn_s_barrier();
+                dma_barrier();
                 stage_run(cur, slot, s, b0, b1, ie, io);
                 slot = slot == 2 ? 0 : slot + 1;
                 wait_vm_lgkm0<12>();
-                __builtin_amdgcn_s_barrier();
+                dma_barrier();
                 stage_run(cur, slot, s + 1, b1, b0, io, ie);
                 slot = slot == 2 ? 0 : slot + 1;
             }
             if (s < nk) {
                 wait_vm_lgkm0<12>();
-                __builtin_amdgcn_s_barrier();
+                dma_barrier();
                 stage_run(cur, slot, s, b0, b1, ie, io);
             }
         }
         wait_vm_lgkm0<0>();  // drain: the next tile's DMA reuses the ring
-        __builtin_amdgcn_s_barrier();
+        dma_barrier();
         // output of this tile, then the next tile's first two stages
         const int og = cur.g, om0 = cur.m0, on0 = cur.n0;
         if (nb < hi) {
