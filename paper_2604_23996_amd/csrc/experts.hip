@@ -1074,6 +1074,7 @@ gemm_bf16_pk_kernel(GemmArgs p) {
 // fragment, 64 bytes of each of 16 rows per wave load: 278 us for 64 gate / up
 // matrices of 2816 x 2048, now 246, 6 TB/s.)
 constexpr int kPackCols = 512;
+typedef uint32_t pack_src4_t __attribute__((ext_vector_type(4), aligned(2)));  // the source may start at any element
 constexpr int64_t kPackBlocks = 1 << 22;  // a launch holds fewer than 2^32 threads
 __global__ void __launch_bounds__(256)
 pack_rows_kernel(const uint16_t* __restrict__ src, unsigned items, int n, int k, int interleave,
@@ -1092,15 +1093,17 @@ pack_rows_kernel(const uint16_t* __restrict__ src, unsigned items, int n, int k,
         const int r0 = interleave ? (g / 4) * 32 + ((g / 2) % 2) * 16 : g * 16;  // of the half
         const int base = interleave ? (g % 2) * n : 0;
         const int col = c0 + lane * 8;
-        uint4 v[4];
+        pack_src4_t v[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int r = r0 + wave * 4 + i;
-            v[i] = r < n && col < k ? *reinterpret_cast<const uint4*>(src + (b * src_rows + base + r) * k + col)
-                                    : make_uint4(0, 0, 0, 0);
+            v[i] = r < n && col < k
+                       ? *reinterpret_cast<const pack_src4_t*>(src + (b * src_rows + base + r) * k + col)
+                       : pack_src4_t{};
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) *reinterpret_cast<uint4*>(&tile[wave * 4 + i][lane * 8]) = v[i];
+        for (int i = 0; i < 4; ++i)
+            *reinterpret_cast<uint4*>(&tile[wave * 4 + i][lane * 8]) = make_uint4(v[i].x, v[i].y, v[i].z, v[i].w);
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < kPackCols / 32 / 4; ++i) {
@@ -1121,7 +1124,6 @@ pack_rows_kernel(const uint16_t* __restrict__ src, unsigned items, int n, int k,
 // 246.)
 __global__ void __launch_bounds__(256)
 pack_cols_kernel(const uint16_t* __restrict__ src, unsigned items, int n, int k, uint16_t* __restrict__ dst) {
-    typedef uint32_t v4_t __attribute__((ext_vector_type(4), aligned(2)));  // the source may start at any element
     constexpr int P = kPackCols + 16;  // row pitch = 8 mod 64 dwords
     __shared__ __attribute__((aligned(16))) uint16_t tile[32 * P];
     const int ng = 2 * ((n + 31) / 32);  // 16-column groups
@@ -1133,11 +1135,11 @@ pack_cols_kernel(const uint16_t* __restrict__ src, unsigned items, int n, int k,
         const int64_t b = item / kc_n / nc;
         const int n0 = static_cast<int>(item / kc_n % nc) * kPackCols;
         const int col = n0 + lane * 8;
-        v4_t v[8];
+        pack_src4_t v[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int kk = c * 32 + wave * 8 + i;
-            v[i] = kk < k && col < n ? *reinterpret_cast<const v4_t*>(src + (b * k + kk) * n + col) : v4_t{};
+            v[i] = kk < k && col < n ? *reinterpret_cast<const pack_src4_t*>(src + (b * k + kk) * n + col) : pack_src4_t{};
         }
 #pragma unroll
         for (int i = 0; i < 8; ++i)
