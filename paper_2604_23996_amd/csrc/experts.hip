@@ -188,7 +188,6 @@ __device__ __forceinline__ uint4 as_uint4(i32x4_t v) {
 struct GemmArgs {
     int64_t T;
     int d, E, k, inter, shared_inter;
-    int packed;  // expert weights in the fragment order of pack_weights_kernel
     int part;    // work items of this launch: 0 all, 1 routed, 2 shared
     const void* x;
     const void* w13;
@@ -1736,7 +1735,6 @@ GemmArgs make_args(const ExpertArgs& a, const ExpWs& w, const int32_t* work, int
     g.k = a.k;
     g.inter = a.inter;
     g.shared_inter = a.shared_inter;
-    g.packed = a.packed;
     g.x = a.x;
     g.w13 = a.w13;
     g.w2 = a.w2;
