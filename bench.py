@@ -667,7 +667,7 @@ def main():
             "tokens_per_s": round(cfg.T / ((fm + bm) * 1e-3), 1),
             "backward_tflops": round(bwd_flops / (bm * 1e-3) / 1e12, 2),
             # the packed path's matrix cores against the dense bf16 peak; the float32
-            # FMA path (fp32 layers, row-major bf16 weights) against the fp32 vector peak
+            # path (fp32 layers, row-major bf16 weights) against the fp32 vector peak
             "backward_peak_tflops": bwd_peak,
             "backward_frac_peak": round(bwd_flops / (bm * 1e-3) / 1e12 / bwd_peak, 4)}
         del packed_t, grads, bws_t, ws_tr

@@ -525,14 +525,16 @@ size_t smoes_backward_workspace_bytes(const smoes_layer* desc);
  * read for bf16 layers with packed weights only (may be NULL otherwise).
  * Two paths: bf16 layers with packed weights run matrix-core GEMMs with bf16
  * operands and bf16 intermediates; fp32 layers and bf16 layers with
- * row-major weights run float32 FMA tiles with float32 intermediates, every
- * step on `stream` (io->streams is not used there). The expert weight
- * gradients are in act_dtype; dx, dw_gate and the logit gradient float32.
+ * row-major weights run row-major matrix-core tiles with float32 products,
+ * sums and intermediates, every step on `stream` (io->streams is not used
+ * there). The expert weight gradients are in act_dtype; dx, dw_gate and the
+ * logit gradient float32.
  * SMOES_ERR_SHAPE (packed path) when 4 T k inter or 4 T shared_inter exceeds
- * INT32_MAX bytes, or a k-packed operand copy (2 (T k + 15 E) max(d, 2 inter)
- * bytes, or 2 T max(d, 2 shared_inter) for the shared experts) would;
- * SMOES_ERR_WORKSPACE when either workspace is NULL or
- * smaller than smoes_workspace_bytes / smoes_backward_workspace_bytes;
+ * INT32_MAX, or 2 (T k + 15 E) max(d, 2 inter), or with shared experts
+ * 2 T max(d, 2 shared_inter), does (columns rounded up to 32, tokens to 16):
+ * a bound on the k-packed operands' bytes; SMOES_ERR_WORKSPACE when either
+ * workspace is NULL or smaller than smoes_workspace_bytes /
+ * smoes_backward_workspace_bytes;
  * SMOES_ERR_ARG for a NULL pointer that is needed. Differentiates the layer
  * output of Sec. 3.1 (softmax router, top-k combine, SwiGLU experts plus the
  * shared experts). Sums run in a fixed order: results are reproducible.

@@ -548,7 +548,7 @@ int smoes_check_inputs(const smoes_layer* L, const smoes_layer_io* io, int32_t* 
 // ------------------------------------------------------------------ layer backward
 
 namespace {
-// fp32 layers and bf16 layers with row-major weights take the float32 FMA backward
+// fp32 layers and bf16 layers with row-major weights take the row-major backward (float32 intermediates)
 bool generic_bwd(const smoes_layer* L) { return L->act_dtype != SMOES_BF16 || !L->weights_packed; }
 // routed rows (T k) from which the packed backward runs on the caller's stream alone
 constexpr int64_t kBwdOverlapRows = 65536;
@@ -624,12 +624,13 @@ int smoes_moe_backward(const smoes_layer* L, const smoes_layer_io* io, const voi
     if (st != SMOES_OK) return st;
     if (io == nullptr || G == nullptr) return SMOES_ERR_ARG;
     const bool gen = generic_bwd(L);
-    // dX = [dA dB] W13 of the packed path reads its A operand (2 inter columns
-    // per row) through a buffer descriptor with 32-bit byte offsets
+    // The packed path addresses an expert's k-packed rows (w H, [dA dB]) through
+    // buffer descriptors with 32-bit byte offsets, x and dout likewise. These two
+    // bounds take all experts' rows together, and the second d columns as well:
+    // stricter than the kernels need, kept as the limit of what a call may ask for.
     if (!gen && (2 * L->T * L->k * 2 * static_cast<int64_t>(L->inter) > INT32_MAX ||
                  2 * L->T * 2 * static_cast<int64_t>(L->shared_inter) > INT32_MAX))
         return SMOES_ERR_SHAPE;
-    // the k-packed weight-gradient operands are read with 32-bit byte offsets as well
     if (!gen) {
         const int64_t kr = kpad_routed(L), ks = kpad_shared(L);
         const int wide = L->d > 2 * L->inter ? L->d : 2 * L->inter;

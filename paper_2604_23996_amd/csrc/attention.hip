@@ -62,8 +62,10 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
 
 // DMA: K and V start on 16-byte boundaries, as the buffer-to-LDS loads want them;
 // at any other start the rows go through registers (not pipelined: correct, slower).
-// Heads of 64 fit three waves per SIMD (with the order below 96 -> 77 us for 7000
-// tokens in five samples, 32 heads over 8).
+// Heads of 64 fit three waves per SIMD. (7000 tokens in five samples, 32 heads of 64
+// over 8, with attn_update_kernel: 166 us with rows staged through registers, query
+// blocks by half of the heads and two waves, now 115. All times in this file: passes one
+// after another, each on other inputs than the last.)
 template <int DH, bool DMA>
 __global__ void __launch_bounds__(AT_THREADS)
 __attribute__((amdgpu_waves_per_eu(DH == 128 ? 2 : 3, DH == 128 ? 2 : 3)))
@@ -81,8 +83,9 @@ attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, 
     // consecutive keys), V rows in 64-byte groups of chunks by the key's low bits
     // (the transposing reads take 64 bytes of each of 8 keys). Against rows staged
     // through registers into one padded buffer, two barriers per block: 178 -> 170
-    // us for 7000 tokens in five samples, 32 heads of 128 over 8 KV heads (with
-    // attn_update_kernel).
+    // us for 7000 tokens in five samples, 32 heads of 128 over 8 KV heads, with
+    // attn_update_kernel (215 before the score channels became matrix products, 163
+    // with the order below).
     constexpr int RB = DH * 2;                    // row bytes
     constexpr int KV_BYTES = AT_BK * RB;
     constexpr int RPI = 1024 / RB;                // rows per load instruction
@@ -102,10 +105,10 @@ attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, 
     // Where several samples make a few rounds of blocks (two per CU at a time),
     // they run longest first over all samples instead, so that the launch ends
     // evenly: every block ranks them for itself from the sample offsets in LDS,
-    // one thread per query block. Attention and update in us, from the last down
-    // / ranked: 512 blocks of 2 samples 75 / 61, 1760 of 5 130 / 123, 1024 of 4
-    // 199 / 181; but 128 blocks of 2 15.7 / 16.2 and 4096 of 16, without grouped
-    // heads, 232 / 263.
+    // one thread per query block. Attention and update in us, heads of 128, from
+    // the last down / ranked: 512 blocks of 2 samples 57.6 / 52.1, 1024 of 4 (4096
+    // tokens) 92.5 / 85.5, 1760 of 5 164.8 / 161.9, 2048 of 8 164.1 / 162.5; but 128
+    // blocks of 2 23.2 / 23.6 and 4096 of 16 314 / 322, without grouped heads 319 / 344.
     const bool ranked = n_batch > 1 && n_batch <= AT_THREADS && nqb <= AT_THREADS && gridDim.x > 256 && gridDim.x <= 2048;
     int qb = static_cast<int>(blockIdx.x) / H;
     if (ranked) {

@@ -1169,7 +1169,9 @@ pack_cols_kernel(const uint16_t* __restrict__ src, unsigned items, int n, int k,
 // own tensors (x, dout, the weights) are exact bf16 operands, and a float32
 // intermediate (dA dB, w H) enters as three bf16 terms cut off its mantissa (8
 // bits each: their sum is the float32 value), so every product is exact and
-// only the float32 accumulation rounds, as on the vector ALUs. Steps:
+// only the float32 accumulation rounds, as on the vector ALUs. (The matrix cores
+// take bf16 operands below 2^-126 for zero: a value loses its third term below
+// about 2^-110, an absolute error under 2^-125.) Steps:
 //   RM_FW1  H = silu(X W1^T) * (X W3^T)          rows: routed rows (x gathered) / tokens
 //   RM_FW2  Y = H W2^T
 //   GB_AB   [A | B] = X W13^T

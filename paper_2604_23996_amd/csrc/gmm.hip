@@ -18,8 +18,8 @@
 //     coefficients of the new state, as gmm_prep does for the old one.
 // At 8192 x 2048 bf16 and K = 2 (33.6 MB) an update and a score take 4 + 18 + 18
 // + 10 + 16 us, bound by latency and by the address unit (the coefficients come
-// through L1 once per wave, so a wave takes four tokens). Before, 5 + 27 + 42 +
-// 21 + 5 + 25: gmm_partial read every row's label before it loaded the row, once
+// through L1 once per wave, so a wave takes four tokens, from 4096 tokens on).
+// Before, 5 + 27 + 42 + 21 + 5 + 25: gmm_partial read every row's label before it loaded the row, once
 // per modality, and its LDS tree had all lanes on one bank; gmm_merge walked
 // 128 chunks with 8 loads in flight; gmm_loglik kept one 512-column stripe of
 // two rows in flight and ran its float64 logarithms once per wave.
@@ -36,8 +36,9 @@ constexpr int kGMergeCols = 64;     // columns per gmm_merge block
 constexpr int kGMergeGroups = 8;    // chunk groups per column
 constexpr int kGMaxParts = 256;     // SMOES_D_MAX / kGMergeCols: parts of a log-variance sum
 // tokens per gmm_loglik wave: 4, or 1 where those would not give every CU a
-// block: a wave's chain of columns is then shorter (score of 2 tokens x 2048, K = 3:
-// 31.1 -> 20.8 us, with the weights and log-variances loaded after the columns)
+// block: a wave's chain of columns is then shorter. EM step and score with K = 2, four /
+// one per wave in us: 64 tokens x 2048 37.7 / 31.8, 3072 48.4 / 45.1, 4095 50.6 / 51.0,
+// 6000 57.5 / 64.3; x 4096: 2048 tokens 58.0 / 49.7, 3072 61.5 / 62.7, 6000 81.0 / 104.9
 constexpr int kGTokPerWave = 4;
 constexpr int64_t kGTokFill = 256 * 4 * kGTokPerWave;
 constexpr int kGThreads = 256;

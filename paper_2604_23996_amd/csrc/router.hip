@@ -50,7 +50,10 @@ __host__ __device__ constexpr int router_ring(int ne) {
 // KS ranges of the hidden dimension of `steps` 32-wide k-steps each (the last
 // may be shorter): about one workgroup per CU, each range at least 8 k-steps.
 // The count is part of the logits' bits (the partial sums round to float32 per
-// range), so a change of it turns the choice of near-tied experts.
+// range), so a change of it turns the choice of near-tied experts: two workgroups
+// per CU for up to 64 experts, whose rings fit a CU twice, route 8000 x 2048 in
+// 24.4 us against 25.6, but four ranges instead of two turned one choice of 98304 at
+// 16384 x 2048.
 struct RouterPlan {
     int ks, steps;
 };

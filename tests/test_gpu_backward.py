@@ -20,8 +20,8 @@ their gradients, H and each routed row's dX in bf16, relative rounding
 plus an elementwise bar of 6e-2 x max|ref| on every gradient (no single
 element far off while the norm is fine).
 
-fp32 layers and bf16 layers with row-major weights take the float32 FMA
-backward (float32 intermediates). For fp32 layers every stored value is
+fp32 layers and bf16 layers with row-major weights take the row-major
+backward (float32 products, sums and intermediates). For fp32 layers every stored value is
 float32 and each gradient entry is a float32 sum of at most a few thousand
 products, so the normwise error is a small multiple of the unit roundoff
 6e-8 amplified by the cancellation in the sum: bars 1e-5 (dbias, a column
