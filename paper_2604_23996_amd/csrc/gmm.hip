@@ -16,8 +16,8 @@
 //     the chunks in a fixed order, applies Eq. 5-7 with the weighted batch
 //     count, mean and centred sum of squares, and writes the score's
 //     coefficients of the new state, as gmm_prep does for the old one.
-// At 8192 x 2048 bf16 and K = 2 (33.6 MB) an update and a score take 4 + 18 + 18
-// + 10 + 16 us, bound by latency and by the address unit (the coefficients come
+// At 8192 x 2048 bf16 and K = 2 (33.6 MB) an update and a score take 4 + 15 + 18
+// + 10 + 17 us, bound by latency and by the address unit (the coefficients come
 // through L1 once per wave, so a wave takes four tokens, from 4096 tokens on).
 // Before, 5 + 27 + 42 + 21 + 5 + 25: gmm_partial read every row's label before it loaded the row, once
 // per modality, and its LDS tree had all lanes on one bank; gmm_merge walked
