@@ -95,7 +95,8 @@ size_t smoes_route_workspace_size(int64_t T, int d, int E, int x_dtype);
  * logits     [T, E] float32 output, or NULL (not stored).
  * probs      [T, E] float32 output: the full softmax over all E experts.
  * topk_idx   [T, k] int32 output: experts by descending logit, ties to the
- *            lower index (decided on the float32 logits).
+ *            lower index (decided on the float32 logits); experts whose
+ *            logit is NaN come last, lower index first.
  * topk_w     [T, k] float32 output: combine weights.
  * Shapes: 1 <= d <= SMOES_D_MAX, d % 8 == 0; 1 <= E <= SMOES_E_MAX;
  *         1 <= k <= min(E, SMOES_K_MAX); for SMOES_BF16, T * d * 2 < 2^31.

@@ -292,10 +292,12 @@ __device__ __forceinline__ void softmax_topk_rows(const float (&z)[Q], bool live
             }
         }
     }
-    // a NaN logit is never chosen, and must not stand before the lane's other experts
-    uint32_t taken = 0;
+    // a NaN logit must not stand before the lane's other experts: it is chosen only when the token
+    // has fewer than k without one (the lowest first), so that every index is an expert
+    uint32_t nans = 0;
 #pragma unroll
-    for (int q = 0; q < Q; ++q) taken |= z[q] != z[q] ? 1u << q : 0u;
+    for (int q = 0; q < Q; ++q) nans |= z[q] != z[q] ? 1u << q : 0u;
+    uint32_t taken = nans;
     int my_i = 0;
     float my_w = 0.0f;
     for (int rr = 0; rr < k; ++rr) {
@@ -310,8 +312,13 @@ __device__ __forceinline__ void softmax_topk_rows(const float (&z)[Q], bool live
             }
         }
         const float gm = row_allreduce(bi == 0x7fffffff ? -INFINITY : bv, [](float a, float b) { return fmaxf(a, b); });
-        const int gi = row_allreduce(bi != 0x7fffffff && bv == gm ? bi : 0x7fffffff,
-                                     [](int a, int b) { return a < b ? a : b; });
+        int gi = row_allreduce(bi != 0x7fffffff && bv == gm ? bi : 0x7fffffff,
+                               [](int a, int b) { return a < b ? a : b; });
+        if (gi == 0x7fffffff) {  // uniform in the row
+            gi = row_allreduce(nans != 0 ? l16 + 16 * __builtin_ctz(nans) : 0x7fffffff,
+                               [](int a, int b) { return a < b ? a : b; });
+            if ((gi & 15) == l16) nans &= nans - 1;
+        }
         if ((gi & 15) == l16) taken |= 1u << (gi >> 4);
         if (l16 == rr) {
             my_i = gi;

@@ -2,7 +2,7 @@
 order of work could turn them into something else: the row-major backward of
 bf16 layers (float32 operands in three bf16 terms) against the float32 layer of
 the same values, the k-packed padding of the packed backward, the MI of a
-sample with an infinite probability, and float32 routing past NaN logits."""
+sample with an infinite probability, and routing past NaN logits."""
 from __future__ import annotations
 
 import dataclasses
@@ -124,3 +124,43 @@ def test_route_f32_past_nan_logits(E, k):
     say("route f32 NaN", E, k)
     idx = host(S.route(t(x), t(w), k)["topk_idx"])
     assert np.array_equal(idx, best)
+
+
+@pytest.mark.parametrize("dtype", [W.BF16, W.F32])
+@pytest.mark.parametrize("E,k", [(4, 4), (20, 6), (100, 16), (256, 16)])
+def test_route_with_too_few_logits_that_are_numbers(E, k, dtype):
+    # three experts have a number and the others, by their bias, NaN; three tokens are NaN
+    # altogether: numbers by value first, then the lowest of the rest, each expert once
+    rng = np.random.default_rng(E + k)
+    T, d = 37, 40
+    x = rng.standard_normal((T, d)).astype(np.float32)
+    w = rng.standard_normal((E, d)).astype(np.float32)
+    bad = [0, 17, 36]
+    x[bad, 3] = np.nan
+    xd = W.f32_to_bf16_bits(x) if dtype == W.BF16 else x
+    good = np.sort(rng.permutation(E)[:3])
+    bias = np.full(E, np.nan, np.float32)
+    bias[good] = 0
+    say("route too few numbers", E, k, dtype)
+    idx = host(S.route(t(xd), t(w), k, t(bias))["topk_idx"])
+    xf = W.bf16_bits_to_f32(xd) if dtype == W.BF16 else x
+    z = xf.astype(np.float64) @ w[good].T.astype(np.float64)
+    rest = np.setdiff1d(np.arange(E), good)
+    for j in range(T):
+        want = np.arange(k) if j in bad else np.concatenate([good[np.argsort(-z[j])], rest])[:k]
+        assert np.array_equal(idx[j], want), j
+
+
+def test_layer_with_a_nan_token():
+    # the token's rows go to the first experts; every other token's output keeps its bits
+    cfg, inp, _, _ = _inputs(CASE, 751)
+    say("layer NaN token")
+    clean = run_gpu_layer(inp)[2]
+    x = inp.x.copy()
+    x[9, 5] = 0x7FC0
+    o = run_gpu_layer(dataclasses.replace(inp, x=x))[2]
+    assert np.array_equal(host(o["topk_idx"])[9], np.arange(cfg.k))
+    keep = np.arange(cfg.T) != 9
+    for n in ("topk_idx", "topk_w", "probs", "out"):
+        assert np.array_equal(host(o[n])[keep], host(clean[n])[keep]), n
+    assert np.isnan(host(o["out"])[9]).all()
